@@ -11,7 +11,7 @@
 // (instance, first interval or node, kind): a Jacobian column over
 // `block * npt` intervals, a Hessian, gradient or variable-row KKT run of
 // `block` nodes, a defect run of 63 intervals per wavefront, an objective
-// group of 256 nodes, a defect-row KKT run of 16 intervals, or an instance's
+// group of 256 nodes, a defect-row KKT run of 16-64 intervals, or an instance's
 // boundary rows.  One list per evaluation mask, instance-major (an instance's
 // tiles together, so the workgroups in flight share the state rows they read).
 // The per-lane arithmetic is the single-instance path's (ocp_device.h,
@@ -132,8 +132,12 @@ __device__ __forceinline__ void jac_cols(const KP &P, const double *z, double *j
 // struct the compiler cannot tell that the tile list, the offset table and
 // the coefficients are never written, and loads them per lane instead of
 // through the scalar cache (14 % slower on the Jacobian/Hessian tiles).
+// The defect-row KKT tiles wait on each tile's descriptors and loads, so more
+// of them in flight help: held to 7 wavefronts per SIMD (71 VGPRs against 73)
+// they take 1.10 ms against 1.17 for 512 instances, n = 6, m = 3 (at 8 the
+// registers spill).
 template <int NB, int BS, int KINDS, int SCHEME>
-__global__ __launch_bounds__(BS) void batch_kernel(BP bp, KKTLayout Lo, const InstDesc *__restrict__ inst,
+__global__ __launch_bounds__(BS, KINDS == kListKktDef ? 7 : 1) void batch_kernel(BP bp, KKTLayout Lo, const InstDesc *__restrict__ inst,
                                                    const TileDesc *__restrict__ tiles, int ntiles, int what,
                                                    bool pair_ok, const double *__restrict__ z_,
                                                    const double *__restrict__ y_, const double *__restrict__ reg_,
@@ -147,7 +151,9 @@ __global__ __launch_bounds__(BS) void batch_kernel(BP bp, KKTLayout Lo, const In
     __shared__ double ws[4];          // objective sums
     const int tid = threadIdx.x;
     for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        const TileDesc td = tiles[t];
+        // the KKT tiles of an instance share lines with their neighbours, so
+        // each XCD takes a contiguous run of them (see xcd_order)
+        const TileDesc td = tiles[KINDS & (kListKktDef | kListKktVar) ? xcd_order(t, ntiles) : t];
         const InstDesc id = inst[td.b];
         const KP P = make_kp<SCHEME>(bp, id, td.b);
         const double *zb = z_ + id.z_off;
@@ -709,7 +715,9 @@ int ocp_batch_create_ex(int32_t count, const int64_t *Ns, int32_t n, int32_t m, 
     b->bp.S = shape.S;
     b->bp.scheme = scheme;
     b->bp.nb = (int)shape.nb;
-    b->bp.defect_lg = __builtin_ctz((unsigned)kkt_defect_kt(n, m, shape.T));
+    int64_t intervals = 0;
+    for (int64_t N : b->Ns) intervals += N;
+    b->bp.defect_lg = __builtin_ctz((unsigned)kkt_defect_kt(n, m, shape.T, intervals));
     b->bp.A = b->coef;
     b->bp.B = b->coef + nA;
     b->bp.gam = b->bp.B + nB;

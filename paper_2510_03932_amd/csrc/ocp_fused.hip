@@ -10,14 +10,15 @@
 // the COO kernels and the assembly.  The tile bodies (ocp_step_device.h) are
 // shared with the batched evaluation.
 //
-// Defect rows: workgroup b owns intervals [b KT, b KT + KT), KT = 16, 32 or
-// 64 so that one row block (KT rows of T+1 entries) holds 500 to 1000 values.
+// Defect rows: a workgroup owns KT = 16, 32 or 64 consecutive intervals
+// (kkt_defect_kt); each XCD takes a contiguous run of the tiles, so that the
+// lines neighbouring tiles share (states read, rows stored) meet in one L2.
 // It stages the states and their cosines at the KT+1 nodes, the rows'
 // regularization and the scaled coefficients -hh A, -hh B, -hh gamma in LDS
 // (a wavefront spans several slots of a row, so coefficient reads from global
 // memory would be per-lane loads, each waited for); then, for each state
 // component i, it computes the tile's KT rows (T Jacobian entries and the
-// diagonal each) slot by slot into an LDS tile and writes the rows'
+// diagonal each) column by column into an LDS tile and writes the rows'
 // contiguous CSR range with full-line stores.
 // Variable rows: one lane per node computes the node's Hessian values (+ reg
 // on the diagonals), as in eval_hess; each state block's rows of the
@@ -42,7 +43,7 @@ __global__ __launch_bounds__(kBlock) void kkt_defect_kernel(KP P, KKTLayout Lo, 
                                                             double *__restrict__ kkt)
 {
     extern __shared__ double lds[];
-    kkt_defect_tile<kBlock>(P, Lo, z, reg, kkt, (int64_t)blockIdx.x << LG, LG, lds);
+    kkt_defect_tile<kBlock>(P, Lo, z, reg, kkt, (int64_t)xcd_order(blockIdx.x, gridDim.x) << LG, LG, lds);
 }
 
 template <int NB>
@@ -52,7 +53,7 @@ __global__ __launch_bounds__(kBlock) void kkt_var_kernel(KP P, KKTLayout Lo, con
                                                          double *__restrict__ kkt)
 {
     __shared__ double buf[3 * kBlock];  // one state block's rows of this workgroup (<= 3 entries each)
-    kkt_var_tile<NB, kBlock>(P, Lo, z, y, sigma, reg, kkt, (int64_t)blockIdx.x * kBlock, buf);
+    kkt_var_tile<NB, kBlock>(P, Lo, z, y, sigma, reg, kkt, (int64_t)xcd_order(blockIdx.x, gridDim.x) * kBlock, buf);
 }
 
 // Boundary rows: their state entry (1) and their diagonal.
@@ -76,7 +77,7 @@ hipError_t launch_eval_kkt(const KP &P, const double *z, const double *y, double
     // defect-row tiles of KT = 2^LG intervals; LDS holds the tile's states,
     // their cosines, the rows' regularization, the scaled coefficients and the
     // output row block
-    const int KT = kkt_defect_kt(P.n, P.m, P.T);
+    const int KT = kkt_defect_kt(P.n, P.m, P.T, P.N);
     const int LG = __builtin_ctz((unsigned)KT);
     const size_t lds = kkt_defect_lds(P.n, P.m, P.T, KT) * sizeof(double);
     hipLaunchKernelGGL(kkt_defect_kernel, dim3(blocks_for(P.N, KT)), dim3(kBlock), lds, stream, P, Lo, LG, z, reg,

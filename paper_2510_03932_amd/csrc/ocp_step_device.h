@@ -190,8 +190,8 @@ __device__ __forceinline__ int64_t kkt_bnd_start(const KP &P, const KKTLayout &L
 }
 
 // Defect-row tiles: KT intervals per tile (a power of two, 16 to 64), chosen
-// per problem by kkt_defect_kt; each row block is computed slot-major into an
-// LDS tile and copied out (see kkt_defect_tile).
+// per problem by kkt_defect_kt; each row block is computed column by column
+// into an LDS tile and copied out (see kkt_defect_tile).
 constexpr int kDefectKTMax = 64;
 constexpr size_t kDefectLdsMax = 64 * 1024;  // bytes of LDS a tile may take
 
@@ -203,58 +203,71 @@ inline size_t kkt_defect_lds(int n, int m, int T, int KT)
     return 2 * (size_t)n * (KT + 1) + (size_t)n * KT + (size_t)n * (n + m) + (size_t)n + (size_t)KT * (T + 1);
 }
 
-// Intervals per defect-row tile: a row block of KT (T+1) entries of about 500
-// to 1000 doubles (measured best at n = 16, m = 8: KT = 16, 784 entries; at
-// n = 6, m = 3: KT = 32, 608 entries), within the LDS bound.
-inline int kkt_defect_kt(int n, int m, int T)
+// Intervals per defect-row tile, for `intervals` of them in all (a batch's
+// instances together): 64 while that leaves at least kDefectTiles tiles and
+// the tile fits the LDS bound, else 32 or 16.  A tile of 64 is the best of
+// 16, 32 and 64 or within 1 % of it at n = 6, m = 3 (0.359 ms against 0.383
+// and 0.43 at N = 2e6), n = 12, m = 5 (0.232 against 0.237 and 0.237 at
+// N = 333,333) and n = 16, m = 8 (1.09 against 1.10 and 1.10 at N = 1e6): its
+// row blocks are long, so few of their lines are stored in part.  Short
+// problems take smaller tiles to reach every CU.
+constexpr int64_t kDefectTiles = 1024;  // 4 workgroups for each of the 256 CUs
+inline int kkt_defect_kt(int n, int m, int T, int64_t intervals)
 {
-    int KT = T + 1 >= 33 ? 16 : (T + 1 >= 17 ? 32 : 64);
-    while (KT > 16 && kkt_defect_lds(n, m, T, KT) * sizeof(double) > kDefectLdsMax) KT /= 2;
+    int KT = kDefectKTMax;
+    while (KT > 16 && (intervals < kDefectTiles * KT || kkt_defect_lds(n, m, T, KT) * sizeof(double) > kDefectLdsMax))
+        KT /= 2;
     return KT;
 }
 
-// Entry t of defect row (i, k0 + kk): T Jacobian slots then the diagonal,
-// from the tile's LDS arrays (states xs and cosines cs at W = KT + 1 nodes,
-// coefficients cf = -w A | -w B, gs = -w gamma, diagonals rg; w = h/2, or h
-// under forward Euler).
-__device__ __forceinline__ double defect_entry(int i, int t, int kk, int n, int m, int T, int W, int KT,
-                                               bool euler, const double *cf, const double *gs,
-                                               const double *xs, const double *cs, const double *rg)
+// The entries of column c (state c < n, control c - n, or c = n + m: the
+// row's diagonal) in defect row (i, k0 + kk), into the tile row `o` (T + 1
+// entries), from the tile's LDS arrays: states xs and cosines cs at
+// W = KT + 1 nodes, coefficients cf = -w A | -w B, gs = -w gamma, the diagonal
+// rg (w = h/2, or h under forward Euler).  A trapezoidal column has two
+// entries (nodes k and k+1), an Euler column one.
+__device__ __forceinline__ void defect_column(int i, int c, int kk, int n, int m, int T, int W, int KT, bool euler,
+                                              const double *cf, const double *gs, const double *xs,
+                                              const double *cs, const double *rg, double *o)
 {
 #pragma clang fp contract(off)
-    double v;
-    if (euler) {
-        // row i: X_0..X_i at k, X_i at k+1, X_{i+1}..X_{n-1} at k, U at k
-        if (t == i + 1) {
-            v = 1.0;
-        } else if (t <= n) {
-            const int j = t <= i ? t : t - 1;
-            const int jn = (j + 1 == n) ? 0 : j + 1;
-            const int jp = (j == 0) ? n - 1 : j - 1;
-            v = cf[i * (n + m) + j] * cs[j * W + kk];
-            if (i == j) v += gs[j] * xs[jn * W + kk] - 1.0;
+    const int cols = n + m;
+    if (c < n) {
+        const double a = cf[i * cols + c];
+        const int jn = (c + 1 == n) ? 0 : c + 1;
+        const int jp = (c == 0) ? n - 1 : c - 1;
+        if (euler) {
+            // row i: X_0..X_i at k, X_i at k+1, X_{i+1}..X_{n-1} at k, U at k
+            double v = a * cs[c * W + kk];
+            if (i == c) v += gs[c] * xs[jn * W + kk] - 1.0;
             if (i == jp) v += gs[jp] * xs[jp * W + kk];
-        } else if (t < T) {
-            v = cf[i * (n + m) + n + (t - n - 1)];
+            o[c <= i ? c : c + 1] = v;
         } else {
-            v = rg[i * KT + kk];
+            double v0 = a * cs[c * W + kk], v1 = a * cs[c * W + kk + 1];
+            if (i == c) {
+                const double d0 = gs[c] * xs[jn * W + kk], d1 = gs[c] * xs[jn * W + kk + 1];
+                v0 += d0 - 1.0;
+                v1 += d1 + 1.0;
+            }
+            if (i == jp) {
+                v0 += gs[jp] * xs[jp * W + kk];
+                v1 += gs[jp] * xs[jp * W + kk + 1];
+            }
+            o[2 * c] = v0;
+            o[2 * c + 1] = v1;
         }
-    } else if (t < 2 * n) {
-        const int j = t >> 1, s = t & 1, u = kk + s;
-        const int jn = (j + 1 == n) ? 0 : j + 1;
-        const int jp = (j == 0) ? n - 1 : j - 1;
-        v = cf[i * (n + m) + j] * cs[j * W + u];
-        if (i == j) {
-            const double dg = gs[j] * xs[jn * W + u];
-            v += s ? dg + 1.0 : dg - 1.0;
+    } else if (c < cols) {
+        const double a = cf[i * cols + c];
+        if (euler) {
+            o[c + 1] = a;
+        } else {
+            o[2 * c] = a;
+            o[2 * c + 1] = a;
         }
-        if (i == jp) v += gs[jp] * xs[jp * W + u];
-    } else if (t < T) {
-        v = cf[i * (n + m) + n + ((t - 2 * n) >> 1)];
     } else {
-        v = rg[i * KT + kk];
+        if (euler) o[i + 1] = 1.0;
+        o[T] = rg[i * KT + kk];
     }
-    return v;
 }
 
 // Defect rows of intervals [k0, k0 + KT): the tile's states and their cosines
@@ -263,13 +276,19 @@ __device__ __forceinline__ double defect_entry(int i, int t, int kk, int n, int 
 // wavefront span several slots of a row, so coefficient reads from global
 // memory would be per-lane loads); then, for each state component i, the rows
 // (i, k0 .. k0 + kn - 1) -- one contiguous CSR range of kn (T + 1) entries,
-// each row its T Jacobian entries and its diagonal -- are computed slot-major
-// (KT lanes share a slot, so a wavefront reads few coefficients and
-// conflict-free state columns) into an LDS tile and copied out with
-// contiguous stores, two barriers per row block.  (Alternating two tiles, one
-// barrier per block, measured 9 % slower at n = 16, m = 8 and 5 % at n = 6,
-// m = 3; storing in output order straight from the sweep, no barrier at all,
-// 15 % slower: the lanes of a wavefront then mix slot kinds and diverge.)
+// each row its T Jacobian entries and its diagonal -- are computed column by
+// column (KT lanes share a column, so a wavefront reads one to four
+// coefficients and conflict-free state columns, and a lane fills both nodes'
+// entries of a column from one coefficient) into an LDS tile and copied out
+// in whole lines, two barriers per row block.  The stores bound it: 1.24 ->
+// 1.09 ms at N = 1e6, n = 16, m = 8 (6.0 TB/s) and 0.297 -> 0.232 ms at the
+// odd N = 333,333, n = 12, m = 5 (5.1 TB/s) against one entry per lane and a
+// copy that starts wherever the row block does; of that, line-aligned stores
+// alone gave 0.240 ms at n = 12 but, with the entry-wise sweep, lost 7 % at
+// n = 16.  (Alternating two tiles, one barrier per block, measured 9 % slower
+// at n = 16, m = 8 and 5 % at n = 6, m = 3; storing in output order straight
+// from the sweep, no barrier at all, 15 % slower: the lanes of a wavefront
+// then mix slot kinds and diverge.)
 // KT = 2^LG <= 64 intervals (the caller's grid uses the same KT); reg: the
 // problem's dim-entry regularization or null.  Ends with a barrier, so a
 // following tile may restage the LDS.
@@ -314,13 +333,13 @@ __device__ __forceinline__ void kkt_defect_tile(const KP &P, const KKTLayout &Lo
     __syncthreads();
     const int64_t cons_start = kkt_cons_start(P, Lo);
     for (int i = 0; i < n; i++) {
-        for (int w = threadIdx.x; w < T1 << LG; w += BS) {
-            const int t = w >> LG, kk = w & (KT - 1);
-            if (kk < kn) tile[kk * T1 + t] = defect_entry(i, t, kk, n, m, T, W, KT, euler, cf, gs, xs, cs, rg);
+        for (int w = threadIdx.x; w < (n + m + 1) << LG; w += BS) {
+            const int c = w >> LG, kk = w & (KT - 1);
+            defect_column(i, c, kk, n, m, T, W, KT, euler, cf, gs, xs, cs, rg, tile + kk * T1);
         }
         __syncthreads();
         double *out = kkt + cons_start + (i * N + k0) * T1;
-        for (int x = threadIdx.x; x < kn * T1; x += BS) st_nt(out + x, tile[x]);
+        copy_lines<BS>(out, tile, kn * T1);
         __syncthreads();
     }
 }
@@ -404,7 +423,7 @@ __device__ __forceinline__ void kkt_var_tile(const KP &P, const KKTLayout &Lo, c
             }
             __syncthreads();
             double *out = kkt + (int64_t)Lo.pre[a] * N1 + k0 * len;
-            for (int t = threadIdx.x; t < kn * len; t += BS) st_nt(out + t, buf[t]);
+            copy_lines<BS>(out, buf, kn * len);
             __syncthreads();
         }
     }

@@ -1,0 +1,69 @@
+"""Kernels whose stores are placed on 128-byte lines, at the sizes and output
+addresses where that placement can go wrong: outputs at any 8-byte offset,
+grids of any remainder, and each tile height.  Values against the oracle
+(within 1e-12 * mu); the elements around the output stay untouched."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from tests.helpers import check_close
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+PAD = 16  # doubles of a line: guard elements before and after an output
+
+
+@pytest.fixture(scope="module")
+def ocp():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2510_03932_amd as ocp
+    ocp.lib()
+    return ocp
+
+
+def _t(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(torch.device("cuda", 0))
+
+
+class Guarded:
+    """An output of `count` doubles at element `offset` past a 128-byte line,
+    with a marker in the elements before and after it."""
+
+    def __init__(self, count, offset):
+        self.raw = torch.full((count + offset + 2 * PAD,), -7.25, dtype=torch.float64, device="cuda")
+        assert self.raw.data_ptr() % (8 * PAD) == 0
+        self.lo, self.hi = PAD + offset, PAD + offset + count
+        self.out = self.raw[self.lo:self.hi]
+        self.out.fill_(float("nan"))
+
+    def values(self):
+        a = self.raw.cpu().numpy()
+        assert np.all(a[:self.lo] == -7.25) and np.all(a[self.hi:] == -7.25), "stored outside the output"
+        return a[self.lo:self.hi]
+
+
+# the fused KKT call's defect rows take tiles of 64 intervals from N = 65,536
+# (n = 20, m = 10: 32, the LDS bound), 32 from 32,768, else 16
+@pytest.mark.parametrize("N,n,m,scheme,bnd,offset", [
+    (65536, 3, 1, 0, 0, 1), (65573, 2, 1, 0, 2, 15), (65599, 3, 2, 1, 1, 8), (65541, 20, 10, 0, 0, 3),
+    (32768, 4, 0, 0, 1, 9), (32799, 3, 1, 1, 2, 0), (32767, 5, 2, 0, 0, 7), (17, 3, 1, 0, 0, 5), (1, 1, 1, 1, 2, 2)])
+def test_fused_kkt_tiles(ocp, N, n, m, scheme, bnd, offset):
+    print(f"[lines] fused N={N} n={n} m={m} scheme={scheme} bnd={bnd} offset={offset}", flush=True)
+    inst = synth.make_instance(N, n, m, seed=71, bnd=bnd, scheme=scheme)
+    prob = ocp.Problem.from_instance(inst, torch.device("cuda", 0))
+    s = prob.sizes
+    rp, _, pj, ph = ocp.kkt_pattern(N, n, m, scheme=scheme, boundary=bnd)
+    reg = np.random.default_rng(5).normal(size=s["dim"])
+    out = Guarded(s["nnzk"], offset)
+    prob.eval_kkt(_t(inst.z), _t(inst.y), 0.7, _t(reg), out=out.out)
+    oj, mj = oracle.jac_ex(inst, scheme, bnd)
+    oh, mh = oracle.hess_ex(inst, scheme, bnd, sigma=0.7)
+    check_close(out.values(), oracle.assemble(rp, pj, oj, ph, oh, reg),
+                oracle.assemble(rp, pj, mj, ph, mh, np.abs(reg)), what="kkt")
+    prob.close()
