@@ -182,22 +182,40 @@ __global__ __launch_bounds__(kBlock) void obj_final_kernel(const double *__restr
 //
 // Jacobian part: the COO values are slot-major (node fastest) while the CSR
 // rows of the constraint block are row-major, so the scatter is a transpose.
-// Workgroup g < gj owns a tile of up to KT consecutive constraint rows of one
-// state component i (intervals k0 .. k0+kn-1).  It reads the tile's T slot rows
-// coalesced (one wavefront per slot row), drops each value into LDS at
-// perm_j[e] - base, where [base, base + ext) is the tile's CSR range from
-// rowptr, adds the tile's diagonals, and then writes the whole range with
-// contiguous full-line stores.  A slot outside the range is stored directly.
-// If the values that landed in LDS do not cover the range exactly (a slot map
-// other than the closed-form one), the tile is redone with direct stores, so
-// the result is the same for any injective slot map.
+// Workgroup g < gj owns a tile of up to KT = 2^LG consecutive constraint rows
+// of one state component i (intervals k0 .. k0+kn-1).  It reads the tile's T
+// slot rows coalesced, drops each value into LDS at perm_j[e] - base, where
+// [base, base + ext) is the tile's CSR range from rowptr, adds the tile's
+// diagonals, and then writes the whole range in full lines.  A slot outside
+// the range is stored directly.  If the values that landed in LDS do not cover
+// the range exactly (a slot map other than the closed-form one), the tile is
+// redone with direct stores, so the result is the same for any injective slot
+// map.
+//
+// Reading bounds it: each slot row gives a tile KT 4-byte slots and KT values,
+// which at an odd N start anywhere in a line.  So each lane takes two adjacent
+// intervals of a slot row with one 16-byte and one 8-byte load at any
+// alignment, four slot rows' loads are in flight per lane, and a tile is as
+// tall as its LDS allows.  Against tiles of 64 rows, one slot row at a time and
+// 8-byte loads at odd entries: 452 -> 339 us at N = 200,001, n = 16, m = 8
+// (forward Euler), 718 -> 592 us at N = 333,333, n = 12, m = 5 (5.1 TB/s),
+// 87 -> 81 us at N = 1e5, n = 8, m = 4, 2.95 -> 2.89 ms at N = 1e6, n = 16,
+// m = 8 (5.8 TB/s).  Tiles of 256 rows leave too few workgroups per CU (4.0 ms
+// at n = 16, m = 8); 512 lanes gain 1 % there and lose 12 % at N = 1e5.
 //
 // Hessian part: workgroups gj.. take nodes and scatter the S Hessian slots
 // directly (rows of 1 to 3 entries, close to contiguous across lanes), adding
-// reg on the variable diagonals in the same IEEE add.
+// reg on the variable diagonals in the same IEEE add; the loads of kHessBatch
+// slots are issued before their stores.
 // ---------------------------------------------------------------------------
+typedef double dbl2_any __attribute__((ext_vector_type(2), aligned(8)));     // at any element
+typedef int32_t int2_any __attribute__((ext_vector_type(2), aligned(4)));
+
+constexpr int kAsmBatch = 4;   // slot rows in flight per lane (Jacobian part)
+constexpr int kHessBatch = 8;  // slots in flight per lane (Hessian part)
+
 __global__ __launch_bounds__(kBlock) void assemble_kernel(
-    KP P, int gj, int gh, int KT, bool vec_ok, const int32_t *__restrict__ perm_j, const int32_t *__restrict__ perm_h,
+    KP P, int gj, int gh, int LG, const int32_t *__restrict__ perm_j, const int32_t *__restrict__ perm_h,
     const int32_t *__restrict__ rowptr, const double *__restrict__ jv,
     const double *__restrict__ hv, const double *__restrict__ reg, double *__restrict__ kkt)
 {
@@ -208,9 +226,10 @@ __global__ __launch_bounds__(kBlock) void assemble_kernel(
     const uint32_t nnzk = (uint32_t)P.nnzk;  // slots outside [0, nnzk) are skipped
     const int T = P.T;
     if ((int)blockIdx.x < gj) {
-        const int tiles_per_i = (P.N + KT - 1) / KT;
+        const int KT = 1 << LG;
+        const int tiles_per_i = (P.N + KT - 1) >> LG;
         const int i = blockIdx.x / tiles_per_i;
-        const int k0 = (blockIdx.x - i * tiles_per_i) * KT;
+        const int k0 = (blockIdx.x - i * tiles_per_i) << LG;
         const int kn = min(KT, P.N - k0);
         const int64_t r0 = nvar + (int64_t)i * N + k0;  // first KKT row of the tile
         const int32_t base = rowptr[r0];
@@ -219,21 +238,43 @@ __global__ __launch_bounds__(kBlock) void assemble_kernel(
         // stage only a range inside [0, nnzk) (a corrupt rowptr falls back
         // to bounds-checked direct stores)
         const bool staged = ext >= 0 && ext <= cap && base >= 0 && (int64_t)base + ext <= (int64_t)nnzk;
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
         if (threadIdx.x == 0) filled = 0;
-        if (staged)
-            for (int x = threadIdx.x; x < ext; x += kBlock) tile[x] = 0.0;
         __syncthreads();
-        int mine = 0;
         const int64_t e0 = (int64_t)i * T * N + k0;
-        // Each lane takes two adjacent intervals of a slot row (16-byte value
-        // and 8-byte slot loads when aligned), so KT/2 lanes cover a slot row
-        // and a wavefront covers 128/KT slot rows per pass.
-        const int lanes_per_row = KT / 2;
-        const int rows_per_wave = 64 / lanes_per_row;
-        const int kl = (lane % lanes_per_row) * 2;
-        const int sub = lane / lanes_per_row;
-        auto place = [&](int32_t q, double v) {
+        // Visit every (slot, value) of the tile; `put` decides where it goes.
+        auto visit = [&](auto put) {
+            const int total = T << (LG - 1);  // interval pairs of the tile's slot rows
+            for (int w0 = threadIdx.x; w0 < total; w0 += kBlock * kAsmBatch) {
+                int2_any q[kAsmBatch];
+                dbl2_any v[kAsmBatch];
+                int live[kAsmBatch];
+#pragma unroll
+                for (int u = 0; u < kAsmBatch; u++) {
+                    const int w = w0 + u * kBlock;
+                    const int kl = 2 * (w & (KT / 2 - 1));
+                    const int64_t e = e0 + (int64_t)(w >> (LG - 1)) * N + kl;
+                    live[u] = w < total ? min(kn - kl, 2) : 0;
+                    if (live[u] == 2) {
+                        q[u] = __builtin_nontemporal_load(reinterpret_cast<const int2_any *>(perm_j + e));
+                        v[u] = __builtin_nontemporal_load(reinterpret_cast<const dbl2_any *>(jv + e));
+                    } else if (live[u] == 1) {
+                        q[u].x = perm_j[e];
+                        v[u].x = jv[e];
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < kAsmBatch; u++) {
+                    if (live[u] >= 1) put(q[u].x, v[u].x);
+                    if (live[u] == 2) put(q[u].y, v[u].y);
+                }
+            }
+            for (int x = threadIdx.x; x < kn; x += kBlock) {
+                const int64_t d = r0 + x;
+                put(rowptr[d + 1] - 1, reg ? reg[d] : 0.0);
+            }
+        };
+        int mine = 0;
+        visit([&](int32_t q, double v) {
             const uint32_t loc = (uint32_t)q - (uint32_t)base;
             if (staged && loc < (uint32_t)ext) {
                 tile[loc] = v;
@@ -241,67 +282,51 @@ __global__ __launch_bounds__(kBlock) void assemble_kernel(
             } else if ((uint32_t)q < nnzk) {
                 kkt[q] = v;
             }
-        };
-        if (kl < kn) {
-            for (int t = wave * rows_per_wave + sub; t < T; t += 4 * rows_per_wave) {
-                const int64_t e = e0 + (int64_t)t * N + kl;
-                if (vec_ok && kl + 1 < kn && (e & 1) == 0) {
-                    const int2v q = __builtin_nontemporal_load(reinterpret_cast<const int2v *>(perm_j + e));
-                    const dbl2 v = __builtin_nontemporal_load(reinterpret_cast<const dbl2 *>(jv + e));
-                    place(q.x, v.x);
-                    place(q.y, v.y);
-                } else {
-                    place(perm_j[e], jv[e]);
-                    if (kl + 1 < kn) place(perm_j[e + 1], jv[e + 1]);
-                }
-            }
-        }
-        if (threadIdx.x < kn) {
-            const int64_t d = r0 + threadIdx.x;
-            place(rowptr[d + 1] - 1, reg ? reg[d] : 0.0);
-        }
+        });
         if (mine) atomicAdd(&filled, mine);
         __syncthreads();
         if (!staged) return;
         if (filled == ext) {
-            double *out = kkt + base;
-            for (int x = threadIdx.x; x < ext; x += kBlock) st_nt(out + x, tile[x]);
+            copy_lines<kBlock>(kkt + base, tile, ext);
         } else {
             // not an exact cover: store this tile's values directly
-            if (kl < kn) {
-                for (int t = wave * rows_per_wave + sub; t < T; t += 4 * rows_per_wave) {
-                    const int64_t e = e0 + (int64_t)t * N + kl;
-                    for (int u = 0; u < 2 && kl + u < kn; u++) {
-                        const int32_t q = perm_j[e + u];
-                        if ((uint32_t)q < nnzk) kkt[q] = jv[e + u];
-                    }
-                }
-            }
-            if (threadIdx.x < kn) {
-                const int64_t d = r0 + threadIdx.x;
-                const int32_t q = rowptr[d + 1] - 1;
-                if ((uint32_t)q < nnzk) kkt[q] = reg ? reg[d] : 0.0;
-            }
+            visit([&](int32_t q, double v) {
+                if ((uint32_t)q < nnzk) kkt[q] = v;
+            });
         }
     } else if ((int)blockIdx.x < gj + gh) {
         const int64_t k = (int64_t)(blockIdx.x - gj) * kBlock + threadIdx.x;
         if (k >= N1) return;
         const int n = P.n, np = P.npair, S = P.S;
-        for (int s = 0; s < S; s++) {
-            int64_t e, row = -1;  // COO entry; KKT row of a diagonal entry
-            if (s < n + np) {
-                e = (int64_t)s * N1 + k;
-                if (s < n) row = e;
-            } else {
-                if (k >= P.NU) break;  // control slots exist on NU nodes
-                const int64_t l = s - n - np;
-                e = (int64_t)(n + np) * N1 + l * P.NU + k;
-                row = (int64_t)n * N1 + l * P.NU + k;
+        for (int s0 = 0; s0 < S; s0 += kHessBatch) {
+            double v[kHessBatch], rg[kHessBatch];
+            int32_t q[kHessBatch];
+#pragma unroll
+            for (int u = 0; u < kHessBatch; u++) {
+                const int s = s0 + u;
+                q[u] = -1;
+                rg[u] = 0.0;
+                if (s >= S) continue;
+                int64_t e, row = -1;  // COO entry; KKT row of a diagonal entry
+                if (s < n + np) {
+                    e = (int64_t)s * N1 + k;
+                    if (s < n) row = e;
+                } else {
+                    if (k >= P.NU) continue;  // control slots exist on NU nodes
+                    const int64_t l = s - n - np;
+                    e = (int64_t)(n + np) * N1 + l * P.NU + k;
+                    row = (int64_t)n * N1 + l * P.NU + k;
+                }
+                q[u] = perm_h[e];
+                v[u] = hv[e];
+                if (reg && row >= 0) rg[u] = reg[row];
             }
-            double v = hv[e];
-            if (reg && row >= 0) v += reg[row];
-            const uint32_t q = (uint32_t)perm_h[e];
-            if (q < nnzk) kkt[q] = v;
+#pragma unroll
+            for (int u = 0; u < kHessBatch; u++) {
+                const int s = s0 + u;
+                const bool diag = s < n || s >= n + np;
+                if ((uint32_t)q[u] < nnzk) kkt[q[u]] = reg && diag ? v[u] + rg[u] : v[u];
+            }
         }
     } else {
         // boundary rows: their Jacobian entry and their diagonal
@@ -598,18 +623,18 @@ int ocp_assemble_kkt(const ocp_problem *p, const int32_t *perm_j, const int32_t 
         return fail(OCP_ERR_ARG, "ocp_assemble_kkt: null array");
     if (p->model == quad::kModel)
         return quad::assemble_kkt(p, perm_j, perm_h, rowptr, jvals, hvals, reg, kkt, stream);
-    // Tile height: 64 constraint rows (one per lane) while the staged CSR
-    // range fits in 64 KiB of LDS, else 32.
-    const int KT = (64 * (p->d.T + 1) * 8 <= 64 * 1024) ? 64 : 32;
-    const unsigned tiles_per_i = (unsigned)((p->d.N + KT - 1) / KT);
-    const unsigned gj = tiles_per_i * (unsigned)p->d.n;
+    // Tile height: 128 constraint rows while the staged CSR range fits in
+    // 64 KiB of LDS, else 64 or 32; shorter while that leaves fewer than two
+    // tiles per CU (a small problem is bound by the latency of one tile).
+    int LG = 7;
+    auto tiles = [&] { return ((p->d.N + (1 << LG) - 1) >> LG) * p->d.n; };
+    while (LG > 5 && (((size_t)(p->d.T + 1) << LG) * sizeof(double) > 64 * 1024 || tiles() < 512)) LG--;
+    const unsigned gj = (unsigned)tiles();
     const unsigned gh = blocks_for(p->d.N1, kBlock);
     const unsigned gb = blocks_for(p->d.nb, kBlock);
-    const size_t lds = (size_t)KT * (p->d.T + 1) * sizeof(double);
-    // paired loads need 16-byte aligned values and 8-byte aligned slots
-    const bool vec_ok = ((uintptr_t)jvals % 16 == 0) && ((uintptr_t)perm_j % 8 == 0);
+    const size_t lds = ((size_t)(p->d.T + 1) << LG) * sizeof(double);
     hipLaunchKernelGGL(assemble_kernel, dim3(gj + gh + gb), dim3(kBlock), lds, stream, p->kp, (int)gj,
-                       (int)gh, KT, vec_ok, perm_j, perm_h, rowptr, jvals, hvals, reg, kkt);
+                       (int)gh, LG, perm_j, perm_h, rowptr, jvals, hvals, reg, kkt);
     return check_launch("ocp_assemble_kkt");
 }
 

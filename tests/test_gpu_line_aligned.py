@@ -67,3 +67,31 @@ def test_fused_kkt_tiles(ocp, N, n, m, scheme, bnd, offset):
     check_close(out.values(), oracle.assemble(rp, pj, oj, ph, oh, reg),
                 oracle.assemble(rp, pj, mj, ph, mh, np.abs(reg)), what="kkt")
     prob.close()
+
+
+# the assembly takes tiles of 128 rows from 512 of them, else 64 or 32; at
+# n = m = 32 (T = 128) the LDS bound gives 32; N odd puts every other slot row
+# off the 16-byte grid
+@pytest.mark.parametrize("N,n,m,scheme,bnd,offset", [
+    (65536, 1, 0, 0, 0, 0), (21845, 3, 1, 0, 1, 1), (21889, 3, 2, 1, 2, 15), (16384, 2, 1, 0, 0, 8),
+    (10923, 3, 1, 0, 0, 3), (5500, 3, 1, 1, 0, 9), (97, 5, 2, 0, 2, 7), (2051, 32, 32, 0, 0, 5), (1, 1, 0, 0, 0, 2),
+    (2, 2, 2, 1, 1, 4)])
+def test_assembly_tiles(ocp, N, n, m, scheme, bnd, offset):
+    print(f"[lines] assembly N={N} n={n} m={m} scheme={scheme} bnd={bnd} offset={offset}", flush=True)
+    prob = ocp.Problem(N, n, m, np.zeros((n, n)), np.zeros((n, m)), np.zeros(n), np.ones(n), np.ones(m),
+                       scheme=scheme, boundary=bnd)
+    s = prob.sizes
+    rng = np.random.default_rng(3)
+    jv, hv, reg = (rng.normal(size=s[k]) for k in ("nnzj", "nnzh", "dim"))
+    rp, _, pj, ph = prob.kkt_pattern()
+    cross = pj.copy()  # an injective map whose tiles exchange slots: no tile covers its range
+    cross[[0, -1 - bnd * n]] = cross[[-1 - bnd * n, 0]]
+    for maps in (pj, cross):
+        for r in (None, reg):
+            out = Guarded(s["nnzk"], offset)
+            # inputs at odd elements too: the paired loads take any alignment
+            prob.assemble_kkt(_t(np.r_[np.int32(0), maps])[1:], _t(ph), _t(rp), _t(np.r_[0.0, jv])[1:], _t(hv),
+                              None if r is None else _t(r), out=out.out)
+            want = oracle.assemble(rp, maps, jv, ph, hv, r)
+            assert np.array_equal(out.values().view(np.uint64), want.view(np.uint64))
+    prob.close()
