@@ -519,8 +519,8 @@ typedef struct ocp_graph ocp_graph;
 /* Tile shape of the persistent launch. */
 typedef struct ocp_batch_config {
     int32_t block;        /* threads per workgroup: 128 or 256 */
-    int32_t pair;         /* 1: Jacobian lanes take two intervals (16-byte stores) where the
-                             instance allows it (N_b even, output 16-byte aligned); 0: one */
+    int32_t pair;         /* 1: Jacobian lanes take two intervals, stored in whole 128-byte
+                             lines, for instances whose slot rows do not all begin on one; 0: one */
     int32_t wgs_per_cu;   /* persistent workgroups per compute unit, 1..32; 0: one
                              workgroup per tile (the loop over tiles runs once) */
     int32_t order;        /* tile order within an instance: 0 node range major (all columns

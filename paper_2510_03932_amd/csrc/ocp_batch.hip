@@ -8,8 +8,8 @@
 // The persistent kernel walks a static tile list: workgroup w takes tiles
 // w, w + G, w + 2G, ... (G = grid size), so every wave reaches the end of the
 // list and exits, and the assignment is fixed (no queue).  A tile is
-// (instance, first interval or node, kind): a Jacobian column over
-// `block * npt` intervals, a Hessian, gradient or variable-row KKT run of
+// (instance, first interval or node, kind): a Jacobian column over `block`
+// intervals (or 2 `block` - 16 stored in whole lines), a Hessian, gradient or variable-row KKT run of
 // `block` nodes, a defect run of 63 intervals per wavefront, an objective
 // group of 256 nodes, a defect-row KKT run of 16-64 intervals, or an instance's
 // boundary rows.  One list per evaluation mask, instance-major (an instance's
@@ -70,7 +70,7 @@ struct TileDesc {
     int32_t b;     // instance
     int32_t k0;    // first interval or node
     int16_t kind;  // TileKind
-    int16_t npt;   // intervals per lane of a Jacobian tile (1 or 2)
+    int16_t npt;   // intervals per lane of a Jacobian tile: 1, or 2 in whole lines
     int32_t col;   // Jacobian column 0 .. n+m-1
 };
 
@@ -117,13 +117,6 @@ __device__ __forceinline__ KP make_kp(const BP &bp, const InstDesc &id, int b)
     return P;
 }
 
-template <int NPT, int SCHEME>
-__device__ __forceinline__ void jac_cols(const KP &P, const double *z, double *jac, int64_t k, int col)
-{
-    if constexpr (SCHEME != 0) jac_column_euler<NPT>(P, z, jac, k, col);
-    else jac_column<NPT>(P, z, jac, k, col);
-}
-
 // KINDS: the evaluation bits this instantiation handles (tiles of other kinds
 // are not in its lists); fewer kinds keep the register footprint of the
 // Jacobian/Hessian-only launch small.  SCHEME: the batch's scheme, fixed at
@@ -135,11 +128,11 @@ __device__ __forceinline__ void jac_cols(const KP &P, const double *z, double *j
 // The defect-row KKT tiles wait on each tile's descriptors and loads, so more
 // of them in flight help: held to 7 wavefronts per SIMD (71 VGPRs against 73)
 // they take 1.10 ms against 1.17 for 512 instances, n = 6, m = 3 (at 8 the
-// registers spill).
+// registers spill).  The Jacobian tiles are held to 6 (80 VGPRs against 98).
 template <int NB, int BS, int KINDS, int SCHEME>
-__global__ __launch_bounds__(BS, KINDS == kListKktDef ? 7 : 1) void batch_kernel(BP bp, KKTLayout Lo, const InstDesc *__restrict__ inst,
+__global__ __launch_bounds__(BS, KINDS == kListKktDef ? 7 : KINDS == OCP_EVAL_JAC ? 6 : 1) void batch_kernel(BP bp, KKTLayout Lo, const InstDesc *__restrict__ inst,
                                                    const TileDesc *__restrict__ tiles, int ntiles, int what,
-                                                   bool pair_ok, const double *__restrict__ z_,
+                                                   const double *__restrict__ z_,
                                                    const double *__restrict__ y_, const double *__restrict__ reg_,
                                                    double sigma, double *__restrict__ grad_,
                                                    double *__restrict__ cons_, double *__restrict__ jac_,
@@ -147,7 +140,7 @@ __global__ __launch_bounds__(BS, KINDS == kListKktDef ? 7 : 1) void batch_kernel
                                                    double *__restrict__ parts_)
 {
     extern __shared__ double lds[];   // defect-row KKT tile (dynamic, only with OCP_EVAL_KKT)
-    __shared__ double vbuf[3 * BS];   // variable-row KKT tile
+    __shared__ double vbuf[(KINDS & OCP_EVAL_JAC ? 6 : 3) * BS];  // Jacobian column or variable-row KKT tile
     __shared__ double ws[4];          // objective sums
     const int tid = threadIdx.x;
     for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
@@ -162,20 +155,11 @@ __global__ __launch_bounds__(BS, KINDS == kListKktDef ? 7 : 1) void batch_kernel
             if (!(KINDS & OCP_EVAL_JAC)) break;
             double *jb = jac_ + id.jac_off;
             if (td.npt == 2) {
-                // two intervals per lane; paired stores need a 16-byte
-                // aligned output, else the lane stores them one by one
-                const int64_t k = td.k0 + 2 * (int64_t)tid;
-                if (k < P.N) {
-                    if (pair_ok) {
-                        jac_cols<2, SCHEME>(P, zb, jb, k, td.col);
-                    } else {
-                        jac_cols<1, SCHEME>(P, zb, jb, k, td.col);
-                        jac_cols<1, SCHEME>(P, zb, jb, k + 1, td.col);
-                    }
-                }
+                jac_column_lines<BS>(P, zb, jb, td.k0, td.col, vbuf);
+                __syncthreads();  // vbuf is reused by the next tile
             } else {
                 const int64_t k = td.k0 + (int64_t)tid;
-                if (k < P.N) jac_cols<1, SCHEME>(P, zb, jb, k, td.col);
+                if (k < P.N) jac_column(P, zb, jb, k, td.col);
             }
             break;
         }
@@ -305,11 +289,12 @@ static bool valid_config(const ocp_batch_config &c)
            c.wgs_per_cu >= 0 && c.wgs_per_cu <= 32 && (c.order == 0 || c.order == 1);
 }
 
-// Tile list of a config and evaluation mask, instance-major.  Jacobian tiles
-// use paired lanes only for instances with an even N and an even packed
-// Jacobian offset (every slot row of the instance then starts on a 16-byte
-// boundary of a 16-byte aligned packed array; forward-Euler rows or boundary
-// rows can make an offset odd).
+// Tile list of a config and evaluation mask, instance-major.  With `pair`,
+// Jacobian tiles take two intervals per lane, stored in whole lines, for the
+// instances whose slot rows do not all begin on a 128-byte line of an aligned
+// packed array (those are stored directly, as launch_jac does).  In lines
+// against directly, n = 6, m = 3: 98 against 139 us (482 MB), 27 against 35 us
+// (118 MB); n = 4, m = 2: 8.3 against 9.1 us (26 MB), the same at 6.5 MB.
 static std::vector<TileDesc> build_tiles(const ocp_batch &b, const ocp_batch_config &c, int what)
 {
     std::vector<TileDesc> t;
@@ -321,14 +306,15 @@ static std::vector<TileDesc> build_tiles(const ocp_batch &b, const ocp_batch_con
             t.push_back({i, (int32_t)k0, (int16_t)kind, (int16_t)npt, (int32_t)col});
         };
         if (what & OCP_EVAL_JAC) {
-            const int npt = (c.pair && N % 2 == 0 && b.jac_off[i] % 2 == 0) ? 2 : 1;
-            const int64_t span = (int64_t)c.block * npt;
+            const int npt = (c.pair && !(N % kLine == 0 && b.jac_off[i] % kLine == 0)) ? 2 : 1;
+            const int64_t span = npt == 2 ? lines_span(c.block) : c.block;
+            const int64_t last = npt == 2 ? N + kHalo : N;  // lines begin up to 15 intervals before k0
             if (c.order == 0) {
-                for (int64_t k0 = 0; k0 < N; k0 += span)
+                for (int64_t k0 = 0; k0 < last; k0 += span)
                     for (int col = 0; col < cols; col++) put(k0, kJac, npt, col);
             } else {
                 for (int col = 0; col < cols; col++)
-                    for (int64_t k0 = 0; k0 < N; k0 += span) put(k0, kJac, npt, col);
+                    for (int64_t k0 = 0; k0 < last; k0 += span) put(k0, kJac, npt, col);
             }
         }
         if (what & OCP_EVAL_HESS)
@@ -446,19 +432,18 @@ static void launch_batch_scheme(const ocp_batch *b, const TileDesc *tiles, int n
 {
     const int cap = b->cfg.wgs_per_cu > 0 ? b->cus * b->cfg.wgs_per_cu : ntiles;
     const unsigned grid = (unsigned)std::max(1, std::min(ntiles, cap));
-    const bool pair_ok = ((uintptr_t)io.jac % 16 == 0);
     const size_t lds = ((KINDS & kListKktDef) && (what & OCP_EVAL_KKT))
                            ? kkt_defect_lds(b->n, b->m, b->shape.T, 1 << b->bp.defect_lg) * sizeof(double)
                            : 0;
     const int n = b->n;
     if (n <= 4)
-        hipLaunchKernelGGL((batch_kernel<4, BS, KINDS, SCHEME>), dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, pair_ok, io.z, io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
+        hipLaunchKernelGGL((batch_kernel<4, BS, KINDS, SCHEME>), dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, io.z, io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
     else if (n <= 8)
-        hipLaunchKernelGGL((batch_kernel<8, BS, KINDS, SCHEME>), dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, pair_ok, io.z, io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
+        hipLaunchKernelGGL((batch_kernel<8, BS, KINDS, SCHEME>), dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, io.z, io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
     else if (n <= 16)
-        hipLaunchKernelGGL((batch_kernel<16, BS, KINDS, SCHEME>), dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, pair_ok, io.z, io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
+        hipLaunchKernelGGL((batch_kernel<16, BS, KINDS, SCHEME>), dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, io.z, io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
     else
-        hipLaunchKernelGGL((batch_kernel<32, BS, KINDS, SCHEME>), dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, pair_ok, io.z, io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
+        hipLaunchKernelGGL((batch_kernel<32, BS, KINDS, SCHEME>), dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, io.z, io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
 }
 
 template <int BS, int KINDS>
@@ -575,13 +560,12 @@ static int batch_launch(const ocp_batch *b, const Plan &plan, int32_t what, int3
     }
     for (int32_t i = 0; i < b->count; i++) {
         const KP P = host_kp(b, i);
-        const bool pair_ok = ((uintptr_t)(io.jac + b->jac_off[i]) % 16 == 0);
         const double *zb = io.z + b->z_off[i];
         hipError_t e = hipSuccess;
         if (what & OCP_EVAL_OBJ) e = launch_obj(P, zb, b->parts + b->part_off[i], io.obj + i, s);
         if (e == hipSuccess && (what & OCP_EVAL_GRAD)) e = launch_grad(P, zb, io.grad + b->z_off[i], s);
         if (e == hipSuccess && (what & OCP_EVAL_CONS)) e = launch_cons(P, zb, io.cons + b->c_off[i], s);
-        if (e == hipSuccess && (what & OCP_EVAL_JAC)) e = launch_jac(P, zb, io.jac + b->jac_off[i], pair_ok, s);
+        if (e == hipSuccess && (what & OCP_EVAL_JAC)) e = launch_jac(P, zb, io.jac + b->jac_off[i], s);
         if (e == hipSuccess && (what & OCP_EVAL_HESS))
             e = launch_hess(P, zb, io.y + b->c_off[i], io.sigma, io.hess + b->hess_off[i], s);
         if (e == hipSuccess && (what & OCP_EVAL_KKT))

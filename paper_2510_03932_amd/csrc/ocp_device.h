@@ -147,81 +147,146 @@ __device__ __forceinline__ double block_sum(double v)
 }
 
 // ---------------------------------------------------------------------------
-// Jacobian values of one column for NPT consecutive intervals k .. k+NPT-1
-// (the caller guarantees k + NPT <= N, and for NPT = 2 a 16-byte aligned
-// output with N even).  Column col < n is state column j: slots 2j, 2j+1 of
-// every row i; col = n + l is control column l: slots 2n+2l, 2n+2l+1, the
-// constant -hh B_il.  NPT = 2 stores a 16-byte pair per lane, so a wavefront
-// store is one contiguous KiB of a slot row.  A state column needs NPT+1
-// cosines per lane; the bilinear term touches only rows i = j (partner
-// X_{j+1}) and i = j-1 (factor X_{j-1}).
+// Jacobian values, one column of the node-local variables at a time.  Column
+// col < n is state column j: it writes slots 2j, 2j+1 (nodes k, k+1) of every
+// row i under the trapezoidal scheme; col = n + l is control column l, the
+// constants -hh B_il.  Forward Euler (paper Sec. 3): row i's slots, in
+// ascending column order, are X_0..X_i at k (slots 0..i), X_i at k+1 (slot
+// i+1), X_{i+1}..X_{n-1} at k (slots i+2..n), U_l at k (slot n+1+l), so state
+// column j writes slot (j <= i ? j : j+1) of every row i and the +1 at slot
+// j+1 of row j.
+//
+// The bilinear term touches only rows i = j (partner X_{j+1}) and i = j-1
+// (factor X_{j-1}).  jac_entry is the state columns' value, the same bits
+// wherever it is used: a = -w A_ij, c = cos X_j, id the identity's part,
+// gj = -w gamma_j, gp = -w gamma_{j-1}, xn = X_{j+1}, xp = X_{j-1}, all at the
+// slot's node.
 // ---------------------------------------------------------------------------
-template <int NPT>
-__device__ __forceinline__ void jac_column(const KP &P, const double *__restrict__ z,
-                                           double *__restrict__ jac, int64_t k, int col)
+__device__ __forceinline__ double jac_entry(bool own, bool prev, double a, double c, double id, double gj, double gp,
+                                            double xn, double xp)
 {
-    const int n = P.n, T = P.T;
+#pragma clang fp contract(off)
+    double v = a * c;
+    if (own) v = __builtin_fma(a, c, __builtin_fma(gj, xn, id));
+    if (prev) v = __builtin_fma(gp, xp, v);
+    return v;
+}
+
+// One column at interval k < N, stored directly: the path of arrays whose slot
+// rows all begin on a 128-byte line, and of small problems (see launch_jac).
+__device__ __forceinline__ void jac_column(const KP &P, const double *__restrict__ z, double *__restrict__ jac,
+                                           int64_t k, int col)
+{
+    const int n = P.n, m = P.m, T = P.T;
     const int64_t N = P.N, N1 = P.N1;
-    const double hh = P.hh;
+    const bool euler = P.scheme != 0;
+    const double w = euler ? P.h : P.hh;
     if (col < n) {
         const int j = col;
         const int jn = (j + 1 == n) ? 0 : j + 1;
         const int jp = (j == 0) ? n - 1 : j - 1;
-        const double *xj = z + j * N1 + k;
-        const double *xn = z + jn * N1 + k;
-        const double *xp = z + jp * N1 + k;
-        double cs[NPT + 1], dg[NPT + 1], lo[NPT + 1];
+        const double gj = -w * P.gam[j], gp = -w * P.gam[jp];
+        const double *xj = z + j * N1 + k, *xn = z + jn * N1 + k, *xp = z + jp * N1 + k;
+        double cs[2], vn[2], vp[2];
 #pragma unroll
-        for (int u = 0; u <= NPT; u++) {
-            cs[u] = cos(xj[u]);
-            dg[u] = -hh * P.gam[j] * xn[u];   // row i = j: gamma_j X_{j+1}
-            lo[u] = -hh * P.gam[jp] * xp[u];  // row i = j-1: gamma_{j-1} X_{j-1}
+        for (int u = 0; u < 2; u++) {
+            if (u == 0 || !euler) {
+                cs[u] = cos(xj[u]);
+                vn[u] = xn[u];
+                vp[u] = xp[u];
+            }
         }
         for (int i = 0; i < n; i++) {
-            const double a = -hh * P.A[i * n + j];
-            double v0[NPT], v1[NPT];
-#pragma unroll
-            for (int u = 0; u < NPT; u++) {
-                v0[u] = a * cs[u];
-                v1[u] = a * cs[u + 1];
-            }
-            if (i == j) {
-#pragma unroll
-                for (int u = 0; u < NPT; u++) {
-                    v0[u] += dg[u] - 1.0;
-                    v1[u] += dg[u + 1] + 1.0;
-                }
-            }
-            if (i == jp) {
-#pragma unroll
-                for (int u = 0; u < NPT; u++) {
-                    v0[u] += lo[u];
-                    v1[u] += lo[u + 1];
-                }
-            }
-            double *o0 = jac + ((int64_t)i * T + 2 * j) * N + k;
-            double *o1 = o0 + N;
-            if constexpr (NPT == 2) {
-                st_nt2(o0, dbl2{v0[0], v0[1]});
-                st_nt2(o1, dbl2{v1[0], v1[1]});
+            const double a = -w * P.A[i * n + j];
+            const double v0 = jac_entry(i == j, i == jp, a, cs[0], -1.0, gj, gp, vn[0], vp[0]);
+            if (euler) {
+                st_nt(jac + ((int64_t)i * T + (j <= i ? j : j + 1)) * N + k, v0);
             } else {
-                st_nt(o0, v0[0]);
-                st_nt(o1, v1[0]);
+                double *o = jac + ((int64_t)i * T + 2 * j) * N + k;
+                st_nt(o, v0);
+                st_nt(o + N, jac_entry(i == j, i == jp, a, cs[1], 1.0, gj, gp, vn[1], vp[1]));
             }
         }
+        if (euler) st_nt(jac + ((int64_t)j * T + j + 1) * N + k, 1.0);
     } else {
-        const int l = col - n, m = P.m;
+        const int l = col - n;
         for (int i = 0; i < n; i++) {
-            const double v = -hh * P.B[i * m + l];
-            double *o0 = jac + ((int64_t)i * T + 2 * n + 2 * l) * N + k;
-            double *o1 = o0 + N;
-            if constexpr (NPT == 2) {
-                st_nt2(o0, dbl2{v, v});
-                st_nt2(o1, dbl2{v, v});
-            } else {
-                st_nt(o0, v);
-                st_nt(o1, v);
-            }
+            const double v = -w * P.B[i * m + l];
+            double *o = jac + ((int64_t)i * T + (euler ? n + 1 + l : 2 * (n + l))) * N + k;
+            st_nt(o, v);
+            if (!euler) st_nt(o + N, v);
+        }
+    }
+}
+
+// Slot rows stored in whole lines.  A workgroup of BS lanes takes a tile of
+// lines_span(BS) = 2 BS - 16 intervals from k0 (a multiple of the span) of a
+// slot row of N values and stores the row's intervals [k0 - sh, k0 - sh +
+// span), sh = row_shift: the 128-byte lines that begin there, so every
+// wavefront's 16-byte stores fill whole lines whatever the row's address.
+// val(x) is the value of interval k0 - 15 + x, 0 <= x < 2 BS - 1.  The tiles
+// of a row are ceil((N + 15) / span).
+constexpr int kHalo = kLine - 1;
+constexpr int lines_span(int bs) { return 2 * bs - kLine; }
+template <int BS, class F>
+__device__ __forceinline__ void store_row_lines(double *__restrict__ row, int64_t N, int64_t k0, F val)
+{
+    const int sh = (int)(((uintptr_t)(row + k0) / sizeof(double)) % kLine);
+    const int x = 2 * (int)threadIdx.x;
+    if (x >= lines_span(BS)) return;
+    const int64_t k = k0 - sh + x;
+    const double v0 = val(kHalo - sh + x), v1 = val(kHalo - sh + x + 1);
+    if (k >= 0 && k + 1 < N) {
+        st_nt2(row + k, dbl2{v0, v1});
+    } else {
+        if (k >= 0 && k < N) st_nt(row + k, v0);
+        if (k + 1 >= 0 && k + 1 < N) st_nt(row + k + 1, v1);
+    }
+}
+
+// One column of a tile of lines_span(BS) intervals from k0, stored in whole
+// lines from 6 BS doubles of LDS (the cosines and the two bilinear factors at
+// the tile's 2 BS nodes; each node is evaluated once).
+template <int BS>
+__device__ __forceinline__ void jac_column_lines(const KP &P, const double *__restrict__ z, double *__restrict__ jac,
+                                                 int64_t k0, int col, double *lds)
+{
+    const int n = P.n, m = P.m, T = P.T;
+    const int64_t N = P.N, N1 = P.N1;
+    const bool euler = P.scheme != 0;
+    const double w = euler ? P.h : P.hh;
+    if (col < n) {
+        const int j = col;
+        const int jn = (j + 1 == n) ? 0 : j + 1;
+        const int jp = (j == 0) ? n - 1 : j - 1;
+        const double gj = -w * P.gam[j], gp = -w * P.gam[jp];
+        double *cs = lds, *xn = lds + 2 * BS, *xp = lds + 4 * BS;
+#pragma unroll
+        for (int u = 0; u < 2; u++) {
+            const int x = (int)threadIdx.x + u * BS;
+            const int64_t k = min(max(k0 - kHalo + x, (int64_t)0), N);  // clamped: values past the ends are not stored
+            cs[x] = cos(z[j * N1 + k]);
+            xn[x] = z[jn * N1 + k];
+            xp[x] = z[jp * N1 + k];
+        }
+        __syncthreads();
+        for (int i = 0; i < n; i++) {
+            const double a = -w * P.A[i * n + j];
+            auto at = [&](int x, double id) {
+                return jac_entry(i == j, i == jp, a, cs[x], id, gj, gp, i == j ? xn[x] : 0.0, i == jp ? xp[x] : 0.0);
+            };
+            double *row = jac + ((int64_t)i * T + (!euler ? 2 * j : j <= i ? j : j + 1)) * N;
+            store_row_lines<BS>(row, N, k0, [&](int x) { return at(x, -1.0); });
+            if (!euler) store_row_lines<BS>(row + N, N, k0, [&](int x) { return at(x + 1, 1.0); });
+        }
+        if (euler) store_row_lines<BS>(jac + ((int64_t)j * T + j + 1) * N, N, k0, [](int) { return 1.0; });
+    } else {
+        const int l = col - n;
+        for (int i = 0; i < n; i++) {
+            const double v = -w * P.B[i * m + l];
+            double *row = jac + ((int64_t)i * T + (euler ? n + 1 + l : 2 * (n + l))) * N;
+            store_row_lines<BS>(row, N, k0, [&](int) { return v; });
+            if (!euler) store_row_lines<BS>(row + N, N, k0, [&](int) { return v; });
         }
     }
 }
@@ -354,74 +419,11 @@ __device__ __forceinline__ double last_of(const double (&a)[NB], int n)
 }
 
 // ---------------------------------------------------------------------------
-// Forward Euler (paper Sec. 3): Jacobian values of one column for NPT
-// consecutive intervals k .. k+NPT-1 (k + NPT <= N; NPT = 2 needs N even and a
-// 16-byte aligned output).  Row i's slots, in ascending column order, are
-// X_0..X_i at k (slots 0..i), X_i at k+1 (slot i+1), X_{i+1}..X_{n-1} at k
-// (slots i+2..n), U_l at k (slot n+1+l).  State column j writes slot
-// (j <= i ? j : j+1) of every row i, -delta_ij - h dF_i/dX_j(k), and the +1
-// at slot j+1 of row j; control column l writes -h B_il at slot n+1+l.
-// ---------------------------------------------------------------------------
-template <int NPT>
-__device__ __forceinline__ void jac_column_euler(const KP &P, const double *__restrict__ z,
-                                                 double *__restrict__ jac, int64_t k, int col)
-{
-    const int n = P.n, T = P.T;
-    const int64_t N = P.N, N1 = P.N1;
-    const double h = P.h;
-    auto put = [&](int64_t i, int t, const double (&v)[NPT]) {
-        double *o = jac + ((int64_t)i * T + t) * N + k;
-        if constexpr (NPT == 2) st_nt2(o, dbl2{v[0], v[1]});
-        else st_nt(o, v[0]);
-    };
-    if (col < n) {
-        const int j = col;
-        const int jn = (j + 1 == n) ? 0 : j + 1;
-        const int jp = (j == 0) ? n - 1 : j - 1;
-        const double *xj = z + j * N1 + k;
-        const double *xn = z + jn * N1 + k;
-        const double *xp = z + jp * N1 + k;
-        double cs[NPT], dg[NPT], lo[NPT];
-#pragma unroll
-        for (int u = 0; u < NPT; u++) {
-            cs[u] = cos(xj[u]);
-            dg[u] = -h * P.gam[j] * xn[u];   // row i = j: gamma_j X_{j+1}
-            lo[u] = -h * P.gam[jp] * xp[u];  // row i = j-1: gamma_{j-1} X_{j-1}
-        }
-        for (int i = 0; i < n; i++) {
-            const double a = -h * P.A[i * n + j];
-            double v[NPT];
-#pragma unroll
-            for (int u = 0; u < NPT; u++) v[u] = a * cs[u];
-            if (i == j) {
-#pragma unroll
-                for (int u = 0; u < NPT; u++) v[u] += dg[u] - 1.0;
-            }
-            if (i == jp) {
-#pragma unroll
-                for (int u = 0; u < NPT; u++) v[u] += lo[u];
-            }
-            put(i, j <= i ? j : j + 1, v);
-        }
-        double one[NPT];
-#pragma unroll
-        for (int u = 0; u < NPT; u++) one[u] = 1.0;
-        put(j, j + 1, one);
-    } else {
-        const int l = col - n, m = P.m;
-        for (int i = 0; i < n; i++) {
-            double v[NPT];
-#pragma unroll
-            for (int u = 0; u < NPT; u++) v[u] = -h * P.B[i * m + l];
-            put(i, n + 1 + l, v);
-        }
-    }
-}
-
 // Forward Euler Hessian-of-Lagrangian values at node k <= N: node k enters
 // only the defect of interval k (multiplier y_k, factor h); node N enters no
 // defect and carries no cost, so its entries are zero.  Control slots exist
 // for k < N only, at (n+npair)(N+1) + l N + k.  NT as for hess_node.
+// ---------------------------------------------------------------------------
 template <int NB, bool NT>
 __device__ __forceinline__ void hess_node_euler(const KP &P, const double *__restrict__ z,
                                                 const double *__restrict__ y, double sigma,
@@ -470,10 +472,11 @@ __device__ __forceinline__ void hess_node_euler(const KP &P, const double *__res
 
 // Host-side launchers of the single-instance kernels (ocp_eval.hip,
 // ocp_fused.hip); the batched path uses them for its per-instance mode.
-// `pair_ok`: the Jacobian output is 16-byte aligned.  launch_obj's
-// `partials` holds min(4096, ceil((N+1) / 256)) doubles.  Each covers the
+// launch_obj's `partials` holds min(4096, ceil((N+1) / 256)) doubles.  Each covers the
 // problem's boundary rows too.
-hipError_t launch_jac(const KP &P, const double *z, double *jac, bool pair_ok, hipStream_t stream);
+// The Jacobian's slot rows all begin on a 128-byte line.
+inline bool jac_rows_on_lines(int64_t N, const void *jac) { return N % kLine == 0 && (uintptr_t)jac % 128 == 0; }
+hipError_t launch_jac(const KP &P, const double *z, double *jac, hipStream_t stream);
 hipError_t launch_hess(const KP &P, const double *z, const double *y, double sigma, double *hv,
                        hipStream_t stream);
 hipError_t launch_obj(const KP &P, const double *z, double *partials, double *obj, hipStream_t stream);

@@ -23,18 +23,24 @@ using namespace ocp::dev;
 namespace {
 
 // ---------------------------------------------------------------------------
-// Jacobian values.  2-D grid: blockIdx.x picks NPT intervals per lane,
-// blockIdx.y the column (state j < n, control n + l).  Many short lanes (a
-// grid of (N/NPT) x (n+m)) keep the write stream at the device's
-// streaming-store rate.
+// Jacobian values.  2-D grid: blockIdx.y is the column (state j < n, control
+// n + l), blockIdx.x the tile: kBlock intervals, one per lane, stored directly
+// (jac_kernel), or lines_span(kBlock) intervals stored in whole lines
+// (jac_lines_kernel).  Many short workgroups keep the write stream at the
+// device's rate for slot rows, 5.5-5.8 TB/s; see launch_jac for the choice.
 // ---------------------------------------------------------------------------
-template <int NPT>
-__global__ __launch_bounds__(kBlock) void jac_kernel(KP P, const double *__restrict__ z,
-                                                     double *__restrict__ jac)
+__global__ __launch_bounds__(kBlock) void jac_kernel(KP P, const double *__restrict__ z, double *__restrict__ jac)
 {
-    const int64_t k = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * NPT;
+    const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (k >= P.N) return;
-    jac_column<NPT>(P, z, jac, k, blockIdx.y);
+    jac_column(P, z, jac, k, blockIdx.y);
+}
+
+__global__ __launch_bounds__(kBlock) void jac_lines_kernel(KP P, const double *__restrict__ z,
+                                                           double *__restrict__ jac)
+{
+    __shared__ double lds[6 * kBlock];
+    jac_column_lines<kBlock>(P, z, jac, (int64_t)blockIdx.x * lines_span(kBlock), blockIdx.y, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -116,15 +122,6 @@ __global__ __launch_bounds__(kBlock) void bnd_jac_kernel(KP P, double *__restric
     const int b = blockIdx.x * kBlock + threadIdx.x;
     if (b >= P.nb) return;
     jac[(int64_t)P.n * P.N * P.T + b] = 1.0;
-}
-
-template <int NPT>
-__global__ __launch_bounds__(kBlock) void jac_euler_kernel(KP P, const double *__restrict__ z,
-                                                           double *__restrict__ jac)
-{
-    const int64_t k = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * NPT;
-    if (k >= P.N) return;
-    jac_column_euler<NPT>(P, z, jac, k, blockIdx.y);
 }
 
 template <int NB>
@@ -350,21 +347,25 @@ __global__ __launch_bounds__(kBlock) void assemble_kernel(
 namespace ocp {
 namespace dev {
 
-hipError_t launch_jac(const KP &P, const double *z, double *jac, bool pair_ok, hipStream_t stream)
+// Slot rows that begin on lines are stored directly, one interval per lane
+// (N = 1e6, n = 16, m = 8: 1.09 ms against 1.11 from LDS, and against 1.11 for
+// two intervals and a 16-byte store per lane); all others in whole lines from
+// LDS (N = 200,001, n = 16, m = 8, Euler: 203 -> 117 us; N = 333,333, n = 12,
+// m = 5: 370 -> 203 us), except outputs up to kJacSmall, the size of the L2s,
+// which merge the partial lines: there LDS and its barrier cost more (n = 8,
+// m = 4, directly against in lines: 31 MB 8.7 and 9.8 us, 61 MB 19.0 and 12.6;
+// N = 1000, n = 4, m = 2: 3.5 and 4.9).
+constexpr int64_t kJacSmall = 32 << 20;  // bytes
+
+hipError_t launch_jac(const KP &P, const double *z, double *jac, hipStream_t stream)
 {
-    // Paired 16-byte stores need every slot row 16-byte aligned: N even and
-    // the output 16-byte aligned.
     const unsigned cols = (unsigned)(P.n + P.m);
-    const bool pair = pair_ok && P.N % 2 == 0;
-    const dim3 g2((unsigned)((P.N / 2 + kBlock - 1) / kBlock), cols);
-    const dim3 g1((unsigned)((P.N + kBlock - 1) / kBlock), cols);
-    if (P.scheme == 0) {
-        if (pair) hipLaunchKernelGGL(jac_kernel<2>, g2, dim3(kBlock), 0, stream, P, z, jac);
-        else hipLaunchKernelGGL(jac_kernel<1>, g1, dim3(kBlock), 0, stream, P, z, jac);
-    } else {
-        if (pair) hipLaunchKernelGGL(jac_euler_kernel<2>, g2, dim3(kBlock), 0, stream, P, z, jac);
-        else hipLaunchKernelGGL(jac_euler_kernel<1>, g1, dim3(kBlock), 0, stream, P, z, jac);
-    }
+    const int64_t bytes = (int64_t)P.n * P.N * P.T * (int64_t)sizeof(double);
+    if (jac_rows_on_lines(P.N, jac) || bytes <= kJacSmall)
+        hipLaunchKernelGGL(jac_kernel, dim3(blocks_for(P.N, kBlock), cols), dim3(kBlock), 0, stream, P, z, jac);
+    else
+        hipLaunchKernelGGL(jac_lines_kernel, dim3(blocks_for((int64_t)P.N + kHalo, lines_span(kBlock)), cols),
+                           dim3(kBlock), 0, stream, P, z, jac);
     if (P.nb > 0)
         hipLaunchKernelGGL(bnd_jac_kernel, dim3((P.nb + kBlock - 1) / kBlock), dim3(kBlock), 0, stream,
                            P, jac);
@@ -595,7 +596,7 @@ int ocp_eval_jac(const ocp_problem *p, const double *z, double *jvals, hipStream
     if (int rc = check_handle(p, "ocp_eval_jac")) return rc;
     if (!z || !jvals) return fail(OCP_ERR_ARG, "ocp_eval_jac: null array");
     if (p->model == quad::kModel) return quad::eval_jac(p, z, jvals, stream);
-    const hipError_t e = launch_jac(p->kp, z, jvals, (uintptr_t)jvals % 16 == 0, stream);
+    const hipError_t e = launch_jac(p->kp, z, jvals, stream);
     if (e != hipSuccess) return hip_fail("ocp_eval_jac", e);
     return OCP_OK;
 }

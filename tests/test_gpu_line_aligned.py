@@ -95,3 +95,40 @@ def test_assembly_tiles(ocp, N, n, m, scheme, bnd, offset):
             want = oracle.assemble(rp, maps, jv, ph, hv, r)
             assert np.array_equal(out.values().view(np.uint64), want.view(np.uint64))
     prob.close()
+
+
+# slot rows are stored in whole lines above 32 MiB of output unless every row
+# begins on a line; a tile holds 496 intervals and reaches 15 before its start
+@pytest.mark.parametrize("N,n,m,scheme,bnd,offset", [
+    (89280, 4, 2, 0, 0, 0), (89281, 4, 2, 0, 2, 1), (89265, 4, 2, 0, 0, 15), (178531, 4, 2, 1, 1, 7),
+    (120011, 6, 1, 1, 2, 8), (524289, 2, 0, 0, 0, 3), (1048579, 1, 1, 0, 1, 4), (2100007, 1, 0, 1, 0, 9),
+    (60000, 5, 3, 0, 0, 0), (60000, 5, 3, 0, 0, 16), (98000, 5, 3, 1, 0, 8), (8001, 16, 8, 0, 0, 2)])
+def test_jacobian_lines(ocp, N, n, m, scheme, bnd, offset):
+    print(f"[lines] jacobian N={N} n={n} m={m} scheme={scheme} bnd={bnd} offset={offset}", flush=True)
+    inst = synth.make_instance(N, n, m, seed=72, bnd=bnd, scheme=scheme)
+    prob = ocp.Problem.from_instance(inst, torch.device("cuda", 0))
+    out = Guarded(prob.sizes["nnzj"], offset)
+    prob.jac(_t(inst.z), out=out.out)
+    want, mu = oracle.jac_ex(inst, scheme, bnd)
+    check_close(out.values(), want, mu, what="jac")
+    prob.close()
+
+
+@pytest.mark.parametrize("scheme,bnd", [(0, 0), (0, 1), (1, 2)])
+def test_batched_jacobian_lines_match_per_instance(ocp, scheme, bnd):
+    """Instances around a tile of 496 (256 lanes) or 240 (128 lanes) intervals,
+    and ones whose rows begin on lines, at an output off the line."""
+    Ns = [496, 481, 482, 480, 240, 225, 226, 1, 16, 15, 17, 2049, 992, 977]
+    insts = synth.make_batch(len(Ns), 5, 2, seed=4, Ns=Ns, scheme=scheme, bnd=bnd)
+    batch = ocp.Batch.from_instances(insts, scheme=scheme, boundary=bnd)
+    z, _ = synth.pack(insts)
+    z, total = _t(z), int(batch.offsets["jac"][-1])
+    want = batch.eval(z, what=ocp.EVAL_JAC, mode="per_instance")[0].cpu().numpy()
+    for block in (128, 256):
+        for wgs in (0, 1):
+            batch.config = {"block": block, "pair": 1, "wgs_per_cu": wgs, "order": 1}
+            for offset in (0, 1, 8):
+                out = Guarded(total, offset)
+                batch.eval(z, jac=out.out, what=ocp.EVAL_JAC)
+                assert np.array_equal(out.values().view(np.uint64), want.view(np.uint64))
+    batch.close()
