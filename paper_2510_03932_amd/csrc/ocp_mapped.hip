@@ -14,7 +14,19 @@
 // ocp_stage_order), the values are staged in LDS and the range is written
 // with contiguous stores, else every value is stored at its slot.  The
 // ranges depend on the slot maps only, so ocp_mapped_plan can record them
-// once and later assemblies skip the first pass.  The result is the same for
+// once and later assemblies skip the first pass.
+//
+// Reading bounds it: a tile takes KT consecutive values and slots of every
+// slot row, runs of 64 to 256 bytes that share their 128-byte lines with the
+// neighbouring tiles.  Each XCD therefore takes a contiguous run of the tiles,
+// so that a line fetched for one tile is found in the L2 by the next.  With
+// that, four entries in flight per lane and tiles of twice the height (runs of
+// 128 bytes at n = 8, m = 4), against tiles dealt round-robin over the XCDs:
+// 159 -> 81 us at N = 1e5, n = 8, m = 4 (2.8 -> 5.6 TB/s), 94 -> 38 us at
+// N = 60,361, n = 10, m = 5 (Euler), 279 -> 115 us at N = 22,869, n = 18,
+// m = 10, 491 -> 404 us for the quadrotor at N = 1e6.  Twice that height again
+// costs occupancy (quadrotor 446 us), non-temporal loads lose the shared lines
+// (n = 18: 186 us).  The result is the same for
 // every injective slot map; no atomics touch global memory.
 #include <hip/hip_runtime.h>
 
@@ -32,8 +44,10 @@ using namespace ocp::dev;
 
 namespace {
 
-constexpr int kMapTarget = 2048;  // values staged per workgroup when a node fits (16 KiB)
-constexpr int kMapCap = 7936;     // most values staged per workgroup (62 KiB of LDS)
+constexpr int kMapTarget = 4096;       // values staged per workgroup (32 KiB of LDS)
+constexpr int kMapTargetSmall = 2048;  // the same for grids too short to give every CU two such tiles
+constexpr int kMapCap = 9216;          // most values staged per workgroup (72 KiB, two workgroups per CU)
+constexpr int kMapBatch = 4;           // Jacobian entries in flight per lane
 
 struct MP {
     int N, N1, NU;
@@ -71,84 +85,99 @@ __device__ __forceinline__ int64_t hess_diag_row(const MP &P, int s, int64_t k)
 }
 
 // Every entry of tile `tb` (nodes [tb KT, tb KT + KT)) is passed to
-// put(slot, value); with_values = false skips the value loads.
-template <class F>
+// put(slot, value); without VALUES the values are not loaded.  The Jacobian
+// entries, nine tenths of a tile, come kMapBatch at a time so that their loads
+// are in flight together.
+template <bool VALUES, class F>
 __device__ __forceinline__ void tile_visit(const MP &P, int64_t tb, const int32_t *__restrict__ perm_j,
                                            const int32_t *__restrict__ perm_h, const int32_t *__restrict__ diag,
                                            const double *__restrict__ jv, const double *__restrict__ hv,
-                                           const double *__restrict__ reg, bool with_values, F put)
+                                           const double *__restrict__ reg, F put)
 {
     const int KT = P.KT, lg = P.lgKT;
     const int64_t k0 = tb * KT;
     const int64_t N = P.N, N1 = P.N1, NU = P.NU;
-    const int nJ = P.nJ, sA = P.sA, sB = P.sB, n = P.n;
-    // segment sizes of the tile's work list
-    const int s1 = nJ << lg, s2 = sA << lg, s3 = sB << lg, s4 = n << lg, s5 = 2 * n;
-    const int total = s1 + s2 + s3 + s4 + s5;
+    const int sA = P.sA, n = P.n;
+    const int jac_total = P.nJ << lg;
+    for (int w0 = threadIdx.x; w0 < jac_total; w0 += kBlock * kMapBatch) {
+        int32_t q[kMapBatch];
+        double v[kMapBatch];
+        bool live[kMapBatch];
+#pragma unroll
+        for (int u = 0; u < kMapBatch; u++) {
+            const int w = w0 + u * kBlock;
+            const int sigma = w >> lg;
+            const int64_t k = k0 - jac_side(P, sigma) + (w & (KT - 1));
+            live[u] = w < jac_total && k >= 0 && k < N;
+            if (live[u]) {
+                const int64_t e = (int64_t)sigma * N + k;
+                q[u] = perm_j[e];
+                v[u] = VALUES ? jv[e] : 0.0;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kMapBatch; u++)
+            if (live[u]) put(q[u], v[u]);
+    }
+    // segment sizes of the rest of the tile's work list
+    const int s2 = sA << lg, s3 = P.sB << lg, s4 = n << lg, s5 = 2 * n;
+    const int total = s2 + s3 + s4 + s5;
     const bool first = k0 == 0, last = k0 + KT > N;
     for (int w = threadIdx.x; w < total; w += kBlock) {
         int32_t q;
         double v = 0.0;
-        if (w < s1) {
-            const int sigma = w >> lg;
-            const int64_t k = k0 - jac_side(P, sigma) + (w & (KT - 1));
-            if (k < 0 || k >= N) continue;
-            const int64_t e = (int64_t)sigma * N + k;
-            q = perm_j[e];
-            if (with_values) v = jv[e];
-        } else if (w < s1 + s2) {
-            const int x = w - s1;
-            const int s = x >> lg;
-            const int64_t k = k0 + (x & (KT - 1));
+        if (w < s2) {
+            const int s = w >> lg;
+            const int64_t k = k0 + (w & (KT - 1));
             if (k >= N1) continue;
             const int64_t e = (int64_t)s * N1 + k;
             q = perm_h[e];
-            if (with_values) {
+            if (VALUES) {
                 v = hv[e];
                 if (reg) {
                     const int64_t row = hess_diag_row(P, s, k);
                     if (row >= 0) v += reg[row];
                 }
             }
-        } else if (w < s1 + s2 + s3) {
-            const int x = w - s1 - s2;
+        } else if (w < s2 + s3) {
+            const int x = w - s2;
             const int l = x >> lg;
             const int64_t k = k0 + (x & (KT - 1));
             if (k >= NU) continue;
             const int64_t e = (int64_t)sA * N1 + (int64_t)l * NU + k;
             q = perm_h[e];
-            if (with_values) {
+            if (VALUES) {
                 v = hv[e];
                 if (reg) v += reg[(int64_t)n * N1 + (int64_t)l * NU + k];
             }
-        } else if (w < s1 + s2 + s3 + s4) {
-            const int x = w - s1 - s2 - s3;
+        } else if (w < s2 + s3 + s4) {
+            const int x = w - s2 - s3;
             const int i = x >> lg;
             const int64_t k = k0 + (x & (KT - 1));
             if (k >= N) continue;
             const int64_t row = P.nvar + (int64_t)i * N + k;
             q = diag[row];
-            if (with_values && reg) v = reg[row];
+            if (VALUES && reg) v = reg[row];
         } else {
             // boundary rows: the initial ones with node 0, the final ones with node N
-            const int b = w - s1 - s2 - s3 - s4;
+            const int b = w - s2 - s3 - s4;
             if (b >= P.nb) continue;
             if (b < n ? !first : !last) continue;
             const int64_t e = P.nnzj_def + b;
             const int64_t row = P.nvar + P.ndef + b;
             q = perm_j[e];
-            if (with_values) v = jv[e];
+            if (VALUES) v = jv[e];
             put(q, v);
             q = diag[row];
-            v = (with_values && reg) ? reg[row] : 0.0;
+            v = (VALUES && reg) ? reg[row] : 0.0;
         }
         put(q, v);
     }
 }
 
-// Range of tile blockIdx.x's slots: (base, count) with base = -1 unless the
+// Range of tile `tb`'s slots: (base, count) with base = -1 unless the
 // slots fill [base, base + count) exactly and the range fits the LDS tile.
-__device__ __forceinline__ int2 tile_range(const MP &P, const int32_t *__restrict__ perm_j,
+__device__ __forceinline__ int2 tile_range(const MP &P, int64_t tb, const int32_t *__restrict__ perm_j,
                                            const int32_t *__restrict__ perm_h, const int32_t *__restrict__ diag)
 {
     __shared__ int smin, smax, scount;
@@ -159,7 +188,7 @@ __device__ __forceinline__ int2 tile_range(const MP &P, const int32_t *__restric
     }
     __syncthreads();
     int lmin = INT_MAX, lmax = INT_MIN, lcount = 0;
-    tile_visit(P, blockIdx.x, perm_j, perm_h, diag, nullptr, nullptr, nullptr, false, [&](int32_t q, double) {
+    tile_visit<false>(P, tb, perm_j, perm_h, diag, nullptr, nullptr, nullptr, [&](int32_t q, double) {
         lmin = min(lmin, (int)q);
         lmax = max(lmax, (int)q);
         lcount++;
@@ -181,10 +210,11 @@ __global__ __launch_bounds__(kBlock) void mapped_plan_kernel(MP P, const int32_t
                                                              const int32_t *__restrict__ diag,
                                                              int32_t *__restrict__ plan)
 {
-    const int2 r = tile_range(P, perm_j, perm_h, diag);
+    const uint32_t tb = xcd_order(blockIdx.x, gridDim.x);
+    const int2 r = tile_range(P, tb, perm_j, perm_h, diag);
     if (threadIdx.x == 0) {
-        plan[2 * blockIdx.x] = r.x;
-        plan[2 * blockIdx.x + 1] = r.y;
+        plan[2 * tb] = r.x;
+        plan[2 * tb + 1] = r.y;
     }
 }
 
@@ -195,14 +225,15 @@ __global__ __launch_bounds__(kBlock) void mapped_assemble_kernel(
 {
     extern __shared__ double tile[];  // the tile's entries (host-sized, <= kMapCap)
     __shared__ int filled;            // tile slots written by this tile's entries
+    const uint32_t tb = xcd_order(blockIdx.x, gridDim.x);
     int base, count;
     if (plan) {
-        base = plan[2 * blockIdx.x];
-        count = plan[2 * blockIdx.x + 1];
+        base = plan[2 * tb];
+        count = plan[2 * tb + 1];
         // a plan from other slot maps must not send stores out of bounds
         if (base < 0 || count < 1 || count > P.cap || (int64_t)base + count > P.nnzk) base = -1;
     } else {
-        const int2 r = tile_range(P, perm_j, perm_h, diag);
+        const int2 r = tile_range(P, tb, perm_j, perm_h, diag);
         base = r.x;
         count = r.y;
     }
@@ -210,7 +241,7 @@ __global__ __launch_bounds__(kBlock) void mapped_assemble_kernel(
         if (threadIdx.x == 0) filled = 0;
         __syncthreads();
         int mine = 0;
-        tile_visit(P, blockIdx.x, perm_j, perm_h, diag, jv, hv, reg, true, [&](int32_t q, double v) {
+        tile_visit<true>(P, tb, perm_j, perm_h, diag, jv, hv, reg, [&](int32_t q, double v) {
             const uint32_t loc = (uint32_t)q - (uint32_t)base;
             if (loc < (uint32_t)count) {
                 tile[loc] = v;
@@ -225,22 +256,23 @@ __global__ __launch_bounds__(kBlock) void mapped_assemble_kernel(
         __syncthreads();
         if (filled == count) {
             // the tile's slots (distinct, the maps being injective) cover the
-            // range exactly: write it with contiguous stores
-            double *out = kkt + base;
-            for (int x = threadIdx.x; x < count; x += kBlock) st_nt(out + x, tile[x]);
+            // range exactly: write it in whole lines
+            copy_lines<kBlock>(kkt + base, tile, count);
             return;
         }
         // else a plan made from other slot maps: the staged values go to
         // their slots one by one below (values stored above are stored again)
     }
-    tile_visit(P, blockIdx.x, perm_j, perm_h, diag, jv, hv, reg, true, [&](int32_t q, double v) {
+    tile_visit<true>(P, tb, perm_j, perm_h, diag, jv, hv, reg, [&](int32_t q, double v) {
         if ((uint32_t)q < (uint32_t)P.nnzk) kkt[q] = v;
     });
 }
 
 // Tile shape for a handle: the largest power of two of nodes whose entries
-// fit a 16 KiB tile (small tiles keep several workgroups per CU), but at
-// least 4 nodes while they fit the 62 KiB maximum.
+// fit a 32 KiB tile (five workgroups per CU), 16 KiB where that would leave
+// fewer than two tiles per CU, but at least 8 nodes (half a line of values)
+// while they fit the 72 KiB maximum: at n = 18, m = 10, 8 nodes in 69 KiB take
+// 115 us and 4 nodes 148 us (N = 22,869).
 MP make_mp(const ocp_problem *p)
 {
     const Dims &d = p->d;
@@ -265,8 +297,10 @@ MP make_mp(const ocp_problem *p)
     const int64_t per_node = (int64_t)P.nJ + P.sA + P.sB + P.n;
     auto need = [&](int lgk) { return ((int64_t)1 << lgk) * per_node + 2 * P.n; };
     int lg = 0;
-    while (lg < 10 && need(lg + 1) <= kMapTarget) lg++;
-    while (lg < 2 && need(lg + 1) <= kMapCap) lg++;
+    while (lg < 10 && need(lg + 1) <= kMapTargetSmall) lg++;
+    const bool many = (P.N1 >> (lg + 1)) >= 512;
+    while (many && lg < 10 && need(lg + 1) <= kMapTarget) lg++;
+    while (lg < 3 && need(lg + 1) <= kMapCap) lg++;
     P.KT = 1 << lg;
     P.lgKT = lg;
     P.cap = (int)need(lg);
@@ -332,6 +366,14 @@ int ocp_assemble_kkt_mapped(const ocp_problem *p, const int32_t *perm_j, const i
             }
             plan = p->mplan;
         }
+    }
+    if ((size_t)P.cap * sizeof(double) > 64 * 1024) {
+        // more dynamic LDS than a kernel may take unasked; set on every such
+        // call, since the attribute belongs to the current device
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(mapped_assemble_kernel),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 kMapCap * (int)sizeof(double));
+        if (e != hipSuccess) return hip_fail("ocp_assemble_kkt_mapped: LDS size", e);
     }
     hipLaunchKernelGGL(mapped_assemble_kernel, dim3(blocks_for(p->d.N1, P.KT)), dim3(kBlock),
                        (size_t)P.cap * sizeof(double), stream, P, plan, perm_j, perm_h, diag, jvals, hvals, reg, kkt);

@@ -132,3 +132,34 @@ def test_batched_jacobian_lines_match_per_instance(ocp, scheme, bnd):
                 batch.eval(z, jac=out.out, what=ocp.EVAL_JAC)
                 assert np.array_equal(out.values().view(np.uint64), want.view(np.uint64))
     batch.close()
+
+
+# the mapped assembly's tiles hold 32 KiB of values from 512 of them, else
+# 16 KiB, and at least 8 nodes while those fit 72 KiB (more LDS than 64 KiB
+# needs the kernel's attribute, also when the call is captured)
+@pytest.mark.parametrize("N,n,m,scheme,bnd,offset", [
+    (32767, 3, 1, 0, 0, 1), (32766, 3, 1, 0, 1, 0), (33001, 3, 1, 1, 2, 15), (100, 18, 10, 0, 2, 8),
+    (37, 24, 20, 0, 0, 3), (50, 32, 32, 1, 1, 5), (4, 20, 0, 0, 2, 7)])
+def test_mapped_assembly_tiles(ocp, N, n, m, scheme, bnd, offset):
+    print(f"[lines] mapped N={N} n={n} m={m} scheme={scheme} bnd={bnd} offset={offset}", flush=True)
+    prob = ocp.Problem(N, n, m, np.zeros((n, n)), np.zeros((n, m)), np.zeros(n), np.ones(n), np.ones(m),
+                       scheme=scheme, boundary=bnd)
+    s = prob.sizes
+    rng = np.random.default_rng(3)
+    jv, hv, reg = (rng.normal(size=s[k]) for k in ("nnzj", "nnzh", "dim"))
+    maps = ocp.kkt_permute(*prob.kkt_pattern(), ocp.stage_order(N, n, m, scheme, bnd))[2:]
+    want = oracle.assemble_mapped(s["nnzk"], maps[2], maps[0], jv, maps[1], hv, reg)
+    dmaps, args = [_t(a) for a in maps], [_t(a) for a in (jv, hv, reg)]
+    for plan in (None, prob.mapped_plan(*dmaps)):
+        out = Guarded(s["nnzk"], offset)
+        prob.assemble_kkt_mapped(*dmaps, *args, out=out.out, plan=plan)
+        assert np.array_equal(out.values().view(np.uint64), want.view(np.uint64))
+    graph, out = torch.cuda.CUDAGraph(), Guarded(s["nnzk"], offset)
+    with torch.cuda.graph(graph):
+        prob.assemble_kkt_mapped(*dmaps, *args, out=out.out, plan=plan)
+    for _ in range(3):
+        out.out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(out.values().view(np.uint64), want.view(np.uint64))
+    prob.close()
