@@ -27,6 +27,11 @@ typedef double dbl2 __attribute__((ext_vector_type(2)));
 typedef double d4 __attribute__((ext_vector_type(4)));  // FP64 MFMA 16x16 accumulator
 typedef int32_t int2v __attribute__((ext_vector_type(2)));
 
+// pairs loaded from any element of an array
+typedef double dbl2_any __attribute__((ext_vector_type(2), aligned(8)));
+typedef int32_t int2_any __attribute__((ext_vector_type(2), aligned(4)));
+constexpr int kAsmBatch = 4;  // pairs in flight per lane in the KKT assembly
+
 constexpr int kBlock = 256;  // threads per workgroup of the single-instance kernels (4 waves)
 
 // Kernel-side view of one problem: sizes and device coefficient pointers.
@@ -474,6 +479,9 @@ __device__ __forceinline__ void hess_node_euler(const KP &P, const double *__res
 // ocp_fused.hip); the batched path uses them for its per-instance mode.
 // launch_obj's `partials` holds min(4096, ceil((N+1) / 256)) doubles.  Each covers the
 // problem's boundary rows too.
+// Jacobian outputs up to this many bytes (the 8 L2s of 4 MiB) are stored
+// directly: the caches merge the partial lines (see launch_jac).
+constexpr int64_t kJacSmall = 32 << 20;
 // The Jacobian's slot rows all begin on a 128-byte line.
 inline bool jac_rows_on_lines(int64_t N, const void *jac) { return N % kLine == 0 && (uintptr_t)jac % 128 == 0; }
 hipError_t launch_jac(const KP &P, const double *z, double *jac, hipStream_t stream);

@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kBlock) void obj_final_kernel(const double *__restr
 // Reading bounds it: each slot row gives a tile KT 4-byte slots and KT values,
 // which at an odd N start anywhere in a line.  So each lane takes two adjacent
 // intervals of a slot row with one 16-byte and one 8-byte load at any
-// alignment, four slot rows' loads are in flight per lane, and a tile is as
+// alignment, kAsmBatch slot rows' loads are in flight per lane, and a tile is as
 // tall as its LDS allows.  Against tiles of 64 rows, one slot row at a time and
 // 8-byte loads at odd entries: 452 -> 339 us at N = 200,001, n = 16, m = 8
 // (forward Euler), 718 -> 592 us at N = 333,333, n = 12, m = 5 (5.1 TB/s),
@@ -205,10 +205,6 @@ __global__ __launch_bounds__(kBlock) void obj_final_kernel(const double *__restr
 // reg on the variable diagonals in the same IEEE add; the loads of kHessBatch
 // slots are issued before their stores.
 // ---------------------------------------------------------------------------
-typedef double dbl2_any __attribute__((ext_vector_type(2), aligned(8)));     // at any element
-typedef int32_t int2_any __attribute__((ext_vector_type(2), aligned(4)));
-
-constexpr int kAsmBatch = 4;   // slot rows in flight per lane (Jacobian part)
 constexpr int kHessBatch = 8;  // slots in flight per lane (Hessian part)
 
 __global__ __launch_bounds__(kBlock) void assemble_kernel(
@@ -355,8 +351,6 @@ namespace dev {
 // which merge the partial lines: there LDS and its barrier cost more (n = 8,
 // m = 4, directly against in lines: 31 MB 8.7 and 9.8 us, 61 MB 19.0 and 12.6;
 // N = 1000, n = 4, m = 2: 3.5 and 4.9).
-constexpr int64_t kJacSmall = 32 << 20;  // bytes
-
 hipError_t launch_jac(const KP &P, const double *z, double *jac, hipStream_t stream)
 {
     const unsigned cols = (unsigned)(P.n + P.m);

@@ -43,69 +43,116 @@ __device__ __forceinline__ void load_att(const QP &P, const double *__restrict__
 }
 
 // ---------------------------------------------------------------------------
-// Jacobian values.  2-D grid: blockIdx.y is the defect row i, blockIdx.x
-// picks NPT intervals per lane.  Row i's 2 kSupLen[i] slots are stored as
-// unit-stride runs across lanes (16-byte pairs for NPT = 2).  Rows 1, 3, 5,
-// 6, 7, 8 need the attitude trigonometry of NPT + 1 nodes; rows 0, 2, 4 are
-// constants.
+// Jacobian values.  2-D grid: blockIdx.y is the defect row i, blockIdx.x the
+// tile.  Row i's 2 kSupLen[i] slots are unit-stride runs across lanes.  Rows 1,
+// 3, 5, 6, 7, 8 need the attitude trigonometry of a node; rows 0, 2, 4 are
+// constants.  quad_jac_kernel stores one interval per lane directly (two
+// nodes' trigonometry each): the path of outputs that fit the L2s.
+// quad_jac_lines_kernel takes tiles of lines_span(kBlock) intervals, evaluates
+// each node's partials once into LDS and stores every slot row in whole lines
+// (see store_row_lines): 32 -> 20 us at N = 200,001 (5.9 TB/s written), 23 ->
+// 20 us at N = 2e5 and 109 -> 105 us at N = 1e6, where two intervals per lane
+// were stored directly.
 // ---------------------------------------------------------------------------
-template <int I, int NPT>
+template <int I>
+constexpr bool kRowHasTrig = !(I == 0 || I == 2 || I == 4);
+
+// The identity's part of row I's p-th support variable at side s.
+__device__ __forceinline__ double jac_id(int i, int p, int s)
+{
+    return pair_is_own_state(i, p) ? (s ? 1.0 : -1.0) : 0.0;
+}
+
+template <int I>
 __device__ __forceinline__ void jac_row(const QP &P, const double *__restrict__ z, double *__restrict__ jac,
                                         int64_t k)
 {
-    constexpr bool kTrig = !(I == 0 || I == 2 || I == 4);
-    constexpr int L = kSupLen[I];
-    Trig t[NPT + 1];
-    double u[NPT + 1][4];
-    if constexpr (kTrig) {
+    Trig t[2] = {};
+    double u[2][4] = {};
+    if constexpr (kRowHasTrig<I>) {
 #pragma unroll
-        for (int j = 0; j <= NPT; j++) {
+        for (int j = 0; j < 2; j++) {
             double a[3];
             load_att(P, z, k + j, a, u[j]);
             t[j] = node_trig(a[0], a[1], a[2]);
         }
-    } else {
-#pragma unroll
-        for (int j = 0; j <= NPT; j++) {
-            t[j] = Trig{};
-#pragma unroll
-            for (int l = 0; l < 4; l++) u[j][l] = 0.0;
-        }
     }
-    const int64_t N = P.N;
 #pragma unroll
-    for (int p = 0; p < L; p++) {
-        const int q = pair_index(I, p);
-        const bool own = pair_is_own_state(I, p);
+    for (int p = 0; p < kSupLen[I]; p++)
 #pragma unroll
-        for (int s = 0; s < 2; s++) {
-            const double id = own ? (s ? 1.0 : -1.0) : 0.0;
-            double v[NPT];
-#pragma unroll
-            for (int j = 0; j < NPT; j++) v[j] = id - P.hh * partial(q, t[j + s], u[j + s]);
-            double *o = jac + (int64_t)(kRowSlot[I] + 2 * p + s) * N + k;
-            if constexpr (NPT == 2) st_nt2(o, dbl2{v[0], v[1]});
-            else st_nt(o, v[0]);
-        }
-    }
+        for (int s = 0; s < 2; s++)
+            st_nt(jac + (int64_t)(kRowSlot[I] + 2 * p + s) * P.N + k,
+                  __builtin_fma(-P.hh, partial(pair_index(I, p), t[s], u[s]), jac_id(I, p, s)));
 }
 
-template <int NPT>
+template <int I>
+__device__ __forceinline__ void jac_row_lines(const QP &P, const double *__restrict__ z, double *__restrict__ jac,
+                                              int64_t k0, double *lds)
+{
+    constexpr int L = kSupLen[I], W = 2 * kBlock;
+    const int64_t N = P.N;
+    if constexpr (kRowHasTrig<I>) {
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+            const int x = (int)threadIdx.x + j * kBlock;
+            const int64_t k = min(max(k0 - kHalo + x, (int64_t)0), N);  // clamped: values past the ends are not stored
+            double a[3], u[4];
+            load_att(P, z, k, a, u);
+            const Trig t = node_trig(a[0], a[1], a[2]);
+#pragma unroll
+            for (int p = 0; p < L; p++) lds[p * W + x] = partial(pair_index(I, p), t, u);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int p = 0; p < L; p++)
+#pragma unroll
+        for (int s = 0; s < 2; s++) {
+            double *row = jac + (int64_t)(kRowSlot[I] + 2 * p + s) * N;
+            const double id = jac_id(I, p, s);
+            if constexpr (kRowHasTrig<I>) {
+                store_row_lines<kBlock>(row, N, k0,
+                                        [&](int x) { return __builtin_fma(-P.hh, lds[p * W + x + s], id); });
+            } else {
+                const double v = __builtin_fma(-P.hh, partial(pair_index(I, p), Trig{}, nullptr), id);
+                store_row_lines<kBlock>(row, N, k0, [&](int) { return v; });
+            }
+        }
+}
+
 __global__ __launch_bounds__(kBlock) void quad_jac_kernel(QP P, const double *__restrict__ z,
                                                           double *__restrict__ jac)
 {
-    const int64_t k = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * NPT;
+    const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (k >= P.N) return;
     switch (blockIdx.y) {
-    case 0: jac_row<0, NPT>(P, z, jac, k); break;
-    case 1: jac_row<1, NPT>(P, z, jac, k); break;
-    case 2: jac_row<2, NPT>(P, z, jac, k); break;
-    case 3: jac_row<3, NPT>(P, z, jac, k); break;
-    case 4: jac_row<4, NPT>(P, z, jac, k); break;
-    case 5: jac_row<5, NPT>(P, z, jac, k); break;
-    case 6: jac_row<6, NPT>(P, z, jac, k); break;
-    case 7: jac_row<7, NPT>(P, z, jac, k); break;
-    default: jac_row<8, NPT>(P, z, jac, k); break;
+    case 0: jac_row<0>(P, z, jac, k); break;
+    case 1: jac_row<1>(P, z, jac, k); break;
+    case 2: jac_row<2>(P, z, jac, k); break;
+    case 3: jac_row<3>(P, z, jac, k); break;
+    case 4: jac_row<4>(P, z, jac, k); break;
+    case 5: jac_row<5>(P, z, jac, k); break;
+    case 6: jac_row<6>(P, z, jac, k); break;
+    case 7: jac_row<7>(P, z, jac, k); break;
+    default: jac_row<8>(P, z, jac, k); break;
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void quad_jac_lines_kernel(QP P, const double *__restrict__ z,
+                                                                double *__restrict__ jac)
+{
+    __shared__ double lds[6 * 2 * kBlock];
+    const int64_t k0 = (int64_t)blockIdx.x * lines_span(kBlock);
+    switch (blockIdx.y) {
+    case 0: jac_row_lines<0>(P, z, jac, k0, lds); break;
+    case 1: jac_row_lines<1>(P, z, jac, k0, lds); break;
+    case 2: jac_row_lines<2>(P, z, jac, k0, lds); break;
+    case 3: jac_row_lines<3>(P, z, jac, k0, lds); break;
+    case 4: jac_row_lines<4>(P, z, jac, k0, lds); break;
+    case 5: jac_row_lines<5>(P, z, jac, k0, lds); break;
+    case 6: jac_row_lines<6>(P, z, jac, k0, lds); break;
+    case 7: jac_row_lines<7>(P, z, jac, k0, lds); break;
+    default: jac_row_lines<8>(P, z, jac, k0, lds); break;
     }
 }
 
@@ -279,18 +326,21 @@ __global__ __launch_bounds__(kBlock) void quad_grad_kernel(QP P, const double *_
 // contiguous stores when the tile's values cover it exactly, as the
 // closed-form maps do; otherwise the tile stores each value directly, so any
 // injective slot map gives the same result.  Blocks after the groups handle
-// the boundary rows.
+// the boundary rows.  As in the synthetic family's assembly the reads bound it
+// and are paired, batched and independent of the alignment: 405 -> 387 us at
+// N = 1e6 (5.0 TB/s), 79 -> 74 us at N = 200,001, 8.6 -> 7.8 us at N = 1200.
+// Tiles of 3072 and 4096 values gain 1 % at N = 1e6 and lose 4-8 % at 2e5.
 // ---------------------------------------------------------------------------
 constexpr int kGroups = kStates + kVars;
 constexpr int kTileCap = 2048;  // values staged per workgroup (16 KiB of LDS)
 
 struct AsmGroups {
     int tile0[kGroups + 1];  // first workgroup of each group; tile0[kGroups] = first boundary workgroup
-    int KT[kGroups];         // rows per tile (even)
+    int KT[kGroups];         // rows per tile (a multiple of 16)
 };
 
 __global__ __launch_bounds__(kBlock) void quad_assemble_kernel(
-    QP P, AsmGroups G, int nnzk, bool vec_j, bool vec_h, const int32_t *__restrict__ perm_j,
+    QP P, AsmGroups G, int nnzk, const int32_t *__restrict__ perm_j,
     const int32_t *__restrict__ perm_h, const int32_t *__restrict__ rowptr, const double *__restrict__ jv,
     const double *__restrict__ hv, const double *__restrict__ reg, double *__restrict__ kkt)
 {
@@ -324,7 +374,6 @@ __global__ __launch_bounds__(kBlock) void quad_assemble_kernel(
     const int64_t d0 = is_h ? gi * N1 + k0 : nvar + gi * N + k0;  // first KKT row of the tile
     const int32_t *perm = is_h ? perm_h : perm_j;
     const double *src = is_h ? hv : jv;
-    const bool vec = is_h ? vec_h : vec_j;
     const int32_t base = rowptr[d0];
     const int32_t ext = (int32_t)((uint32_t)rowptr[d0 + kn] - (uint32_t)base);
     // stage only a range inside [0, nnzk) (a corrupt rowptr falls back to
@@ -335,37 +384,42 @@ __global__ __launch_bounds__(kBlock) void quad_assemble_kernel(
     const int half = KT / 2;
 
     // Visit every (slot, value) of the tile; `put` decides where it goes.
+    // Each lane takes two adjacent rows of a slot at a time, at any alignment,
+    // kAsmBatch of them in flight.
     auto visit = [&](auto put) {
-        for (int w = threadIdx.x; w < count * half; w += kBlock) {
-            const int t = w / half;
-            const int kl = 2 * (w - t * half);
-            if (kl >= kn) continue;
-            const int64_t e = (int64_t)(first + t) * stride + k0 + kl;
-            const bool diag = is_h && t == count - 1;
-            const bool two = kl + 1 < kn;
-            double v0, v1 = 0.0;
-            int32_t q0, q1 = 0;
-            if (vec && two && (e & 1) == 0) {
-                const dbl2 v = __builtin_nontemporal_load(reinterpret_cast<const dbl2 *>(src + e));
-                const int2v q = __builtin_nontemporal_load(reinterpret_cast<const int2v *>(perm + e));
-                v0 = v.x;
-                v1 = v.y;
-                q0 = q.x;
-                q1 = q.y;
-            } else {
-                v0 = src[e];
-                q0 = perm[e];
-                if (two) {
-                    v1 = src[e + 1];
-                    q1 = perm[e + 1];
+        const int total = count * half;
+        for (int w0 = threadIdx.x; w0 < total; w0 += kBlock * kAsmBatch) {
+            int2_any q[kAsmBatch];
+            dbl2_any v[kAsmBatch];
+            double g[kAsmBatch][2];
+            int live[kAsmBatch];
+#pragma unroll
+            for (int u = 0; u < kAsmBatch; u++) {
+                const int w = w0 + u * kBlock;
+                const int t = w / half;
+                const int kl = 2 * (w - t * half);
+                const int64_t e = (int64_t)(first + t) * stride + k0 + kl;
+                const bool diag = is_h && reg && t == count - 1;
+                live[u] = w < total ? min(kn - kl, 2) : 0;
+                g[u][0] = g[u][1] = 0.0;
+                if (live[u] == 2) {
+                    q[u] = __builtin_nontemporal_load(reinterpret_cast<const int2_any *>(perm + e));
+                    v[u] = __builtin_nontemporal_load(reinterpret_cast<const dbl2_any *>(src + e));
+                } else if (live[u] == 1) {
+                    q[u].x = perm[e];
+                    v[u].x = src[e];
                 }
+                if (diag && live[u] >= 1) g[u][0] = reg[d0 + kl];
+                if (diag && live[u] == 2) g[u][1] = reg[d0 + kl + 1];
             }
-            if (diag && reg) {
-                v0 += reg[d0 + kl];
-                if (two) v1 += reg[d0 + kl + 1];
+#pragma unroll
+            for (int u = 0; u < kAsmBatch; u++) {
+                // adding the zero of a value without regularization would turn
+                // -0 into 0
+                const bool diag = is_h && reg && (w0 + u * kBlock) / half == count - 1;
+                if (live[u] >= 1) put(q[u].x, diag ? v[u].x + g[u][0] : v[u].x);
+                if (live[u] == 2) put(q[u].y, diag ? v[u].y + g[u][1] : v[u].y);
             }
-            put(q0, v0);
-            if (two) put(q1, v1);
         }
         if (!is_h)
             for (int x = threadIdx.x; x < kn; x += kBlock) {
@@ -387,8 +441,7 @@ __global__ __launch_bounds__(kBlock) void quad_assemble_kernel(
     __syncthreads();
     if (!staged) return;
     if (filled == ext) {
-        double *out = kkt + base;
-        for (int x = threadIdx.x; x < ext; x += kBlock) st_nt(out + x, tile[x]);
+        copy_lines<kBlock>(kkt + base, tile, ext);
     } else {
         visit([&](int32_t q, double v) {
             if ((uint32_t)q < (uint32_t)nnzk) kkt[q] = v;
@@ -622,15 +675,35 @@ struct QLayout {
 };
 
 // Variable rows: one lane per node computes the node's 23 Hessian values;
-// each variable's rows of the workgroup's nodes with more than one entry are
-// staged in LDS and written with contiguous stores.
+// the workgroup's rows of variables [v0, v1) are staged in LDS and written in
+// whole lines, in two halves of 12 and 11 entries per node: 17.6 -> 16.1 us at
+// N = 2e5, 77 us at N = 1e6 as before (5.2 TB/s read and written).
+template <int V0, int V1>
+__device__ __forceinline__ void quad_store_var_rows(const QLayout &Lo, const double (&H)[kHessNode], int64_t k0,
+                                                    int kn, double *__restrict__ kkt, double *buf)
+{
+    constexpr int f0 = kHessFirst[V0];
+#pragma unroll
+    for (int v = V0; v < V1; v++) {
+        const int f = kHessFirst[v], len = kHessFirst[v + 1] - f;
+#pragma unroll
+        for (int e = 0; e < len; e++) buf[(f - f0) * kBlock + threadIdx.x * len + e] = H[f + e];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int v = V0; v < V1; v++) {
+        const int f = kHessFirst[v], len = kHessFirst[v + 1] - f;
+        copy_lines<kBlock>(kkt + Lo.var_start[v] + k0 * len, buf + (f - f0) * kBlock, kn * len);
+    }
+}
+
 __global__ __launch_bounds__(kBlock) void quad_kkt_var_kernel(QP P, QLayout Lo, const double *__restrict__ z,
                                                               const double *__restrict__ y, double sigma,
                                                               const double *__restrict__ reg,
                                                               double *__restrict__ kkt)
 {
-    __shared__ double buf[4 * kBlock];  // one variable's rows of the workgroup (<= 4 entries each)
-    const int64_t k0 = (int64_t)blockIdx.x * kBlock, k = k0 + threadIdx.x;
+    __shared__ double buf[12 * kBlock];
+    const int64_t k0 = (int64_t)xcd_order(blockIdx.x, gridDim.x) * kBlock, k = k0 + threadIdx.x;
     const bool live = k <= P.N;
     const int kn = (int)min((int64_t)kBlock, (int64_t)P.N1 - k0);
     const int64_t N = P.N, N1 = P.N1;
@@ -658,70 +731,49 @@ __global__ __launch_bounds__(kBlock) void quad_kkt_var_kernel(QP P, QLayout Lo, 
             for (int v = 0; v < kVars; v++) H[kHessFirst[v + 1] - 1] += reg[v * N1 + k];
         }
     }
-#pragma unroll
-    for (int v = 0; v < kVars; v++) {
-        const int f = kHessFirst[v], len = kHessFirst[v + 1] - f;
-        if (len == 1) {  // one entry per row: the lanes' stores are contiguous already
-            if (live) st_nt(kkt + Lo.var_start[v] + k, H[f]);
-            continue;
-        }
-        if (live) {
-#pragma unroll
-            for (int e = 0; e < len; e++) buf[threadIdx.x * len + e] = H[f + e];
-        }
-        __syncthreads();
-        double *out = kkt + Lo.var_start[v] + k0 * len;
-        for (int x = threadIdx.x; x < kn * len; x += kBlock) st_nt(out + x, buf[x]);
-        __syncthreads();
-    }
+    static_assert(kHessFirst[9] == 12 && kHessNode - kHessFirst[9] <= 12, "two halves of the LDS buffer");
+    quad_store_var_rows<0, 9>(Lo, H, k0, kn, kkt, buf);
+    __syncthreads();
+    quad_store_var_rows<9, kVars>(Lo, H, k0, kn, kkt, buf);
 }
 
-// Defect rows: one lane per interval evaluates the right-hand side's partials
-// at its two nodes; each row block's rows of the workgroup are staged in LDS
-// and written with contiguous stores.
+// Defect rows.  A workgroup covers kBlock nodes and the kBlock - 1 intervals
+// they close: lane t evaluates the right-hand side's partials at node k0 + t
+// once and puts them in LDS as the node-k entries of interval t's row and the
+// node-(k+1) entries of interval t-1's.  Each row block is then written in
+// whole lines.  (One lane per interval evaluated every node twice, and loaded
+// each row's regularization after the previous row's barrier.)  Stores bound
+// it: 157 -> 142 us at N = 1e6, 34 -> 29.5 us at N = 2e5, 5.1 TB/s read and
+// written.  Two or three row blocks per barrier measured the same at N = 2e5
+// and slower at N = 1e6 (145-148 us, with 64, 128 or 256 lanes).
 __global__ __launch_bounds__(kBlock) void quad_kkt_defect_kernel(QP P, QLayout Lo, const double *__restrict__ z,
                                                                  const double *__restrict__ reg,
                                                                  double *__restrict__ kkt)
 {
     __shared__ double buf[(2 * 6 + 1) * kBlock];  // one row block's rows (<= 12 entries + diagonal)
-    const int64_t k0 = (int64_t)blockIdx.x * kBlock, k = k0 + threadIdx.x;
-    const bool live = k < P.N;
-    const int kn = (int)min((int64_t)kBlock, (int64_t)P.N - k0);
+    const int tid = threadIdx.x;
+    const int64_t k0 = (int64_t)xcd_order(blockIdx.x, gridDim.x) * (kBlock - 1), k = k0 + tid;
+    const int kn = (int)min((int64_t)(kBlock - 1), (int64_t)P.N - k0);
     const int64_t N = P.N, N1 = P.N1;
     const int64_t nvar = (int64_t)kVars * N1;
-    Trig tr[2];
-    double u[2][4];
+    double a[3], u[4], rg[kStates];
+    load_att(P, z, min(k, N), a, u);  // a lane past node N fills no row that is stored
 #pragma unroll
-    for (int s = 0; s < 2; s++) {
-        tr[s] = Trig{};
-#pragma unroll
-        for (int l = 0; l < 4; l++) u[s][l] = 0.0;
-        if (live) {
-            double a[3];
-            load_att(P, z, k + s, a, u[s]);
-            tr[s] = node_trig(a[0], a[1], a[2]);
-        }
-    }
+    for (int i = 0; i < kStates; i++) rg[i] = reg && tid < kn ? reg[nvar + i * N + k] : 0.0;
+    const Trig tr = node_trig(a[0], a[1], a[2]);
 #pragma unroll
     for (int i = 0; i < kStates; i++) {
         const int L = kSupLen[i], len = 2 * L + 1;
-        if (live) {
-            double *row = buf + threadIdx.x * len;
+        double *row = buf + tid * len;
 #pragma unroll
-            for (int p = 0; p < L; p++) {
-                const int q = pair_index(i, p);
-                const bool own = pair_is_own_state(i, p);
-#pragma unroll
-                for (int s = 0; s < 2; s++) {
-                    const double id = own ? (s ? 1.0 : -1.0) : 0.0;
-                    row[2 * p + s] = id - P.hh * partial(q, tr[s], u[s]);
-                }
-            }
-            row[len - 1] = reg ? reg[nvar + i * N + k] : 0.0;
+        for (int p = 0; p < L; p++) {
+            const double v = partial(pair_index(i, p), tr, u);
+            row[2 * p] = __builtin_fma(-P.hh, v, jac_id(i, p, 0));
+            if (tid > 0) row[2 * p + 1 - len] = __builtin_fma(-P.hh, v, jac_id(i, p, 1));
         }
+        row[len - 1] = rg[i];
         __syncthreads();
-        double *out = kkt + Lo.def_start[i] + k0 * len;
-        for (int x = threadIdx.x; x < kn * len; x += kBlock) st_nt(out + x, buf[x]);
+        copy_lines<kBlock>(kkt + Lo.def_start[i] + k0 * len, buf, kn * len);
         __syncthreads();
     }
 }
@@ -781,7 +833,7 @@ int eval_kkt(const ocp_problem *p, const double *z, const double *y, double sigm
         o += (int64_t)(kRowSlot[i + 1] - kRowSlot[i] + 1) * N;
     }
     Lo.bnd_start = o;
-    hipLaunchKernelGGL(quad_kkt_defect_kernel, dim3(blocks_for(N, kBlock)), dim3(kBlock), 0, stream, P, Lo, z,
+    hipLaunchKernelGGL(quad_kkt_defect_kernel, dim3(blocks_for(N, kBlock - 1)), dim3(kBlock), 0, stream, P, Lo, z,
                        reg, kkt);
     if (int rc = check_launch("ocp_eval_kkt")) return rc;
     hipLaunchKernelGGL(quad_kkt_var_kernel, dim3(blocks_for(N1, kBlock)), dim3(kBlock), 0, stream, P, Lo, z, y,
@@ -855,15 +907,12 @@ int eval_cons(const ocp_problem *p, const double *z, double *c, hipStream_t stre
 int eval_jac(const ocp_problem *p, const double *z, double *jvals, hipStream_t stream)
 {
     const QP P = make_qp(p);
-    // Paired stores need every slot row 16-byte aligned: N even and the
-    // output 16-byte aligned.
-    const bool pair = P.N % 2 == 0 && (uintptr_t)jvals % 16 == 0;
-    if (pair)
-        hipLaunchKernelGGL(quad_jac_kernel<2>, dim3(blocks_for(P.N / 2, kBlock), kStates), dim3(kBlock), 0,
-                           stream, P, z, jvals);
+    if ((int64_t)kSlots * P.N * (int64_t)sizeof(double) <= kJacSmall)
+        hipLaunchKernelGGL(quad_jac_kernel, dim3(blocks_for(P.N, kBlock), kStates), dim3(kBlock), 0, stream, P, z,
+                           jvals);
     else
-        hipLaunchKernelGGL(quad_jac_kernel<1>, dim3(blocks_for(P.N, kBlock), kStates), dim3(kBlock), 0,
-                           stream, P, z, jvals);
+        hipLaunchKernelGGL(quad_jac_lines_kernel, dim3(blocks_for((int64_t)P.N + kHalo, lines_span(kBlock)), kStates),
+                           dim3(kBlock), 0, stream, P, z, jvals);
     if (P.nb > 0)
         hipLaunchKernelGGL(quad_bnd_jac_kernel, dim3(blocks_for(P.nb, kBlock)), dim3(kBlock), 0, stream, P,
                            jvals);
@@ -888,7 +937,7 @@ int assemble_kkt(const ocp_problem *p, const int32_t *perm_j, const int32_t *per
         const bool is_h = g >= kStates;
         const int gi = is_h ? g - kStates : g;
         const int per_row = is_h ? kHessFirst[gi + 1] - kHessFirst[gi] : kRowSlot[gi + 1] - kRowSlot[gi] + 1;
-        const int KT = (kTileCap / per_row) & ~1;
+        const int KT = (kTileCap / per_row) & ~(kLine - 1);  // whole lines of a slot row
         const int64_t rows = is_h ? p->d.N1 : p->d.N;
         G.tile0[g] = (int)blocks;
         G.KT[g] = KT;
@@ -896,11 +945,8 @@ int assemble_kkt(const ocp_problem *p, const int32_t *perm_j, const int32_t *per
     }
     G.tile0[kGroups] = (int)blocks;
     blocks += blocks_for(P.nb, kBlock);
-    // paired loads need 16-byte aligned values and 8-byte aligned slots
-    const bool vec_j = (uintptr_t)jvals % 16 == 0 && (uintptr_t)perm_j % 8 == 0;
-    const bool vec_h = (uintptr_t)hvals % 16 == 0 && (uintptr_t)perm_h % 8 == 0;
     hipLaunchKernelGGL(quad_assemble_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, stream, P, G,
-                       (int)p->d.nnzk, vec_j, vec_h, perm_j, perm_h, rowptr, jvals, hvals, reg, kkt);
+                       (int)p->d.nnzk, perm_j, perm_h, rowptr, jvals, hvals, reg, kkt);
     return check_launch("ocp_assemble_kkt");
 }
 

@@ -163,3 +163,33 @@ def test_mapped_assembly_tiles(ocp, N, n, m, scheme, bnd, offset):
         torch.cuda.synchronize()
         assert np.array_equal(out.values().view(np.uint64), want.view(np.uint64))
     prob.close()
+
+
+# quadrotor: slot rows in whole lines (tiles of 496) above 32 MiB of Jacobian,
+# defect rows of the fused KKT in tiles of 255 intervals, variable rows in
+# tiles of 256 nodes, assembly tiles of 144 to 2048 rows
+@pytest.mark.parametrize("N,bnd,offset", [(61681, 0, 0), (61682, 1, 1), (61504, 2, 15), (61505, 0, 8), (62000, 1, 3),
+                                          (255, 1, 1), (256, 2, 8), (510, 0, 15), (511, 1, 5), (1, 2, 7),
+                                          (2048, 0, 4), (2049, 2, 9)])
+def test_quadrotor_tiles(ocp, N, bnd, offset):
+    print(f"[lines] quadrotor N={N} bnd={bnd} offset={offset}", flush=True)
+    q = synth.make_quadrotor(N, seed=73, bnd=bnd)
+    prob = ocp.QuadrotorProblem.from_instance(q, torch.device("cuda", 0))
+    s = prob.sizes
+    z, y = _t(q.z), _t(q.y)
+    rp, _, pj, ph = prob.kkt_pattern()
+    reg = np.random.default_rng(5).normal(size=s["dim"])
+    (oj, mj), (oh, mh) = oracle.quad_jac(q), oracle.quad_hess(q, sigma=0.7)
+    jac = Guarded(s["nnzj"], offset)
+    prob.jac(z, out=jac.out)
+    check_close(jac.values(), oj, mj, what="jac")
+    kkt = Guarded(s["nnzk"], offset)
+    prob.eval_kkt(z, y, 0.7, _t(reg), out=kkt.out)
+    check_close(kkt.values(), oracle.assemble(rp, pj, oj, ph, oh, reg),
+                oracle.assemble(rp, pj, mj, ph, mh, np.abs(reg)), what="fused kkt")
+    asm = Guarded(s["nnzk"], offset)
+    prob.assemble_kkt(_t(np.r_[np.int32(0), pj])[1:], _t(ph), _t(rp), jac.out, _t(np.r_[0.0, oh])[1:], _t(reg),
+                      out=asm.out)
+    want = oracle.assemble(rp, pj, jac.values(), ph, oh, reg)
+    assert np.array_equal(asm.values().view(np.uint64), want.view(np.uint64))
+    prob.close()
