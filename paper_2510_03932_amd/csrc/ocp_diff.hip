@@ -39,6 +39,7 @@
 #include "ocp_internal.h"
 #include "ocp_problem.h"
 #include "ocp_quad.h"
+#include "ocp_step_device.h"
 
 using namespace ocp;
 using namespace ocp::dev;
@@ -339,18 +340,8 @@ __global__ __launch_bounds__(kBlock) void jvp_kernel(KP P, const double *__restr
         for (int i = 0; i < NB; i++)
             if (i < n) st_nt(out + i * N + k, Ms[i][tid + 1] - Pk[i]);
     }
-}
-
-// Boundary rows of J v: row n N + b holds the state X_{b mod n} at node 0
-// (b < n) or at node N.
-__global__ __launch_bounds__(kBlock) void bnd_jvp_kernel(KP P, const double *__restrict__ v,
-                                                         double *__restrict__ out)
-{
-    const int b = blockIdx.x * kBlock + threadIdx.x;
-    if (b >= P.nb) return;
-    const int i = b % P.n;
-    const int64_t node = b < P.n ? 0 : P.N;
-    out[(int64_t)P.n * P.N + b] = v[(int64_t)i * P.N1 + node];
+    // boundary rows, in the first workgroup: the direction at the fixed state
+    if (blockIdx.x == 0 && tid < P.nb) out[n * N + tid] = bnd_value(P, v, tid);
 }
 
 // Coefficient gradient, pass 1.  With yt_i(k) the multiplier weight of node
@@ -899,10 +890,6 @@ int ocp_eval_jvp(const ocp_problem *p, const double *z, const double *v, double 
     if (p->model == quad::kModel) return quad::eval_jvp(p, z, v, out, stream);
     OCP_DISPATCH_NB(p->d.n, jvp_kernel, dim3(blocks_for(p->d.N, kBlock - 1)), stream, p->kp, z, v,
                     out);
-    if (int rc = check_launch("ocp_eval_jvp")) return rc;
-    if (p->d.nb > 0)
-        hipLaunchKernelGGL(bnd_jvp_kernel, dim3(blocks_for(p->d.nb, kBlock)), dim3(kBlock), 0, stream,
-                           p->kp, v, out);
     return check_launch("ocp_eval_jvp");
 }
 

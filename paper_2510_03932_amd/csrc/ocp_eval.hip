@@ -29,11 +29,22 @@ namespace {
 // (jac_lines_kernel).  Many short workgroups keep the write stream at the
 // device's rate for slot rows, 5.5-5.8 TB/s; see launch_jac for the choice.
 // ---------------------------------------------------------------------------
+// Boundary row b's single Jacobian entry (1.0), after the defect entries.  The
+// boundary rows (at most 2 OCP_MAX_DIM = 64) ride in the first workgroup of
+// the kernel that writes the defect rows: a launch of their own took 4-5 us.
+// They come last in it: after a store the compiler no longer reads the
+// coefficients through the scalar cache (stored first, the fused KKT's
+// variable rows took 65 us instead of 53 at N = 333,333, n = 12, m = 5).
+__device__ __forceinline__ void bnd_jac(const KP &P, double *__restrict__ jac, int64_t b)
+{
+    if (b < P.nb) jac[(int64_t)P.n * P.N * P.T + b] = 1.0;
+}
+
 __global__ __launch_bounds__(kBlock) void jac_kernel(KP P, const double *__restrict__ z, double *__restrict__ jac)
 {
     const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (k >= P.N) return;
-    jac_column(P, z, jac, k, blockIdx.y);
+    if (k < P.N) jac_column(P, z, jac, k, blockIdx.y);
+    bnd_jac(P, jac, blockIdx.y == 0 ? k : P.nb);
 }
 
 __global__ __launch_bounds__(kBlock) void jac_lines_kernel(KP P, const double *__restrict__ z,
@@ -41,6 +52,7 @@ __global__ __launch_bounds__(kBlock) void jac_lines_kernel(KP P, const double *_
 {
     __shared__ double lds[6 * kBlock];
     jac_column_lines<kBlock>(P, z, jac, (int64_t)blockIdx.x * lines_span(kBlock), blockIdx.y, lds);
+    bnd_jac(P, jac, blockIdx.x == 0 && blockIdx.y == 0 ? threadIdx.x : P.nb);
 }
 
 // ---------------------------------------------------------------------------
@@ -91,6 +103,7 @@ __global__ __launch_bounds__(kBlock) void cons_kernel(KP P, const double *__rest
         for (int i = 0; i < NB; i++)
             if (i < n) st_nt(c + i * N + k, Ms[i][tid + 1] - Pk[i]);
     }
+    if (blockIdx.x == 0 && tid < P.nb) c[n * N + tid] = bnd_value(P, z, tid);  // boundary rows
 }
 
 // ---------------------------------------------------------------------------
@@ -102,26 +115,8 @@ __global__ __launch_bounds__(kBlock) void cons_euler_kernel(KP P, const double *
                                                             double *__restrict__ c)
 {
     const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (k >= P.N) return;
-    cons_euler_interval<NB, MB>(P, z, c, k);
-}
-
-// Boundary rows after the n N defect rows: row b holds X_{b mod n} at node 0
-// (b < n) or node N; its single Jacobian entry (1.0) follows the defect
-// entries.
-__global__ __launch_bounds__(kBlock) void bnd_cons_kernel(KP P, const double *__restrict__ z,
-                                                          double *__restrict__ c)
-{
-    const int b = blockIdx.x * kBlock + threadIdx.x;
-    if (b >= P.nb) return;
-    c[(int64_t)P.n * P.N + b] = bnd_value(P, z, b);
-}
-
-__global__ __launch_bounds__(kBlock) void bnd_jac_kernel(KP P, double *__restrict__ jac)
-{
-    const int b = blockIdx.x * kBlock + threadIdx.x;
-    if (b >= P.nb) return;
-    jac[(int64_t)P.n * P.N * P.T + b] = 1.0;
+    if (k < P.N) cons_euler_interval<NB, MB>(P, z, c, k);
+    if (k < P.nb) c[(int64_t)P.n * P.N + k] = bnd_value(P, z, (int)k);  // boundary rows
 }
 
 template <int NB>
@@ -360,9 +355,6 @@ hipError_t launch_jac(const KP &P, const double *z, double *jac, hipStream_t str
     else
         hipLaunchKernelGGL(jac_lines_kernel, dim3(blocks_for((int64_t)P.N + kHalo, lines_span(kBlock)), cols),
                            dim3(kBlock), 0, stream, P, z, jac);
-    if (P.nb > 0)
-        hipLaunchKernelGGL(bnd_jac_kernel, dim3((P.nb + kBlock - 1) / kBlock), dim3(kBlock), 0, stream,
-                           P, jac);
     return hipGetLastError();
 }
 
@@ -440,10 +432,6 @@ hipError_t launch_cons(const KP &P, const double *z, double *c, hipStream_t stre
         else if (n <= 16) launch_cons_euler<16>(P, g, z, c, stream);
         else launch_cons_euler<32>(P, g, z, c, stream);
     }
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (P.nb > 0)
-        hipLaunchKernelGGL(bnd_cons_kernel, dim3(blocks_for(P.nb, kBlock)), dim3(kBlock), 0, stream, P, z, c);
     return hipGetLastError();
 }
 

@@ -54,15 +54,8 @@ __global__ __launch_bounds__(kBlock) void kkt_var_kernel(KP P, KKTLayout Lo, con
 {
     __shared__ double buf[3 * kBlock];  // one state block's rows of this workgroup (<= 3 entries each)
     kkt_var_tile<NB, kBlock>(P, Lo, z, y, sigma, reg, kkt, (int64_t)xcd_order(blockIdx.x, gridDim.x) * kBlock, buf);
-}
-
-// Boundary rows: their state entry (1) and their diagonal.
-__global__ __launch_bounds__(kBlock) void kkt_bnd_kernel(KP P, KKTLayout Lo, const double *__restrict__ reg,
-                                                         double *__restrict__ kkt)
-{
-    const int b = blockIdx.x * kBlock + threadIdx.x;
-    if (b >= P.nb) return;
-    kkt_bnd_row(P, Lo, reg, kkt, b);
+    // the boundary rows ride in the first workgroup, after its own
+    if (blockIdx.x == 0 && (int)threadIdx.x < P.nb) kkt_bnd_row(P, Lo, reg, kkt, threadIdx.x);
 }
 
 }  // namespace
@@ -82,18 +75,13 @@ hipError_t launch_eval_kkt(const KP &P, const double *z, const double *y, double
     const size_t lds = kkt_defect_lds(P.n, P.m, P.T, KT) * sizeof(double);
     hipLaunchKernelGGL(kkt_defect_kernel, dim3(blocks_for(P.N, KT)), dim3(kBlock), lds, stream, P, Lo, LG, z, reg,
                        kkt);
-    hipError_t e = hipGetLastError();
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const dim3 g(blocks_for(P.N1, kBlock));
     if (P.n <= 4) hipLaunchKernelGGL(kkt_var_kernel<4>, g, dim3(kBlock), 0, stream, P, Lo, z, y, sigma, reg, kkt);
     else if (P.n <= 8) hipLaunchKernelGGL(kkt_var_kernel<8>, g, dim3(kBlock), 0, stream, P, Lo, z, y, sigma, reg, kkt);
     else if (P.n <= 16) hipLaunchKernelGGL(kkt_var_kernel<16>, g, dim3(kBlock), 0, stream, P, Lo, z, y, sigma, reg, kkt);
     else hipLaunchKernelGGL(kkt_var_kernel<32>, g, dim3(kBlock), 0, stream, P, Lo, z, y, sigma, reg, kkt);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (P.nb > 0)
-        hipLaunchKernelGGL(kkt_bnd_kernel, dim3(blocks_for(P.nb, kBlock)), dim3(kBlock), 0, stream, P, Lo, reg,
-                           kkt);
     return hipGetLastError();
 }
 

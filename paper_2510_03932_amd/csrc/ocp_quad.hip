@@ -120,12 +120,25 @@ __device__ __forceinline__ void jac_row_lines(const QP &P, const double *__restr
         }
 }
 
+// Boundary row b's single Jacobian entry (1.0), after the defect entries.  The
+// boundary rows (at most 18) ride in the first workgroup of the kernel that
+// writes the defect rows.
+__device__ __forceinline__ void bnd_jac(const QP &P, double *__restrict__ jac, int64_t b)
+{
+    if (b < P.nb) jac[(int64_t)kSlots * P.N + b] = 1.0;
+}
+
+// Boundary row b of a z-shaped array: the state itself (X_i0, then X_iN).
+__device__ __forceinline__ double bnd_state(const QP &P, const double *__restrict__ z, int b)
+{
+    return z[(int64_t)(b % kStates) * P.N1 + (b < kStates ? 0 : P.N)];
+}
+
 __global__ __launch_bounds__(kBlock) void quad_jac_kernel(QP P, const double *__restrict__ z,
                                                           double *__restrict__ jac)
 {
     const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (k >= P.N) return;
-    switch (blockIdx.y) {
+    if (k < P.N) switch (blockIdx.y) {
     case 0: jac_row<0>(P, z, jac, k); break;
     case 1: jac_row<1>(P, z, jac, k); break;
     case 2: jac_row<2>(P, z, jac, k); break;
@@ -136,6 +149,7 @@ __global__ __launch_bounds__(kBlock) void quad_jac_kernel(QP P, const double *__
     case 7: jac_row<7>(P, z, jac, k); break;
     default: jac_row<8>(P, z, jac, k); break;
     }
+    bnd_jac(P, jac, blockIdx.y == 0 ? k : P.nb);
 }
 
 __global__ __launch_bounds__(kBlock) void quad_jac_lines_kernel(QP P, const double *__restrict__ z,
@@ -154,13 +168,7 @@ __global__ __launch_bounds__(kBlock) void quad_jac_lines_kernel(QP P, const doub
     case 7: jac_row_lines<7>(P, z, jac, k0, lds); break;
     default: jac_row_lines<8>(P, z, jac, k0, lds); break;
     }
-}
-
-// Boundary rows: one Jacobian entry 1.0 each, after the defect entries.
-__global__ __launch_bounds__(kBlock) void quad_bnd_jac_kernel(QP P, double *__restrict__ jac)
-{
-    const int b = blockIdx.x * kBlock + threadIdx.x;
-    if (b < P.nb) jac[(int64_t)kSlots * P.N + b] = 1.0;
+    bnd_jac(P, jac, blockIdx.x == 0 && blockIdx.y == 0 ? threadIdx.x : P.nb);
 }
 
 // ---------------------------------------------------------------------------
@@ -231,16 +239,7 @@ __global__ __launch_bounds__(kBlock) void quad_cons_kernel(QP P, const double *_
         for (int i = 0; i < kStates; i++)
             st_nt(c + i * N + k, (Xs[i][tid + 1] - x[i]) - P.hh * (F[i] + Fs[i][tid + 1]));
     }
-}
-
-// Boundary rows: the state itself (X_i0, then X_iN).
-__global__ __launch_bounds__(kBlock) void quad_bnd_cons_kernel(QP P, const double *__restrict__ z,
-                                                               double *__restrict__ c)
-{
-    const int b = blockIdx.x * kBlock + threadIdx.x;
-    if (b >= P.nb) return;
-    const int64_t node = b < kStates ? 0 : P.N;
-    c[(int64_t)kStates * P.N + b] = z[(int64_t)(b % kStates) * P.N1 + node];
+    if (blockIdx.x == 0 && tid < P.nb) c[kStates * N + tid] = bnd_state(P, z, tid);  // boundary rows
 }
 
 // ---------------------------------------------------------------------------
@@ -646,16 +645,8 @@ __global__ __launch_bounds__(kBlock) void quad_jvp_kernel(QP P, const double *__
 #pragma unroll
         for (int i = 0; i < kStates; i++) st_nt(out + i * N + k, Ms[i][tid + 1] - Pk[i]);
     }
-}
-
-// Boundary rows of J v: the direction at the fixed state.
-__global__ __launch_bounds__(kBlock) void quad_bnd_jvp_kernel(QP P, const double *__restrict__ v,
-                                                              double *__restrict__ out)
-{
-    const int b = blockIdx.x * kBlock + threadIdx.x;
-    if (b >= P.nb) return;
-    const int64_t node = b < kStates ? 0 : P.N;
-    out[(int64_t)kStates * P.N + b] = v[(int64_t)(b % kStates) * P.N1 + node];
+    // boundary rows: the direction at the fixed state
+    if (blockIdx.x == 0 && tid < P.nb) out[kStates * N + tid] = bnd_state(P, v, tid);
 }
 
 // ---------------------------------------------------------------------------
@@ -735,6 +726,11 @@ __global__ __launch_bounds__(kBlock) void quad_kkt_var_kernel(QP P, QLayout Lo, 
     quad_store_var_rows<0, 9>(Lo, H, k0, kn, kkt, buf);
     __syncthreads();
     quad_store_var_rows<9, kVars>(Lo, H, k0, kn, kkt, buf);
+    if (blockIdx.x == 0 && (int)threadIdx.x < P.nb) {  // a boundary row: its state entry (1) and its diagonal
+        const int b = threadIdx.x;
+        kkt[Lo.bnd_start + 2 * b] = 1.0;
+        kkt[Lo.bnd_start + 2 * b + 1] = reg ? reg[kVars * N1 + kStates * N + b] : 0.0;
+    }
 }
 
 // Defect rows.  A workgroup covers kBlock nodes and the kBlock - 1 intervals
@@ -776,17 +772,6 @@ __global__ __launch_bounds__(kBlock) void quad_kkt_defect_kernel(QP P, QLayout L
         copy_lines<kBlock>(kkt + Lo.def_start[i] + k0 * len, buf, kn * len);
         __syncthreads();
     }
-}
-
-// Boundary rows: their state entry (1) and their diagonal.
-__global__ __launch_bounds__(kBlock) void quad_kkt_bnd_kernel(QP P, QLayout Lo, const double *__restrict__ reg,
-                                                              double *__restrict__ kkt)
-{
-    const int b = blockIdx.x * kBlock + threadIdx.x;
-    if (b >= P.nb) return;
-    const int64_t row = (int64_t)kVars * P.N1 + (int64_t)kStates * P.N + b;
-    kkt[Lo.bnd_start + 2 * b] = 1.0;
-    kkt[Lo.bnd_start + 2 * b + 1] = reg ? reg[row] : 0.0;
 }
 
 QP make_qp(const ocp_problem *p)
@@ -838,10 +823,6 @@ int eval_kkt(const ocp_problem *p, const double *z, const double *y, double sigm
     if (int rc = check_launch("ocp_eval_kkt")) return rc;
     hipLaunchKernelGGL(quad_kkt_var_kernel, dim3(blocks_for(N1, kBlock)), dim3(kBlock), 0, stream, P, Lo, z, y,
                        sigma, reg, kkt);
-    if (int rc = check_launch("ocp_eval_kkt")) return rc;
-    if (P.nb > 0)
-        hipLaunchKernelGGL(quad_kkt_bnd_kernel, dim3(blocks_for(P.nb, kBlock)), dim3(kBlock), 0, stream, P, Lo,
-                           reg, kkt);
     return check_launch("ocp_eval_kkt");
 }
 
@@ -879,10 +860,6 @@ int eval_jvp(const ocp_problem *p, const double *z, const double *v, double *out
     const QP P = make_qp(p);
     hipLaunchKernelGGL(quad_jvp_kernel, dim3(blocks_for(p->d.N, kBlock - 1)), dim3(kBlock), 0, stream, P, z,
                        v, out);
-    if (int rc = check_launch("ocp_eval_jvp")) return rc;
-    if (P.nb > 0)
-        hipLaunchKernelGGL(quad_bnd_jvp_kernel, dim3(blocks_for(P.nb, kBlock)), dim3(kBlock), 0, stream, P, v,
-                           out);
     return check_launch("ocp_eval_jvp");
 }
 
@@ -898,9 +875,6 @@ int eval_cons(const ocp_problem *p, const double *z, double *c, hipStream_t stre
     const QP P = make_qp(p);
     hipLaunchKernelGGL(quad_cons_kernel, dim3(blocks_for(p->d.N, kBlock - 1)), dim3(kBlock), 0, stream, P,
                        z, c);
-    if (P.nb > 0)
-        hipLaunchKernelGGL(quad_bnd_cons_kernel, dim3(blocks_for(P.nb, kBlock)), dim3(kBlock), 0, stream, P,
-                           z, c);
     return check_launch("ocp_eval_cons");
 }
 
@@ -913,9 +887,6 @@ int eval_jac(const ocp_problem *p, const double *z, double *jvals, hipStream_t s
     else
         hipLaunchKernelGGL(quad_jac_lines_kernel, dim3(blocks_for((int64_t)P.N + kHalo, lines_span(kBlock)), kStates),
                            dim3(kBlock), 0, stream, P, z, jvals);
-    if (P.nb > 0)
-        hipLaunchKernelGGL(quad_bnd_jac_kernel, dim3(blocks_for(P.nb, kBlock)), dim3(kBlock), 0, stream, P,
-                           jvals);
     return check_launch("ocp_eval_jac");
 }
 
