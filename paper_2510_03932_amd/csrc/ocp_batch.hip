@@ -242,9 +242,7 @@ __global__ __launch_bounds__(kBlock) void batch_obj_final_kernel(const InstDesc 
                                                                  double *__restrict__ obj)
 {
     const InstDesc id = inst[blockIdx.x];
-    double acc = 0.0;
-    for (int i = threadIdx.x; i < id.nparts; i += kBlock) acc += parts[id.part0 + i];
-    const double t = block_sum<kBlock>(acc);
+    const double t = sum_partials(parts + id.part0, id.nparts);
     if (threadIdx.x == 0) obj[blockIdx.x] = t;
 }
 
@@ -564,7 +562,7 @@ static int batch_launch(const ocp_batch *b, const Plan &plan, int32_t what, int3
         hipError_t e = hipSuccess;
         if (what & OCP_EVAL_OBJ) e = launch_obj(P, zb, b->parts + b->part_off[i], io.obj + i, s);
         if (e == hipSuccess && (what & OCP_EVAL_GRAD)) e = launch_grad(P, zb, io.grad + b->z_off[i], s);
-        if (e == hipSuccess && (what & OCP_EVAL_CONS)) e = launch_cons(P, zb, io.cons + b->c_off[i], s);
+        if (e == hipSuccess && (what & OCP_EVAL_CONS)) e = launch_cons(P, zb, io.cons + b->c_off[i], nullptr, s);
         if (e == hipSuccess && (what & OCP_EVAL_JAC)) e = launch_jac(P, zb, io.jac + b->jac_off[i], s);
         if (e == hipSuccess && (what & OCP_EVAL_HESS))
             e = launch_hess(P, zb, io.y + b->c_off[i], io.sigma, io.hess + b->hess_off[i], s);

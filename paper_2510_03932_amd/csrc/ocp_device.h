@@ -116,6 +116,9 @@ __device__ __forceinline__ uint32_t xcd_order(uint32_t b, uint32_t nb)
 // the same or slower here, ordinary ones 10-30 % slower.
 // ---------------------------------------------------------------------------
 constexpr int kLine = 16;  // doubles per 128-byte line
+// Intervals per workgroup of the kernels whose lanes exchange values with the
+// next node's (kBlock nodes close kBlock - 1): a multiple of a line.
+constexpr int kSpan = kBlock - kLine;
 template <int BS>
 __device__ __forceinline__ void copy_lines(double *__restrict__ out, const double *src, int cnt)
 {
@@ -149,6 +152,25 @@ __device__ __forceinline__ double block_sum(double v)
         for (int i = 0; i < BS / 64; i++) t += ws[i];
     }
     return t;  // valid in thread 0
+}
+
+// A reduction's second pass, one workgroup of kBlock lanes: lane t adds
+// partials t, t + kBlock, ... in order, kSumBatch of them loaded at a time
+// (one at a time, each addition waited for its own load), then the fixed tree.
+// The result is valid in thread 0.
+constexpr int kSumBatch = 8;
+__device__ __forceinline__ double sum_partials(const double *__restrict__ partials, int count)
+{
+    double acc = 0.0;
+    for (int i0 = threadIdx.x; i0 < count; i0 += kSumBatch * kBlock) {
+        double v[kSumBatch];
+#pragma unroll
+        for (int u = 0; u < kSumBatch; u++) v[u] = i0 + u * kBlock < count ? partials[i0 + u * kBlock] : 0.0;
+#pragma unroll
+        for (int u = 0; u < kSumBatch; u++)
+            if (i0 + u * kBlock < count) acc += v[u];
+    }
+    return block_sum<kBlock>(acc);
 }
 
 // ---------------------------------------------------------------------------
@@ -360,25 +382,32 @@ __device__ __forceinline__ void hess_node(const KP &P, const double *__restrict_
 // ---------------------------------------------------------------------------
 // Dynamics at node k <= N: the node's states x[i] = X_ik and F_i(k) for every
 // i < n (NB >= n, entries beyond n are zero).  F_i sums j ascending, then l
-// ascending, then the bilinear term.  The states and the first MB controls
-// are loaded before any arithmetic (further controls, when m > MB, after);
-// a caller that knows m <= MB < NB saves the registers of NB - MB controls.
+// ascending, then the bilinear term.  dyn_load loads the states of node k and
+// the first MB controls of node ku, before any arithmetic; dyn_eval computes F
+// (further controls, when m > MB, loaded there); a caller that knows
+// m <= MB < NB saves the registers of NB - MB controls.
 // ---------------------------------------------------------------------------
-template <int NB, int MB = NB>
-__device__ __forceinline__ void dyn_node(const KP &P, const double *__restrict__ z, int64_t k,
-                                         double (&x)[NB], double (&F)[NB])
+template <int NB, int MB>
+__device__ __forceinline__ void dyn_load(const KP &P, const double *__restrict__ z, int64_t k, int64_t ku,
+                                         double (&x)[NB], double (&u)[MB])
 {
     static_assert(MB <= NB, "the control bound is at most the state bound");
-    const int n = P.n, m = P.m;
-    const int64_t N1 = P.N1;
-    const double *U = z + (int64_t)n * N1;
-    double u[MB];
+    const double *U = z + (int64_t)P.n * P.N1;
 #pragma unroll
     for (int i = 0; i < NB; i++) {
-        x[i] = (i < n) ? z[i * N1 + k] : 0.0;
-        if (i < MB) u[i] = (i < m) ? U[(int64_t)i * P.NU + k] : 0.0;
-        F[i] = 0.0;
+        x[i] = (i < P.n) ? z[i * (int64_t)P.N1 + k] : 0.0;
+        if (i < MB) u[i] = (i < P.m) ? U[(int64_t)i * P.NU + ku] : 0.0;
     }
+}
+
+template <int NB, int MB>
+__device__ __forceinline__ void dyn_eval(const KP &P, const double *__restrict__ z, int64_t ku,
+                                         const double (&x)[NB], const double (&u)[MB], double (&F)[NB])
+{
+    const int n = P.n, m = P.m;
+    const double *U = z + (int64_t)n * P.N1;
+#pragma unroll
+    for (int i = 0; i < NB; i++) F[i] = 0.0;
 #pragma unroll
     for (int j = 0; j < NB; j++) {
         if (j < n) {
@@ -397,7 +426,7 @@ __device__ __forceinline__ void dyn_node(const KP &P, const double *__restrict__
         }
     }
     for (int l = MB; l < m; l++) {
-        const double ul = U[(int64_t)l * P.NU + k];
+        const double ul = U[(int64_t)l * P.NU + ku];
         const double *b = P.BT + l * kLd;
 #pragma unroll
         for (int i = 0; i < NB; i++) F[i] = __builtin_fma(b[i], ul, F[i]);
@@ -409,6 +438,15 @@ __device__ __forceinline__ void dyn_node(const KP &P, const double *__restrict__
             F[i] = __builtin_fma(P.gam[i] * x[i], xp, F[i]);  // explicit: same bits in every kernel
         }
     }
+}
+
+template <int NB, int MB = NB>
+__device__ __forceinline__ void dyn_node(const KP &P, const double *__restrict__ z, int64_t k,
+                                         double (&x)[NB], double (&F)[NB])
+{
+    double u[MB];
+    dyn_load<NB, MB>(P, z, k, k, x, u);
+    dyn_eval<NB, MB>(P, z, k, x, u, F);
 }
 
 // Entry n-1 of a register array (n is a run-time value <= NB), by selects so
@@ -489,7 +527,8 @@ hipError_t launch_hess(const KP &P, const double *z, const double *y, double sig
                        hipStream_t stream);
 hipError_t launch_obj(const KP &P, const double *z, double *partials, double *obj, hipStream_t stream);
 hipError_t launch_grad(const KP &P, const double *z, double *g, hipStream_t stream);
-hipError_t launch_cons(const KP &P, const double *z, double *c, hipStream_t stream);
+// `scale`: null, or a device double that every value is multiplied by
+hipError_t launch_cons(const KP &P, const double *z, double *c, const double *scale, hipStream_t stream);
 hipError_t launch_eval_kkt(const KP &P, const double *z, const double *y, double sigma, const double *reg,
                            double *kkt, hipStream_t stream);
 

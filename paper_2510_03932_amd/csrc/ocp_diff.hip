@@ -61,81 +61,91 @@ namespace {
 // defect kernel); workgroups take chunks c = blockIdx.x, + gridDim.x, ...
 // A node's cost term is counted by the chunk that owns it (lane < B-1, or
 // the last node N).
-template <int NB>
+// Every load of a chunk is issued before its arithmetic, the controls once for
+// the dynamics and the cost.  LOOP = false is the grid of one chunk per
+// workgroup (N up to 1e6): with the loop in place the compiler keeps every
+// coefficient live across it (n <= 8: 160 VGPRs and 88 spilled SGPRs against 86
+// and none; n <= 16: 256 VGPRs against 183).  Loads, the sines' latency and
+// the launch bound it: with the loop, the multipliers waited for before the
+// states were requested and the controls loaded again one by one for the cost,
+// 19.6 us at N = 2e5, n = 8, m = 4; so, 15.8 us.
+template <int NB, int MB, bool LOOP>
+__device__ __forceinline__ void lag_chunk(const KP &P, const double *__restrict__ z, const double *__restrict__ y,
+                                          double sigma, int ch, double (&Ms)[NB][kBlock], double &acc)
+{
+    const int tid = threadIdx.x;
+    const int n = P.n, m = P.m;
+    const int64_t N = P.N, NU = P.NU;
+    const double *U = z + (int64_t)n * P.N1;
+    const double *yb = y + (int64_t)n * N;  // boundary-row multipliers
+    const bool euler = P.scheme != 0;
+    const double al = euler ? P.h : P.hh, be = euler ? 0.0 : P.hh;
+    const int64_t k = (int64_t)ch * (kBlock - 1) + tid;
+    // every load of the lane, its interval's multipliers included, from
+    // indices clamped into the rows: a lane past the last node computes values
+    // that it does not use
+    double yv[NB], x[NB], F[NB], u[MB], Pk[NB];
+    const int64_t ky = min(k, N - 1), ku = min(k, NU - 1);
+#pragma unroll
+    for (int i = 0; i < NB; i++) yv[i] = y[(int64_t)(i < n ? i : 0) * N + ky];
+    dyn_load<NB, MB>(P, z, min(k, N), ku, x, u);
+    dyn_eval<NB, MB>(P, z, ku, x, u, F);
+#pragma unroll
+    for (int i = 0; i < NB; i++) {
+        if (i < n) {
+            const double Fi = k < NU ? F[i] : 0.0;  // forward Euler: F(N) enters no row
+            Ms[i][tid] = x[i] - be * Fi;
+            Pk[i] = x[i] + al * Fi;
+        }
+    }
+    if (k <= N && (tid < kBlock - 1 || k == N)) {
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < NB; i++)
+            if (i < n) s += P.q[i] * x[i] * x[i];
+        if (k < NU) {
+#pragma unroll
+            for (int l = 0; l < MB; l++)
+                if (l < m) s += P.r[l] * u[l] * u[l];
+            for (int l = MB; l < m; l++) {
+                const double ul = U[l * NU + k];
+                s += P.r[l] * ul * ul;
+            }
+        }
+        acc += sigma * node_weight(P, (int)k) * s;
+        // boundary rows: the state at node 0 (and at node N)
+        if (P.nb >= n && k == 0) {
+#pragma unroll
+            for (int i = 0; i < NB; i++)
+                if (i < n) acc += yb[i] * x[i];
+        }
+        if (P.nb >= 2 * n && k == N) {
+#pragma unroll
+            for (int i = 0; i < NB; i++)
+                if (i < n) acc += yb[n + i] * x[i];
+        }
+    }
+    __syncthreads();
+    if (tid < kBlock - 1 && k < N) {
+#pragma unroll
+        for (int i = 0; i < NB; i++)
+            if (i < n) acc += yv[i] * (Ms[i][tid + 1] - Pk[i]);
+    }
+    if (LOOP) __syncthreads();
+}
+
+template <int NB, int MB, bool LOOP>
 __global__ __launch_bounds__(kBlock) void lag_partial_kernel(KP P, const double *__restrict__ z,
                                                              const double *__restrict__ y,
                                                              double sigma, int nchunks,
                                                              double *__restrict__ partials)
 {
     __shared__ double Ms[NB][kBlock];
-    const int tid = threadIdx.x;
-    const int n = P.n, m = P.m;
-    const int64_t N = P.N, N1 = P.N1, NU = P.NU;
-    const double *U = z + (int64_t)n * N1;
-    const double *yb = y + (int64_t)n * N;  // boundary-row multipliers
-    const bool euler = P.scheme != 0;
-    const double al = euler ? P.h : P.hh, be = euler ? 0.0 : P.hh;
     double acc = 0.0;
-    for (int ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
-        const int64_t k = (int64_t)ch * (kBlock - 1) + tid;
-        // the multipliers of this lane's interval, loaded up front so that
-        // they arrive while the node's dynamics are evaluated (index clamped
-        // into the row; used only for k < N)
-        double yv[NB];
-        const int64_t ky = k < N ? k : N - 1;
-#pragma unroll
-        for (int i = 0; i < NB; i++) yv[i] = y[(int64_t)(i < n ? i : 0) * N + ky];
-        double Pk[NB];
-        if (k <= N) {
-            double x[NB], F[NB];
-            if (k < NU) {
-                dyn_node<NB>(P, z, k, x, F);
-            } else {  // forward Euler, node N: F(N) enters no row
-#pragma unroll
-                for (int i = 0; i < NB; i++) {
-                    x[i] = (i < n) ? z[i * N1 + k] : 0.0;
-                    F[i] = 0.0;
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < NB; i++) {
-                if (i < n) {
-                    Ms[i][tid] = x[i] - be * F[i];
-                    Pk[i] = x[i] + al * F[i];
-                }
-            }
-            if (tid < kBlock - 1 || k == N) {
-                double s = 0.0;
-#pragma unroll
-                for (int i = 0; i < NB; i++)
-                    if (i < n) s += P.q[i] * x[i] * x[i];
-                if (k < NU) {
-                    for (int l = 0; l < m; l++) {
-                        const double u = U[l * NU + k];
-                        s += P.r[l] * u * u;
-                    }
-                }
-                acc += sigma * node_weight(P, (int)k) * s;
-                // boundary rows: the state at node 0 (and at node N)
-                if (P.nb >= n && k == 0) {
-#pragma unroll
-                    for (int i = 0; i < NB; i++)
-                        if (i < n) acc += yb[i] * x[i];
-                }
-                if (P.nb >= 2 * n && k == N) {
-#pragma unroll
-                    for (int i = 0; i < NB; i++)
-                        if (i < n) acc += yb[n + i] * x[i];
-                }
-            }
-        }
-        __syncthreads();
-        if (tid < kBlock - 1 && k < N) {
-#pragma unroll
-            for (int i = 0; i < NB; i++)
-                if (i < n) acc += yv[i] * (Ms[i][tid + 1] - Pk[i]);
-        }
-        __syncthreads();
+    if constexpr (LOOP) {
+        for (int ch = blockIdx.x; ch < nchunks; ch += gridDim.x) lag_chunk<NB, MB, true>(P, z, y, sigma, ch, Ms, acc);
+    } else {
+        lag_chunk<NB, MB, false>(P, z, y, sigma, blockIdx.x, Ms, acc);
     }
     const double t = block_sum<kBlock>(acc);
     if (threadIdx.x == 0) partials[blockIdx.x] = t;
@@ -144,9 +154,7 @@ __global__ __launch_bounds__(kBlock) void lag_partial_kernel(KP P, const double 
 __global__ __launch_bounds__(kBlock) void sum_partials_kernel(const double *__restrict__ partials,
                                                               int count, double *__restrict__ out)
 {
-    double acc = 0.0;
-    for (int i = threadIdx.x; i < count; i += kBlock) acc += partials[i];
-    const double t = block_sum<kBlock>(acc);
+    const double t = sum_partials(partials, count);
     if (threadIdx.x == 0) out[0] = t;
 }
 
@@ -186,9 +194,11 @@ __device__ __forceinline__ void node_controls(const KP &P, const double *__restr
 template <int NB>
 __global__ __launch_bounds__(kBlock) void lag_grad_kernel(KP P, const double *__restrict__ z,
                                                           const double *__restrict__ y, double sigma,
-                                                          double *__restrict__ g)
+                                                          double *__restrict__ g,
+                                                          const double *__restrict__ scale)
 {
     const int k = blockIdx.x * kBlock + threadIdx.x;
+    const double f = scale ? *scale : 1.0;
     if (k > P.N) return;
     const int n = P.n, m = P.m;
     const int64_t N = P.N, N1 = P.N1, NU = P.NU;
@@ -218,7 +228,7 @@ __global__ __launch_bounds__(kBlock) void lag_grad_kernel(KP P, const double *__
             const double G = cos(x[j]) * s + yt[j] * P.gam[j] * xn + ym * P.gam[jm] * xm;
             double val = 2.0 * sigma * w * P.q[j] * x[j] + (yl[j] - yr[j]) - wF * G;
             if (yb) val += yb[j];
-            st_nt(g + j * N1 + k, val);
+            st_nt(g + j * N1 + k, val * f);
         }
     }
     if (k >= NU) return;  // forward Euler: no controls at node N
@@ -228,7 +238,7 @@ __global__ __launch_bounds__(kBlock) void lag_grad_kernel(KP P, const double *__
         double s = 0.0;
 #pragma unroll
         for (int i = 0; i < NB; i++) s = __builtin_fma(yt[i], b[i], s);
-        st_nt(g + n * N1 + l * NU + k, 2.0 * sigma * w * P.r[l] * U[l * NU + k] - wF * s);
+        st_nt(g + n * N1 + l * NU + k, (2.0 * sigma * w * P.r[l] * U[l * NU + k] - wF * s) * f);
     }
 }
 
@@ -276,7 +286,7 @@ __global__ __launch_bounds__(kBlock) void hvp_kernel(KP P, const double *__restr
     }
 }
 
-// J v, laid out like the defects: lane k publishes v_ik - be D_i(k) for lane
+// J v, laid out like the defects (kSpan intervals per workgroup): lane k publishes v_ik - be D_i(k) for lane
 // k-1 and keeps v_ik + al D_i(k).
 template <int NB>
 __global__ __launch_bounds__(kBlock) void jvp_kernel(KP P, const double *__restrict__ z,
@@ -285,7 +295,7 @@ __global__ __launch_bounds__(kBlock) void jvp_kernel(KP P, const double *__restr
 {
     __shared__ double Ms[NB][kBlock];
     const int tid = threadIdx.x;
-    const int64_t k = (int64_t)blockIdx.x * (kBlock - 1) + tid;
+    const int64_t k = (int64_t)blockIdx.x * kSpan + tid;
     const int n = P.n, m = P.m;
     const int64_t N = P.N, N1 = P.N1, NU = P.NU;
     const bool euler = P.scheme != 0;
@@ -335,7 +345,7 @@ __global__ __launch_bounds__(kBlock) void jvp_kernel(KP P, const double *__restr
         }
     }
     __syncthreads();
-    if (tid < kBlock - 1 && k < N) {
+    if (tid < kSpan && k < N) {
 #pragma unroll
         for (int i = 0; i < NB; i++)
             if (i < n) st_nt(out + i * N + k, Ms[i][tid + 1] - Pk[i]);
@@ -569,7 +579,8 @@ __global__ __launch_bounds__(kBlock) void coef_partial_kernel(
 __global__ __launch_bounds__(kBlock) void coef_final_kernel(KP P, const double *__restrict__ cpart,
                                                             int G, double *__restrict__ gA,
                                                             double *__restrict__ gB,
-                                                            double *__restrict__ gg)
+                                                            double *__restrict__ gg,
+                                                            const double *__restrict__ scale)
 {
     const int n = P.n, m = P.m, ncol = n + m + 1, nc = n * ncol;
     const int idx = blockIdx.x;
@@ -577,7 +588,8 @@ __global__ __launch_bounds__(kBlock) void coef_final_kernel(KP P, const double *
     for (int b = threadIdx.x; b < G; b += kBlock) s += cpart[(int64_t)b * nc + idx];
     s = block_sum<kBlock>(s);
     if (threadIdx.x != 0) return;
-    const double val = -(P.scheme != 0 ? P.h : P.hh) * s;
+    double val = -(P.scheme != 0 ? P.h : P.hh) * s;
+    if (scale) val *= *scale;
     const int i = idx / ncol, col = idx - i * ncol;
     if (col < n) gA[i * n + col] = val;
     else if (col < n + m) gB[i * m + (col - n)] = val;
@@ -595,8 +607,8 @@ __global__ __launch_bounds__(kBlock) void coef_final_kernel(KP P, const double *
 // z-gradient is the coefficient part of J^T y with theta := t:
 //   at X_jk  -wF (cos X_jk (tA^T yt)_j + yt_j tg_j X_p(j)k + yt_q tg_q X_qk),
 //   at U_lk  -wF (tB^T yt)_l,
-// q = (j-1) mod n being the row whose bilinear partner is j.  Chunks of B
-// nodes close B-1 intervals, as in the defect kernel: lane k publishes
+// q = (j-1) mod n being the row whose bilinear partner is j.  Workgroups
+// of kBlock nodes close kSpan intervals, as in the defect kernel: lane k publishes
 // Ft(k) in LDS for lane k-1, and node k's z-entries are written by the chunk
 // in which it is not the overlap node.  Every workgroup copies t from the
 // caller's row-major arrays into zero-padded columns in LDS (the same region
@@ -618,7 +630,7 @@ __global__ __launch_bounds__(kBlock) void coef_adjoint_kernel(KP P, const double
     const int tid = threadIdx.x;
     const int n = P.n, m = P.m;
     const int64_t N = P.N, N1 = P.N1, NU = P.NU;
-    const int64_t k = (int64_t)blockIdx.x * (kBlock - 1) + tid;
+    const int64_t k = (int64_t)blockIdx.x * kSpan + tid;
     const bool live = k <= N;
     const bool euler = P.scheme != 0;
     const double wF = euler ? P.h : P.hh;
@@ -651,7 +663,7 @@ __global__ __launch_bounds__(kBlock) void coef_adjoint_kernel(KP P, const double
     if (gy && blockIdx.x == 0 && tid < P.nb) gy[(int64_t)n * N + tid] = 0.0;  // boundary rows
     __syncthreads();
     if (live) {
-        if (gz && (tid < kBlock - 1 || k == N)) {
+        if (gz && (tid < kSpan || k == N)) {
             const double x_last = last_of<NB>(x, n), yt_last = last_of<NB>(yt, n);
 #pragma unroll
             for (int j = 0; j < NB; j++) {
@@ -664,7 +676,7 @@ __global__ __launch_bounds__(kBlock) void coef_adjoint_kernel(KP P, const double
                     const double xm = (j == 0) ? x_last : x[(j + NB - 1) % NB];
                     const double ym = (j == 0) ? yt_last : yt[(j + NB - 1) % NB];
                     const double G = cos(x[j]) * s + yt[j] * cg[j] * xn + ym * cg[jm] * xm;
-                    gz[j * N1 + k] = -wF * G;
+                    st_nt(gz + j * N1 + k, -wF * G);
                 }
             }
             if (k < NU) {
@@ -672,7 +684,7 @@ __global__ __launch_bounds__(kBlock) void coef_adjoint_kernel(KP P, const double
                     double s = 0.0;
 #pragma unroll
                     for (int i = 0; i < NB; i++) s = __builtin_fma(yt[i], cB[l * NB + i], s);
-                    gz[n * N1 + l * NU + k] = -wF * s;
+                    st_nt(gz + n * N1 + l * NU + k, -wF * s);
                 }
             }
         }
@@ -710,41 +722,14 @@ __global__ __launch_bounds__(kBlock) void coef_adjoint_kernel(KP P, const double
             if (i < n) lds[i * kBlock + tid] = Ft[i];
     }
     __syncthreads();
-    if (tid < kBlock - 1 && k < N) {
+    if (tid < kSpan && k < N) {
 #pragma unroll
         for (int i = 0; i < NB; i++) {
             if (i < n) {
                 const double v = euler ? -P.h * Ft[i] : -P.hh * (Ft[i] + lds[i * kBlock + tid + 1]);
-                gy[i * N + k] = v;
+                st_nt(gy + i * N + k, v);
             }
         }
-    }
-}
-
-// Up to five device arrays scaled in place by one device double (the
-// incoming gradient of a backward pass), in one launch over their
-// concatenation; end[j] is the cumulative length through array j.
-struct ScaleSegs {
-    double *p[5];
-    int64_t end[5];
-    int count;
-};
-
-__global__ __launch_bounds__(kBlock) void scale_kernel(ScaleSegs s, const double *__restrict__ g)
-{
-    const int64_t total = s.end[s.count - 1];
-    const double f = *g;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < total; i += (int64_t)gridDim.x * kBlock) {
-        double *dst = s.p[0];
-        int64_t off = i;
-#pragma unroll
-        for (int j = 1; j < 5; j++) {
-            if (j < s.count && i >= s.end[j - 1]) {
-                dst = s.p[j];
-                off = i - s.end[j - 1];
-            }
-        }
-        dst[off] *= f;
     }
 }
 
@@ -808,7 +793,10 @@ double *noalloc_scratch(int device)
 }
 
 static int launch_coef_grad(const ocp_problem *p, const double *z, const double *y, const double *v, double *gA,
-                            double *gB, double *ggamma, double *cpart, hipStream_t stream, const char *fn);
+                            double *gB, double *ggamma, double *cpart, const double *scale, hipStream_t stream,
+                            const char *fn);
+static int launch_lag_grad(const ocp_problem *p, const double *z, const double *y, double sigma, double *g,
+                           const double *scale, hipStream_t stream, const char *fn);
 
 #define OCP_DISPATCH_NB(n, KERNEL, grid, ...)                                                   \
     do {                                                                                        \
@@ -819,6 +807,29 @@ static int launch_coef_grad(const ocp_problem *p, const double *z, const double 
         default: hipLaunchKernelGGL(KERNEL<32>, grid, dim3(kBlock), 0, __VA_ARGS__); break;    \
         }                                                                                       \
     } while (0)
+
+// The first pass of the Lagrangian's value for the state bound NB: the
+// controls' register bound is halved when m <= NB / 2, as for the defects, and
+// a grid that covers every chunk takes the kernel without the chunk loop.
+template <int NB, int MB>
+static void launch_lag_partial_mb(const KP &P, int g, const double *z, const double *y, double sigma, int nchunks,
+                                  double *partials, hipStream_t stream)
+{
+    if (nchunks <= g)
+        hipLaunchKernelGGL((lag_partial_kernel<NB, MB, false>), dim3(g), dim3(kBlock), 0, stream, P, z, y, sigma,
+                           nchunks, partials);
+    else
+        hipLaunchKernelGGL((lag_partial_kernel<NB, MB, true>), dim3(g), dim3(kBlock), 0, stream, P, z, y, sigma,
+                           nchunks, partials);
+}
+
+template <int NB>
+static void launch_lag_partial(const KP &P, int g, const double *z, const double *y, double sigma, int nchunks,
+                               double *partials, hipStream_t stream)
+{
+    if (P.m <= NB / 2) launch_lag_partial_mb<NB, NB / 2>(P, g, z, y, sigma, nchunks, partials, stream);
+    else launch_lag_partial_mb<NB, NB>(P, g, z, y, sigma, nchunks, partials, stream);
+}
 
 extern "C" {
 
@@ -849,7 +860,12 @@ int ocp_eval_lagrangian(const ocp_problem *p, const double *z, const double *y, 
     if (p->model == quad::kModel) return quad::eval_lagrangian(p, z, y, sigma, L, stream);
     const int nchunks = (int)blocks_for(p->d.N, kBlock - 1);
     const int g = std::min(nchunks, kObjBlocks);
-    OCP_DISPATCH_NB(p->d.n, lag_partial_kernel, dim3(g), stream, p->kp, z, y, sigma, nchunks, p->partials);
+    switch (nb_of(p->d.n)) {
+    case 4: launch_lag_partial<4>(p->kp, g, z, y, sigma, nchunks, p->partials, stream); break;
+    case 8: launch_lag_partial<8>(p->kp, g, z, y, sigma, nchunks, p->partials, stream); break;
+    case 16: launch_lag_partial<16>(p->kp, g, z, y, sigma, nchunks, p->partials, stream); break;
+    default: launch_lag_partial<32>(p->kp, g, z, y, sigma, nchunks, p->partials, stream); break;
+    }
     if (int rc = check_launch("ocp_eval_lagrangian")) return rc;
     hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(kBlock), 0, stream, p->partials, g, L);
     return check_launch("ocp_eval_lagrangian");
@@ -862,10 +878,7 @@ int ocp_eval_lag_grad(const ocp_problem *p, const double *z, const double *y, do
     if (int rc = check_handle(p, "ocp_eval_lag_grad")) return rc;
     if (!z || !y || !g) return fail(OCP_ERR_ARG, "ocp_eval_lag_grad: null array");
     if (!std::isfinite(sigma)) return fail(OCP_ERR_ARG, "ocp_eval_lag_grad: sigma is not finite");
-    if (p->model == quad::kModel) return quad::eval_lag_grad(p, z, y, sigma, g, stream);
-    OCP_DISPATCH_NB(p->d.n, lag_grad_kernel, dim3(blocks_for(p->d.N1, kBlock)), stream, p->kp, z, y,
-                    sigma, g);
-    return check_launch("ocp_eval_lag_grad");
+    return launch_lag_grad(p, z, y, sigma, g, nullptr, stream, "ocp_eval_lag_grad");
 }
 
 int ocp_eval_hvp(const ocp_problem *p, const double *z, const double *y, double sigma,
@@ -888,7 +901,7 @@ int ocp_eval_jvp(const ocp_problem *p, const double *z, const double *v, double 
     if (int rc = check_handle(p, "ocp_eval_jvp")) return rc;
     if (!z || !v || !out) return fail(OCP_ERR_ARG, "ocp_eval_jvp: null array");
     if (p->model == quad::kModel) return quad::eval_jvp(p, z, v, out, stream);
-    OCP_DISPATCH_NB(p->d.n, jvp_kernel, dim3(blocks_for(p->d.N, kBlock - 1)), stream, p->kp, z, v,
+    OCP_DISPATCH_NB(p->d.n, jvp_kernel, dim3(blocks_for(p->d.N, kSpan)), stream, p->kp, z, v,
                     out);
     return check_launch("ocp_eval_jvp");
 }
@@ -901,7 +914,7 @@ int ocp_eval_coef_grad(const ocp_problem *p, const double *z, const double *y, d
     if (int rc = check_coefficients(p, "ocp_eval_coef_grad")) return rc;
     if (!z || !y || !gA || !ggamma || (p->d.m > 0 && !gB))
         return fail(OCP_ERR_ARG, "ocp_eval_coef_grad: null array");
-    return launch_coef_grad(p, z, y, nullptr, gA, gB, ggamma, p->cpart, stream, "ocp_eval_coef_grad");
+    return launch_coef_grad(p, z, y, nullptr, gA, gB, ggamma, p->cpart, nullptr, stream, "ocp_eval_coef_grad");
 }
 
 int ocp_eval_coef_mixed(const ocp_problem *p, const double *z, const double *y, const double *v, double *gA,
@@ -912,7 +925,7 @@ int ocp_eval_coef_mixed(const ocp_problem *p, const double *z, const double *y, 
     if (int rc = check_coefficients(p, "ocp_eval_coef_mixed")) return rc;
     if (!z || !y || !v || !gA || !ggamma || (p->d.m > 0 && !gB))
         return fail(OCP_ERR_ARG, "ocp_eval_coef_mixed: null array");
-    return launch_coef_grad(p, z, y, v, gA, gB, ggamma, p->cpart, stream, "ocp_eval_coef_mixed");
+    return launch_coef_grad(p, z, y, v, gA, gB, ggamma, p->cpart, nullptr, stream, "ocp_eval_coef_mixed");
 }
 
 int ocp_eval_lagrangian_backward(const ocp_problem *p, const double *z, const double *y, double sigma,
@@ -931,33 +944,22 @@ int ocp_eval_lagrangian_backward(const ocp_problem *p, const double *z, const do
             return fail(OCP_ERR_ARG, std::string(fn) + ": gA and ggamma (and gB when m > 0) go together");
     }
     if (!gz && !gy && !coef) return fail(OCP_ERR_ARG, std::string(fn) + ": no output");
-    // the same kernels as the three separate calls, then one scale
+    // the kernels of the three separate calls, each multiplying its values by
+    // gL as it stores them (a scaling pass of its own read and wrote every
+    // output again: 13.6 us at N = 2e5, n = 8, m = 4)
     if (gz)
-        if (int rc = ocp_eval_lag_grad(p, z, y, sigma, gz, stream)) return rc;
-    if (gy)
-        if (int rc = ocp_eval_cons(p, z, gy, stream)) return rc;
-    if (coef)
-        if (int rc = ocp_eval_coef_grad(p, z, y, gA, gB, ggamma, stream)) return rc;
-    ScaleSegs segs{};
-    int64_t total = 0;
-    auto add = [&](double *ptr, int64_t len) {
-        if (!ptr || len <= 0) return;
-        total += len;
-        segs.p[segs.count] = ptr;
-        segs.end[segs.count++] = total;
-    };
-    const int64_t n = p->d.n, m = p->d.m;
-    add(gz, p->d.nvar);
-    add(gy, p->d.ncon);
-    if (coef) {
-        add(gA, n * n);
-        add(gB, n * m);
-        add(ggamma, n);
+        if (int rc = launch_lag_grad(p, z, y, sigma, gz, gL, stream, fn)) return rc;
+    if (gy) {
+        if (p->model == quad::kModel) {
+            if (int rc = quad::eval_cons(p, z, gy, gL, stream)) return rc;
+        } else {
+            const hipError_t e = launch_cons(p->kp, z, gy, gL, stream);
+            if (e != hipSuccess) return hip_fail(fn, e);
+        }
     }
-    if (segs.count == 0) return OCP_OK;
-    const unsigned grid = std::min<unsigned>(blocks_for(total, kBlock), 4096u);
-    hipLaunchKernelGGL(scale_kernel, dim3(grid), dim3(kBlock), 0, stream, segs, gL);
-    return check_launch(fn);
+    if (coef)
+        if (int rc = launch_coef_grad(p, z, y, nullptr, gA, gB, ggamma, p->cpart, gL, stream, fn)) return rc;
+    return OCP_OK;
 }
 
 int ocp_eval_coef_adjoint(const ocp_problem *p, const double *z, const double *y, const double *tA,
@@ -969,7 +971,7 @@ int ocp_eval_coef_adjoint(const ocp_problem *p, const double *z, const double *y
     if (int rc = check_coefficients(p, fn)) return rc;
     if (!z || !y || !tA || !tgamma || (p->d.m > 0 && !tB)) return fail(OCP_ERR_ARG, std::string(fn) + ": null array");
     if (!gz && !gy) return fail(OCP_ERR_ARG, std::string(fn) + ": no output (gz and gy are both NULL)");
-    OCP_DISPATCH_NB(p->d.n, coef_adjoint_kernel, dim3(blocks_for(p->d.N, kBlock - 1)), stream, p->kp, z, y, tA, tB,
+    OCP_DISPATCH_NB(p->d.n, coef_adjoint_kernel, dim3(blocks_for(p->d.N, kSpan)), stream, p->kp, z, y, tA, tB,
                     tgamma, gz, gy);
     return check_launch(fn);
 }
@@ -994,10 +996,19 @@ int ocp_eval_coef_grad_noalloc(const ocp_problem *p, const double *z, const doub
         return fail(OCP_ERR_ARG, std::string(fn) + ": the current device is not the handle's");
     double *ws = noalloc_scratch(dev);
     if (!ws) return fail(OCP_ERR_HIP, std::string(fn) + ": the scratch array's device address is unknown");
-    return launch_coef_grad(p, z, y, nullptr, gA, gB, ggamma, ws, stream, fn);
+    return launch_coef_grad(p, z, y, nullptr, gA, gB, ggamma, ws, nullptr, stream, fn);
 }
 
 }  // extern "C"
+
+// grad_z L; `scale`: null, or a device double that multiplies every value.
+static int launch_lag_grad(const ocp_problem *p, const double *z, const double *y, double sigma, double *g,
+                           const double *scale, hipStream_t stream, const char *fn)
+{
+    if (p->model == quad::kModel) return quad::eval_lag_grad(p, z, y, sigma, g, scale, stream);
+    OCP_DISPATCH_NB(p->d.n, lag_grad_kernel, dim3(blocks_for(p->d.N1, kBlock)), stream, p->kp, z, y, sigma, g, scale);
+    return check_launch(fn);
+}
 
 template <bool MIXED>
 static void launch_coef_partial(const ocp_problem *p, const double *z, const double *y, const double *v, int G,
@@ -1022,8 +1033,10 @@ static void launch_coef_partial(const ocp_problem *p, const double *z, const dou
 }
 
 // v == nullptr: the coefficient gradient; otherwise its derivative along v.
+// `scale`: null, or a device double that multiplies every value.
 static int launch_coef_grad(const ocp_problem *p, const double *z, const double *y, const double *v, double *gA,
-                            double *gB, double *ggamma, double *cpart, hipStream_t stream, const char *fn)
+                            double *gB, double *ggamma, double *cpart, const double *scale, hipStream_t stream,
+                            const char *fn)
 {
     const int n = p->d.n, m = p->d.m, ncol = n + m + 1;
     const int G = coef_blocks(p->d.N1);
@@ -1031,6 +1044,6 @@ static int launch_coef_grad(const ocp_problem *p, const double *z, const double 
     else launch_coef_partial<false>(p, z, y, nullptr, G, cpart, stream);
     if (int rc = check_launch(fn)) return rc;
     hipLaunchKernelGGL(coef_final_kernel, dim3(n * ncol), dim3(kBlock), 0, stream, p->kp, cpart, G,
-                       gA, gB, ggamma);
+                       gA, gB, ggamma, scale);
     return check_launch(fn);
 }

@@ -69,22 +69,25 @@ __global__ __launch_bounds__(kBlock) void hess_kernel(KP P, const double *__rest
 }
 
 // ---------------------------------------------------------------------------
-// Defects.  Workgroup b evaluates the dynamics at nodes [b (B-1), b (B-1) + B),
-// one node per lane, and writes the B-1 intervals they close (one node of
-// overlap between workgroups).  With
+// Defects.  Workgroup b evaluates the dynamics at kBlock nodes from b kSpan,
+// one node per lane, and writes kSpan of the intervals they close.  With
 //   c_ik = (X_{i,k+1} - hh F_i(k+1)) - (X_ik + hh F_i(k)),
 // lane k keeps X_ik + hh F_i(k) in registers and publishes X_ik - hh F_i(k)
-// in LDS for lane k-1, so every state value is read from HBM once.
+// in LDS for lane k-1, so every state value is read from HBM once.  kSpan is
+// 240, not the 255 intervals the nodes close: a multiple of a line, so that
+// where N is one too every wavefront stores whole lines.  `scale`: null, or a
+// device double that multiplies every value (a backward pass).
 // ---------------------------------------------------------------------------
 template <int NB, int MB>
 __global__ __launch_bounds__(kBlock) void cons_kernel(KP P, const double *__restrict__ z,
-                                                      double *__restrict__ c)
+                                                      double *__restrict__ c, const double *__restrict__ scale)
 {
     __shared__ double Ms[NB][kBlock];
     const int tid = threadIdx.x;
-    const int64_t k = (int64_t)blockIdx.x * (kBlock - 1) + tid;
+    const int64_t k = (int64_t)blockIdx.x * kSpan + tid;
     const int n = P.n;
     const int64_t N = P.N;
+    const double f = scale ? *scale : 1.0;
     double Pk[NB];
     if (k <= N) {
         double x[NB], F[NB];
@@ -98,12 +101,12 @@ __global__ __launch_bounds__(kBlock) void cons_kernel(KP P, const double *__rest
         }
     }
     __syncthreads();
-    if (tid < kBlock - 1 && k < N) {
+    if (tid < kSpan && k < N) {
 #pragma unroll
         for (int i = 0; i < NB; i++)
-            if (i < n) st_nt(c + i * N + k, Ms[i][tid + 1] - Pk[i]);
+            if (i < n) st_nt(c + i * N + k, (Ms[i][tid + 1] - Pk[i]) * f);
     }
-    if (blockIdx.x == 0 && tid < P.nb) c[n * N + tid] = bnd_value(P, z, tid);  // boundary rows
+    if (blockIdx.x == 0 && tid < P.nb) c[n * N + tid] = bnd_value(P, z, tid) * f;  // boundary rows
 }
 
 // ---------------------------------------------------------------------------
@@ -112,11 +115,13 @@ __global__ __launch_bounds__(kBlock) void cons_kernel(KP P, const double *__rest
 // ---------------------------------------------------------------------------
 template <int NB, int MB>
 __global__ __launch_bounds__(kBlock) void cons_euler_kernel(KP P, const double *__restrict__ z,
-                                                            double *__restrict__ c)
+                                                            double *__restrict__ c,
+                                                            const double *__restrict__ scale)
 {
     const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (k < P.N) cons_euler_interval<NB, MB>(P, z, c, k);
-    if (k < P.nb) c[(int64_t)P.n * P.N + k] = bnd_value(P, z, (int)k);  // boundary rows
+    const double f = scale ? *scale : 1.0;
+    if (k < P.N) cons_euler_interval<NB, MB>(P, z, c, k, f);
+    if (k < P.nb) c[(int64_t)P.n * P.N + k] = bnd_value(P, z, (int)k) * f;  // boundary rows
 }
 
 template <int NB>
@@ -163,9 +168,7 @@ __global__ __launch_bounds__(kBlock) void obj_partial_kernel(KP P, const double 
 __global__ __launch_bounds__(kBlock) void obj_final_kernel(const double *__restrict__ partials,
                                                            int count, double *__restrict__ obj)
 {
-    double acc = 0.0;
-    for (int i = threadIdx.x; i < count; i += kBlock) acc += partials[i];
-    const double t = block_sum<kBlock>(acc);
+    const double t = sum_partials(partials, count);
     if (threadIdx.x == 0) obj[0] = t;
 }
 
@@ -402,35 +405,35 @@ hipError_t launch_grad(const KP &P, const double *z, double *g, hipStream_t stre
 // of 125, 4 wavefronts per SIMD either way, 1-3 % faster at N = 1e6).  The
 // sums run in the same order, so the values are the same bits.
 template <int NB>
-void launch_cons_trap(const KP &P, unsigned g, const double *z, double *c, hipStream_t stream)
+void launch_cons_trap(const KP &P, unsigned g, const double *z, double *c, const double *scale, hipStream_t stream)
 {
-    if (P.m <= NB / 2) hipLaunchKernelGGL((cons_kernel<NB, NB / 2>), dim3(g), dim3(kBlock), 0, stream, P, z, c);
-    else hipLaunchKernelGGL((cons_kernel<NB, NB>), dim3(g), dim3(kBlock), 0, stream, P, z, c);
+    if (P.m <= NB / 2) hipLaunchKernelGGL((cons_kernel<NB, NB / 2>), dim3(g), dim3(kBlock), 0, stream, P, z, c, scale);
+    else hipLaunchKernelGGL((cons_kernel<NB, NB>), dim3(g), dim3(kBlock), 0, stream, P, z, c, scale);
 }
 
 // The forward-Euler defect kernel, with the same control bound.
 template <int NB>
-void launch_cons_euler(const KP &P, unsigned g, const double *z, double *c, hipStream_t stream)
+void launch_cons_euler(const KP &P, unsigned g, const double *z, double *c, const double *scale, hipStream_t stream)
 {
-    if (P.m <= NB / 2) hipLaunchKernelGGL((cons_euler_kernel<NB, NB / 2>), dim3(g), dim3(kBlock), 0, stream, P, z, c);
-    else hipLaunchKernelGGL((cons_euler_kernel<NB, NB>), dim3(g), dim3(kBlock), 0, stream, P, z, c);
+    if (P.m <= NB / 2) hipLaunchKernelGGL((cons_euler_kernel<NB, NB / 2>), dim3(g), dim3(kBlock), 0, stream, P, z, c, scale);
+    else hipLaunchKernelGGL((cons_euler_kernel<NB, NB>), dim3(g), dim3(kBlock), 0, stream, P, z, c, scale);
 }
 
-hipError_t launch_cons(const KP &P, const double *z, double *c, hipStream_t stream)
+hipError_t launch_cons(const KP &P, const double *z, double *c, const double *scale, hipStream_t stream)
 {
     const int n = P.n;
     if (P.scheme == 0) {
-        const unsigned g = blocks_for(P.N, kBlock - 1);
-        if (n <= 4) launch_cons_trap<4>(P, g, z, c, stream);
-        else if (n <= 8) launch_cons_trap<8>(P, g, z, c, stream);
-        else if (n <= 16) launch_cons_trap<16>(P, g, z, c, stream);
-        else launch_cons_trap<32>(P, g, z, c, stream);
+        const unsigned g = blocks_for(P.N, kSpan);
+        if (n <= 4) launch_cons_trap<4>(P, g, z, c, scale, stream);
+        else if (n <= 8) launch_cons_trap<8>(P, g, z, c, scale, stream);
+        else if (n <= 16) launch_cons_trap<16>(P, g, z, c, scale, stream);
+        else launch_cons_trap<32>(P, g, z, c, scale, stream);
     } else {
         const unsigned g = blocks_for(P.N, kBlock);
-        if (n <= 4) launch_cons_euler<4>(P, g, z, c, stream);
-        else if (n <= 8) launch_cons_euler<8>(P, g, z, c, stream);
-        else if (n <= 16) launch_cons_euler<16>(P, g, z, c, stream);
-        else launch_cons_euler<32>(P, g, z, c, stream);
+        if (n <= 4) launch_cons_euler<4>(P, g, z, c, scale, stream);
+        else if (n <= 8) launch_cons_euler<8>(P, g, z, c, scale, stream);
+        else if (n <= 16) launch_cons_euler<16>(P, g, z, c, scale, stream);
+        else launch_cons_euler<32>(P, g, z, c, scale, stream);
     }
     return hipGetLastError();
 }
@@ -566,8 +569,8 @@ int ocp_eval_cons(const ocp_problem *p, const double *z, double *c, hipStream_t 
     clear_error();
     if (int rc = check_handle(p, "ocp_eval_cons")) return rc;
     if (!z || !c) return fail(OCP_ERR_ARG, "ocp_eval_cons: null array");
-    if (p->model == quad::kModel) return quad::eval_cons(p, z, c, stream);
-    const hipError_t e = launch_cons(p->kp, z, c, stream);
+    if (p->model == quad::kModel) return quad::eval_cons(p, z, c, nullptr, stream);
+    const hipError_t e = launch_cons(p->kp, z, c, nullptr, stream);
     if (e != hipSuccess) return hip_fail("ocp_eval_cons", e);
     return OCP_OK;
 }

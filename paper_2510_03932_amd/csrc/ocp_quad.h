@@ -20,7 +20,8 @@ int make_dims(int64_t N, int32_t bnd, Dims *d);
 
 int eval_obj(const ocp_problem *p, const double *z, double *obj, hipStream_t stream);
 int eval_grad(const ocp_problem *p, const double *z, double *g, hipStream_t stream);
-int eval_cons(const ocp_problem *p, const double *z, double *c, hipStream_t stream);
+// `scale`: null, or a device double that multiplies every value
+int eval_cons(const ocp_problem *p, const double *z, double *c, const double *scale, hipStream_t stream);
 int eval_jac(const ocp_problem *p, const double *z, double *jvals, hipStream_t stream);
 int eval_hess(const ocp_problem *p, const double *z, const double *y, double sigma, double *hvals,
               hipStream_t stream);
@@ -33,7 +34,7 @@ int eval_kkt(const ocp_problem *p, const double *z, const double *y, double sigm
 int eval_lagrangian(const ocp_problem *p, const double *z, const double *y, double sigma, double *L,
                     hipStream_t stream);
 int eval_lag_grad(const ocp_problem *p, const double *z, const double *y, double sigma, double *g,
-                  hipStream_t stream);
+                  const double *scale, hipStream_t stream);
 int eval_hvp(const ocp_problem *p, const double *z, const double *y, double sigma, const double *v,
              double *out, hipStream_t stream);
 int eval_jvp(const ocp_problem *p, const double *z, const double *v, double *out, hipStream_t stream);

@@ -206,19 +206,21 @@ __global__ __launch_bounds__(kBlock) void quad_hess_kernel(QP P, const double *_
 }
 
 // ---------------------------------------------------------------------------
-// Defects.  Workgroup b owns nodes [b (B-1), b (B-1) + B): every lane reads
-// its node once, evaluates F there and leaves (x, F) in LDS; lane t < B-1
-// then forms the defect of interval k = b (B-1) + t from its own node and
-// its neighbour's.
+// Defects.  Workgroup b owns kBlock nodes from b kSpan: every lane reads its
+// node once, evaluates F there and leaves (x, F) in LDS; lane t < kSpan then
+// forms the defect of interval b kSpan + t from its own node and its
+// neighbour's.  `scale`: null, or a device double that multiplies every value.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void quad_cons_kernel(QP P, const double *__restrict__ z,
-                                                           double *__restrict__ c)
+                                                           double *__restrict__ c,
+                                                           const double *__restrict__ scale)
 {
     __shared__ double Xs[kStates][kBlock];
     __shared__ double Fs[kStates][kBlock];
     const int tid = threadIdx.x;
-    const int64_t k = (int64_t)blockIdx.x * (kBlock - 1) + tid;
+    const int64_t k = (int64_t)blockIdx.x * kSpan + tid;
     const int64_t N = P.N, N1 = P.N1;
+    const double f = scale ? *scale : 1.0;
     double x[kStates], F[kStates];
     if (k <= N) {
         double u[4];
@@ -234,12 +236,12 @@ __global__ __launch_bounds__(kBlock) void quad_cons_kernel(QP P, const double *_
         }
     }
     __syncthreads();
-    if (tid < kBlock - 1 && k < N) {
+    if (tid < kSpan && k < N) {
 #pragma unroll
         for (int i = 0; i < kStates; i++)
-            st_nt(c + i * N + k, (Xs[i][tid + 1] - x[i]) - P.hh * (F[i] + Fs[i][tid + 1]));
+            st_nt(c + i * N + k, ((Xs[i][tid + 1] - x[i]) - P.hh * (F[i] + Fs[i][tid + 1])) * f);
     }
-    if (blockIdx.x == 0 && tid < P.nb) c[kStates * N + tid] = bnd_state(P, z, tid);  // boundary rows
+    if (blockIdx.x == 0 && tid < P.nb) c[kStates * N + tid] = bnd_state(P, z, tid) * f;  // boundary rows
 }
 
 // ---------------------------------------------------------------------------
@@ -286,9 +288,7 @@ __global__ __launch_bounds__(kBlock) void quad_obj_partial_kernel(QP P, const do
 __global__ __launch_bounds__(kBlock) void quad_obj_final_kernel(const double *__restrict__ partials, int count,
                                                                 double *__restrict__ obj)
 {
-    double acc = 0.0;
-    for (int i = threadIdx.x; i < count; i += kBlock) acc += partials[i];
-    const double t = block_sum<kBlock>(acc);
+    const double t = sum_partials(partials, count);
     if (threadIdx.x == 0) obj[0] = t;
 }
 
@@ -546,11 +546,13 @@ __global__ __launch_bounds__(kBlock) void quad_lag_partial_kernel(QP P, const do
 
 __global__ __launch_bounds__(kBlock) void quad_lag_grad_kernel(QP P, const double *__restrict__ z,
                                                                const double *__restrict__ y, double sigma,
-                                                               double *__restrict__ g)
+                                                               double *__restrict__ g,
+                                                               const double *__restrict__ scale)
 {
     const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (k > P.N) return;
     const int64_t N = P.N, N1 = P.N1;
+    const double f = scale ? *scale : 1.0;
     double x[kVars], yl[kStates], yr[kStates], G[kVars];
     load_node(P, z, k, x);
 #pragma unroll
@@ -578,7 +580,7 @@ __global__ __launch_bounds__(kBlock) void quad_lag_grad_kernel(QP P, const doubl
         for (int j = 0; j < kStates; j++) G[j] += y[kStates * N + kStates + j];
     }
 #pragma unroll
-    for (int j = 0; j < kVars; j++) st_nt(g + j * N1 + k, G[j]);
+    for (int j = 0; j < kVars; j++) st_nt(g + j * N1 + k, G[j] * f);
 }
 
 __global__ __launch_bounds__(kBlock) void quad_hvp_kernel(QP P, const double *__restrict__ z,
@@ -625,7 +627,7 @@ __global__ __launch_bounds__(kBlock) void quad_jvp_kernel(QP P, const double *__
 {
     __shared__ double Ms[kStates][kBlock];
     const int tid = threadIdx.x;
-    const int64_t k = (int64_t)blockIdx.x * (kBlock - 1) + tid;
+    const int64_t k = (int64_t)blockIdx.x * kSpan + tid;
     const int64_t N = P.N;
     double Pk[kStates];
     if (k <= N) {
@@ -641,7 +643,7 @@ __global__ __launch_bounds__(kBlock) void quad_jvp_kernel(QP P, const double *__
         }
     }
     __syncthreads();
-    if (tid < kBlock - 1 && k < N) {
+    if (tid < kSpan && k < N) {
 #pragma unroll
         for (int i = 0; i < kStates; i++) st_nt(out + i * N + k, Ms[i][tid + 1] - Pk[i]);
     }
@@ -840,10 +842,10 @@ int eval_lagrangian(const ocp_problem *p, const double *z, const double *y, doub
 }
 
 int eval_lag_grad(const ocp_problem *p, const double *z, const double *y, double sigma, double *g,
-                  hipStream_t stream)
+                  const double *scale, hipStream_t stream)
 {
     hipLaunchKernelGGL(quad_lag_grad_kernel, dim3(blocks_for(p->d.N1, kBlock)), dim3(kBlock), 0, stream,
-                       make_qp(p), z, y, sigma, g);
+                       make_qp(p), z, y, sigma, g, scale);
     return check_launch("ocp_eval_lag_grad");
 }
 
@@ -858,7 +860,7 @@ int eval_hvp(const ocp_problem *p, const double *z, const double *y, double sigm
 int eval_jvp(const ocp_problem *p, const double *z, const double *v, double *out, hipStream_t stream)
 {
     const QP P = make_qp(p);
-    hipLaunchKernelGGL(quad_jvp_kernel, dim3(blocks_for(p->d.N, kBlock - 1)), dim3(kBlock), 0, stream, P, z,
+    hipLaunchKernelGGL(quad_jvp_kernel, dim3(blocks_for(p->d.N, kSpan)), dim3(kBlock), 0, stream, P, z,
                        v, out);
     return check_launch("ocp_eval_jvp");
 }
@@ -870,11 +872,11 @@ int eval_grad(const ocp_problem *p, const double *z, double *g, hipStream_t stre
     return check_launch("ocp_eval_grad");
 }
 
-int eval_cons(const ocp_problem *p, const double *z, double *c, hipStream_t stream)
+int eval_cons(const ocp_problem *p, const double *z, double *c, const double *scale, hipStream_t stream)
 {
     const QP P = make_qp(p);
-    hipLaunchKernelGGL(quad_cons_kernel, dim3(blocks_for(p->d.N, kBlock - 1)), dim3(kBlock), 0, stream, P,
-                       z, c);
+    hipLaunchKernelGGL(quad_cons_kernel, dim3(blocks_for(p->d.N, kSpan)), dim3(kBlock), 0, stream, P, z, c,
+                       scale);
     return check_launch("ocp_eval_cons");
 }
 

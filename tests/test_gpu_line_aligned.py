@@ -193,3 +193,50 @@ def test_quadrotor_tiles(ocp, N, bnd, offset):
     want = oracle.assemble(rp, pj, jac.values(), ph, oh, reg)
     assert np.array_equal(asm.values().view(np.uint64), want.view(np.uint64))
     prob.close()
+
+
+# workgroups of the defect, J v and coefficient-adjoint kernels close 240
+# intervals from 256 nodes; the Lagrangian's first pass takes one chunk of 255
+# per workgroup up to 4096 of them; its controls' register bound halves when
+# m <= half the state bound
+@pytest.mark.parametrize("N,n,m,scheme,bnd", [
+    (240, 4, 2, 0, 1), (241, 4, 3, 0, 0), (255, 8, 4, 0, 2), (256, 8, 5, 1, 1), (480, 3, 0, 0, 0), (479, 16, 8, 0, 1),
+    (511, 16, 9, 1, 0), (1, 2, 1, 0, 2), (239, 20, 10, 0, 0), (1044480, 1, 1, 0, 0), (1044481, 1, 1, 0, 1)])
+def test_node_spans(ocp, N, n, m, scheme, bnd):
+    print(f"[lines] spans N={N} n={n} m={m} scheme={scheme} bnd={bnd}", flush=True)
+    inst = synth.make_instance(N, n, m, seed=74, bnd=bnd, scheme=scheme)
+    prob = ocp.Problem.from_instance(inst, torch.device("cuda", 0))
+    z, y = _t(inst.z), _t(inst.y)
+    rng = np.random.default_rng(8)
+    v = rng.normal(size=prob.sizes["nvar"])
+    t = [rng.normal(size=sh) for sh in ((n, n), (n, m), (n,))]
+    cons, jv = Guarded(prob.sizes["ncon"], 1), Guarded(prob.sizes["ncon"], 3)
+    prob.cons(z, out=cons.out)
+    check_close(cons.values(), *oracle.cons_ex(inst, scheme, bnd), what="cons")
+    prob.jvp(z, _t(v), out=jv.out)
+    check_close(jv.values(), *oracle.jvp_ex(inst, v, scheme, bnd), what="jvp")
+    L = prob.lagrangian(z, y, 0.7).cpu().numpy()
+    want, mu = oracle.lagrangian_ex(inst, scheme, bnd, sigma=0.7)
+    check_close(L, np.atleast_1d(want), np.atleast_1d(mu), what="L")
+    gz, gy = Guarded(prob.sizes["nvar"], 0), Guarded(prob.sizes["ncon"], 9)
+    prob.coef_adjoint(z, y, *(_t(a) for a in t), out_z=gz.out, out_y=gy.out)
+    (wz, wy), (mz, my) = oracle.coef_adjoint_ex(inst, *t, scheme, bnd)
+    check_close(gz.values(), wz, mz, what="adjoint z")
+    check_close(gy.values(), wy, my, what="adjoint y")
+    prob.close()
+
+
+@pytest.mark.parametrize("quad,bnd", [(False, 0), (False, 2), (True, 1)])
+def test_scaled_backward_bits(ocp, quad, bnd):
+    """The one-call backward equals the separate calls' values times the
+    incoming gradient, bit for bit, with each kernel scaling its own stores."""
+    inst = synth.make_quadrotor(777, seed=75, bnd=bnd) if quad else synth.make_instance(777, 5, 3, seed=75, bnd=bnd)
+    prob = (ocp.QuadrotorProblem if quad else ocp.Problem).from_instance(inst, torch.device("cuda", 0))
+    z, y = _t(inst.z), _t(inst.y)
+    g = _t(np.array([-0.37]))
+    gz, gy, coef = prob.lagrangian_backward(z, y, 0.7, g, want_coef=not quad)
+    same = lambda a, b: torch.equal(a.view(torch.int64), b.view(torch.int64))  # noqa: E731
+    assert same(gz, prob.lag_grad(z, y, 0.7) * g) and same(gy, prob.cons(z) * g)
+    if not quad:
+        assert all(same(a, b * g) for a, b in zip(coef, prob.coef_grad(z, y)))
+    prob.close()
