@@ -286,9 +286,19 @@ def quad_kkt_pattern(N: int, boundary: int = 1, rowptr=True, colind=True, perm_j
     return rp, ci, pj, ph
 
 
+_torch_mod = None
+_Tensor = _float64 = _int32 = _raw_stream_of = None  # set with _torch_mod
+
+
 def _torch():
-    import torch
-    return torch
+    """torch, imported on first use (the host index layer works without it)."""
+    global _torch_mod, _Tensor, _float64, _int32, _raw_stream_of
+    if _torch_mod is None:
+        import torch
+        _Tensor, _float64, _int32 = torch.Tensor, torch.float64, torch.int32
+        _raw_stream_of = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _torch_mod = torch
+    return _torch_mod
 
 
 def _raw_stream(device):
@@ -297,9 +307,8 @@ def _raw_stream(device):
     returns the handle without building a Stream object, which saves about
     2 us of host time per library call; the public call is the fallback."""
     torch = _torch()
-    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    if raw is not None and device.index is not None:
-        return ctypes.c_void_p(raw(device.index))
+    if _raw_stream_of is not None and device.index is not None:
+        return ctypes.c_void_p(_raw_stream_of(device.index))
     return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
 
 
@@ -314,6 +323,7 @@ class Problem:
         self.options = _opts(scheme, boundary)
         self.device = torch.device("cuda", torch.cuda.current_device() if device is None
                                    else torch.device(device).index or 0)
+        self._index = self.device.index
         f64 = lambda a, shape: np.ascontiguousarray(np.asarray(a, np.float64).reshape(shape))
         A = f64(A, (n, n))
         B = f64(B, (n, m)) if m else np.zeros((n, 0))
@@ -359,6 +369,14 @@ class Problem:
 
     # -- marshalling helpers ---------------------------------------------------
     def _dev(self, t, numel, dtype, what):
+        """The address of tensor t, checked.  The one expression that holds for
+        a valid tensor comes first; the checks that name what is wrong run only
+        when it does not.  (The host time of the calls bounds small problems:
+        with this and the addresses passed as integers, the six calls of a step
+        at N = 1000 take 32.7 us against 37.)"""
+        if isinstance(t, _Tensor) and t.dtype is dtype and t.is_cuda and t.get_device() == self._index \
+                and t.numel() == numel and t.is_contiguous():
+            return t.data_ptr()
         torch = _torch()
         if not isinstance(t, torch.Tensor):
             raise TypeError(f"{what}: expected a torch tensor on {self.device}")
@@ -370,64 +388,57 @@ class Problem:
             raise ValueError(f"{what}: tensor must be contiguous")
         if t.numel() != numel:
             raise ValueError(f"{what}: {t.numel()} elements, expected {numel}")
-        return ctypes.c_void_p(t.data_ptr())
+        return t.data_ptr()
 
     def _out(self, out, numel, what):
-        torch = _torch()
         if out is None:
-            out = torch.empty(numel, dtype=torch.float64, device=self.device)
-        return out, self._dev(out, numel, torch.float64, what)
+            out = _torch_mod.empty(numel, dtype=_float64, device=self.device)
+        return out, self._dev(out, numel, _float64, what)
 
     def _stream(self):
         return _raw_stream(self.device)
 
     # -- evaluations -------------------------------------------------------------
     def obj(self, z, out=None):
-        torch = _torch()
-        zp = self._dev(z, self.sizes["nvar"], torch.float64, "z")
+        zp = self._dev(z, self.sizes["nvar"], _float64, "z")
         out, op = self._out(out, 1, "obj")
         _check(lib().ocp_eval_obj(self._h, zp, op, self._stream()), "ocp_eval_obj")
         return out
 
     def grad(self, z, out=None):
-        torch = _torch()
-        zp = self._dev(z, self.sizes["nvar"], torch.float64, "z")
+        zp = self._dev(z, self.sizes["nvar"], _float64, "z")
         out, op = self._out(out, self.sizes["nvar"], "grad")
         _check(lib().ocp_eval_grad(self._h, zp, op, self._stream()), "ocp_eval_grad")
         return out
 
     def cons(self, z, out=None):
-        torch = _torch()
-        zp = self._dev(z, self.sizes["nvar"], torch.float64, "z")
+        zp = self._dev(z, self.sizes["nvar"], _float64, "z")
         out, op = self._out(out, self.sizes["ncon"], "cons")
         _check(lib().ocp_eval_cons(self._h, zp, op, self._stream()), "ocp_eval_cons")
         return out
 
     def jac(self, z, out=None):
-        torch = _torch()
-        zp = self._dev(z, self.sizes["nvar"], torch.float64, "z")
+        zp = self._dev(z, self.sizes["nvar"], _float64, "z")
         out, op = self._out(out, self.sizes["nnzj"], "jac")
         _check(lib().ocp_eval_jac(self._h, zp, op, self._stream()), "ocp_eval_jac")
         return out
 
     def hess(self, z, y, sigma=1.0, out=None):
-        torch = _torch()
-        zp = self._dev(z, self.sizes["nvar"], torch.float64, "z")
-        yp = self._dev(y, self.sizes["ncon"], torch.float64, "y")
+        zp = self._dev(z, self.sizes["nvar"], _float64, "z")
+        yp = self._dev(y, self.sizes["ncon"], _float64, "y")
         out, op = self._out(out, self.sizes["nnzh"], "hess")
         _check(lib().ocp_eval_hess(self._h, zp, yp, float(sigma), op, self._stream()),
                "ocp_eval_hess")
         return out
 
     def assemble_kkt(self, perm_j, perm_h, rowptr, jvals, hvals, reg=None, out=None):
-        torch = _torch()
         s = self.sizes
-        pj = self._dev(perm_j, s["nnzj"], torch.int32, "perm_j")
-        ph = self._dev(perm_h, s["nnzh"], torch.int32, "perm_h")
-        rp = self._dev(rowptr, s["dim"] + 1, torch.int32, "rowptr")
-        jp = self._dev(jvals, s["nnzj"], torch.float64, "jvals")
-        hp = self._dev(hvals, s["nnzh"], torch.float64, "hvals")
-        gp = None if reg is None else self._dev(reg, s["dim"], torch.float64, "reg")
+        pj = self._dev(perm_j, s["nnzj"], _int32, "perm_j")
+        ph = self._dev(perm_h, s["nnzh"], _int32, "perm_h")
+        rp = self._dev(rowptr, s["dim"] + 1, _int32, "rowptr")
+        jp = self._dev(jvals, s["nnzj"], _float64, "jvals")
+        hp = self._dev(hvals, s["nnzh"], _float64, "hvals")
+        gp = None if reg is None else self._dev(reg, s["dim"], _float64, "reg")
         out, op = self._out(out, s["nnzk"], "kkt")
         _check(lib().ocp_assemble_kkt(self._h, pj, ph, rp, jp, hp, gp, op, self._stream()),
                "ocp_assemble_kkt")
@@ -436,45 +447,42 @@ class Problem:
     def eval_kkt(self, z, y, sigma=1.0, reg=None, out=None):
         """Jacobian and Hessian evaluated straight into the KKT values (the
         layout of kkt_pattern), the fused form of jac + hess + assemble_kkt."""
-        torch = _torch()
         s = self.sizes
-        zp = self._dev(z, s["nvar"], torch.float64, "z")
-        yp = self._dev(y, s["ncon"], torch.float64, "y")
-        gp = None if reg is None else self._dev(reg, s["dim"], torch.float64, "reg")
+        zp = self._dev(z, s["nvar"], _float64, "z")
+        yp = self._dev(y, s["ncon"], _float64, "y")
+        gp = None if reg is None else self._dev(reg, s["dim"], _float64, "reg")
         out, op = self._out(out, s["nnzk"], "kkt")
         _check(lib().ocp_eval_kkt(self._h, zp, yp, float(sigma), gp, op, self._stream()), "ocp_eval_kkt")
         return out
 
     def mapped_plan(self, perm_j, perm_h, diag):
         """Per-tile CSR ranges of slot maps, for assemble_kkt_mapped (int32 device tensor)."""
-        torch = _torch()
         s = self.sizes
-        pj = self._dev(perm_j, s["nnzj"], torch.int32, "perm_j")
-        ph = self._dev(perm_h, s["nnzh"], torch.int32, "perm_h")
-        dg = self._dev(diag, s["dim"], torch.int32, "diag")
+        pj = self._dev(perm_j, s["nnzj"], _int32, "perm_j")
+        ph = self._dev(perm_h, s["nnzh"], _int32, "perm_h")
+        dg = self._dev(diag, s["dim"], _int32, "diag")
         cnt = ctypes.c_int64()
         _check(lib().ocp_mapped_plan_size(self._h, ctypes.byref(cnt)), "ocp_mapped_plan_size")
-        plan = torch.empty(cnt.value, dtype=torch.int32, device=self.device)
-        _check(lib().ocp_mapped_plan(self._h, pj, ph, dg, ctypes.c_void_p(plan.data_ptr()), self._stream()),
+        plan = _torch_mod.empty(cnt.value, dtype=_int32, device=self.device)
+        _check(lib().ocp_mapped_plan(self._h, pj, ph, dg, plan.data_ptr(), self._stream()),
                "ocp_mapped_plan")
         return plan
 
     def assemble_kkt_mapped(self, perm_j, perm_h, diag, jvals, hvals, reg=None, out=None, plan=None):
         """Assembly through slot maps alone (any ordering, e.g. from kkt_permute);
         plan (from mapped_plan for the same maps) skips a pass over the maps."""
-        torch = _torch()
         s = self.sizes
-        pj = self._dev(perm_j, s["nnzj"], torch.int32, "perm_j")
-        ph = self._dev(perm_h, s["nnzh"], torch.int32, "perm_h")
-        dg = self._dev(diag, s["dim"], torch.int32, "diag")
-        jp = self._dev(jvals, s["nnzj"], torch.float64, "jvals")
-        hp = self._dev(hvals, s["nnzh"], torch.float64, "hvals")
-        gp = None if reg is None else self._dev(reg, s["dim"], torch.float64, "reg")
+        pj = self._dev(perm_j, s["nnzj"], _int32, "perm_j")
+        ph = self._dev(perm_h, s["nnzh"], _int32, "perm_h")
+        dg = self._dev(diag, s["dim"], _int32, "diag")
+        jp = self._dev(jvals, s["nnzj"], _float64, "jvals")
+        hp = self._dev(hvals, s["nnzh"], _float64, "hvals")
+        gp = None if reg is None else self._dev(reg, s["dim"], _float64, "reg")
         pl = None
         if plan is not None:
             cnt = ctypes.c_int64()
             _check(lib().ocp_mapped_plan_size(self._h, ctypes.byref(cnt)), "ocp_mapped_plan_size")
-            pl = self._dev(plan, cnt.value, torch.int32, "plan")
+            pl = self._dev(plan, cnt.value, _int32, "plan")
         out, op = self._out(out, s["nnzk"], "kkt")
         _check(lib().ocp_assemble_kkt_mapped(self._h, pj, ph, dg, pl, jp, hp, gp, op, self._stream()),
                "ocp_assemble_kkt_mapped")
@@ -484,50 +492,45 @@ class Problem:
     def set_coefficients(self, A, B, gamma):
         """Copy device tensors A (n, n), B (n, m), gamma (n,) into the handle
         (stream-ordered on the current stream)."""
-        torch = _torch()
         n, m = self.n, self.m
         # the contiguous copies stay referenced until the copies are queued:
         # a freed temporary could be handed to the next temporary's copy kernel
         A, gamma = A.contiguous(), gamma.contiguous()
         B = B.contiguous() if m else None
-        Ap = self._dev(A, n * n, torch.float64, "A")
-        Bp = self._dev(B, n * m, torch.float64, "B") if m else None
-        gp = self._dev(gamma, n, torch.float64, "gamma")
+        Ap = self._dev(A, n * n, _float64, "A")
+        Bp = self._dev(B, n * m, _float64, "B") if m else None
+        gp = self._dev(gamma, n, _float64, "gamma")
         _check(lib().ocp_set_coefficients(self._h, Ap, Bp, gp, self._stream()), "ocp_set_coefficients")
         self._coef_key = None  # an upload the autograd functions did not make
 
     def lagrangian(self, z, y, sigma=1.0, out=None):
-        torch = _torch()
-        zp = self._dev(z, self.sizes["nvar"], torch.float64, "z")
-        yp = self._dev(y, self.sizes["ncon"], torch.float64, "y")
+        zp = self._dev(z, self.sizes["nvar"], _float64, "z")
+        yp = self._dev(y, self.sizes["ncon"], _float64, "y")
         out, op = self._out(out, 1, "L")
         _check(lib().ocp_eval_lagrangian(self._h, zp, yp, float(sigma), op, self._stream()),
                "ocp_eval_lagrangian")
         return out
 
     def lag_grad(self, z, y, sigma=1.0, out=None):
-        torch = _torch()
-        zp = self._dev(z, self.sizes["nvar"], torch.float64, "z")
-        yp = self._dev(y, self.sizes["ncon"], torch.float64, "y")
+        zp = self._dev(z, self.sizes["nvar"], _float64, "z")
+        yp = self._dev(y, self.sizes["ncon"], _float64, "y")
         out, op = self._out(out, self.sizes["nvar"], "grad_z L")
         _check(lib().ocp_eval_lag_grad(self._h, zp, yp, float(sigma), op, self._stream()),
                "ocp_eval_lag_grad")
         return out
 
     def hvp(self, z, y, v, sigma=1.0, out=None):
-        torch = _torch()
-        zp = self._dev(z, self.sizes["nvar"], torch.float64, "z")
-        yp = self._dev(y, self.sizes["ncon"], torch.float64, "y")
-        vp = self._dev(v, self.sizes["nvar"], torch.float64, "v")
+        zp = self._dev(z, self.sizes["nvar"], _float64, "z")
+        yp = self._dev(y, self.sizes["ncon"], _float64, "y")
+        vp = self._dev(v, self.sizes["nvar"], _float64, "v")
         out, op = self._out(out, self.sizes["nvar"], "H v")
         _check(lib().ocp_eval_hvp(self._h, zp, yp, float(sigma), vp, op, self._stream()),
                "ocp_eval_hvp")
         return out
 
     def jvp(self, z, v, out=None):
-        torch = _torch()
-        zp = self._dev(z, self.sizes["nvar"], torch.float64, "z")
-        vp = self._dev(v, self.sizes["nvar"], torch.float64, "v")
+        zp = self._dev(z, self.sizes["nvar"], _float64, "z")
+        vp = self._dev(v, self.sizes["nvar"], _float64, "v")
         out, op = self._out(out, self.sizes["ncon"], "J v")
         _check(lib().ocp_eval_jvp(self._h, zp, vp, op, self._stream()), "ocp_eval_jvp")
         return out
@@ -539,44 +542,42 @@ class Problem:
         workspace; bitwise the same result).  out: optional (gA, gB, gamma)
         contiguous float64 tensors of n * n, n * m and n elements on the
         problem's device, written in place and returned."""
-        torch = _torch()
         n, m = self.n, self.m
-        zp = self._dev(z, self.sizes["nvar"], torch.float64, "z")
-        yp = self._dev(y, self.sizes["ncon"], torch.float64, "y")
+        zp = self._dev(z, self.sizes["nvar"], _float64, "z")
+        yp = self._dev(y, self.sizes["ncon"], _float64, "y")
         if out is None:
-            f64 = dict(dtype=torch.float64, device=self.device)
-            gA, gB, gg = torch.empty(n, n, **f64), torch.empty(n, m, **f64), torch.empty(n, **f64)
+            f64 = dict(dtype=_float64, device=self.device)
+            gA, gB, gg = _torch_mod.empty(n, n, **f64), _torch_mod.empty(n, m, **f64), _torch_mod.empty(n, **f64)
         else:
             gA, gB, gg = out
-            self._dev(gA, n * n, torch.float64, "out[0]")
-            self._dev(gB, n * m, torch.float64, "out[1]")
-            self._dev(gg, n, torch.float64, "out[2]")
+            self._dev(gA, n * n, _float64, "out[0]")
+            self._dev(gB, n * m, _float64, "out[1]")
+            self._dev(gg, n, _float64, "out[2]")
         fn = "ocp_eval_coef_grad_noalloc" if noalloc else "ocp_eval_coef_grad"
-        _check(getattr(lib(), fn)(self._h, zp, yp, ctypes.c_void_p(gA.data_ptr()),
-                                  ctypes.c_void_p(gB.data_ptr()) if m else None,
-                                  ctypes.c_void_p(gg.data_ptr()), self._stream()), fn)
+        _check(getattr(lib(), fn)(self._h, zp, yp, gA.data_ptr(),
+                                  gB.data_ptr() if m else None,
+                                  gg.data_ptr(), self._stream()), fn)
         return gA, gB, gg
 
     def coef_mixed(self, z, y, v, out=None):
         """The derivative of coef_grad(z, y) along the direction v of z (nvar
         doubles): d/d(A, B, gamma) of v^T grad_z L, as (n, n), (n, m) and (n,)
         device tensors (or written into out, as for coef_grad)."""
-        torch = _torch()
         n, m = self.n, self.m
-        zp = self._dev(z, self.sizes["nvar"], torch.float64, "z")
-        yp = self._dev(y, self.sizes["ncon"], torch.float64, "y")
-        vp_ = self._dev(v, self.sizes["nvar"], torch.float64, "v")
+        zp = self._dev(z, self.sizes["nvar"], _float64, "z")
+        yp = self._dev(y, self.sizes["ncon"], _float64, "y")
+        vp_ = self._dev(v, self.sizes["nvar"], _float64, "v")
         if out is None:
-            f64 = dict(dtype=torch.float64, device=self.device)
-            gA, gB, gg = torch.empty(n, n, **f64), torch.empty(n, m, **f64), torch.empty(n, **f64)
+            f64 = dict(dtype=_float64, device=self.device)
+            gA, gB, gg = _torch_mod.empty(n, n, **f64), _torch_mod.empty(n, m, **f64), _torch_mod.empty(n, **f64)
         else:
             gA, gB, gg = out
-            self._dev(gA, n * n, torch.float64, "out[0]")
-            self._dev(gB, n * m, torch.float64, "out[1]")
-            self._dev(gg, n, torch.float64, "out[2]")
-        _check(lib().ocp_eval_coef_mixed(self._h, zp, yp, vp_, ctypes.c_void_p(gA.data_ptr()),
-                                          ctypes.c_void_p(gB.data_ptr()) if m else None,
-                                          ctypes.c_void_p(gg.data_ptr()), self._stream()),
+            self._dev(gA, n * n, _float64, "out[0]")
+            self._dev(gB, n * m, _float64, "out[1]")
+            self._dev(gg, n, _float64, "out[2]")
+        _check(lib().ocp_eval_coef_mixed(self._h, zp, yp, vp_, gA.data_ptr(),
+                                          gB.data_ptr() if m else None,
+                                          gg.data_ptr(), self._stream()),
                "ocp_eval_coef_mixed")
         return gA, gB, gg
 
@@ -585,13 +586,12 @@ class Problem:
         gL times (grad_z L, c(z), (dL/dA, dL/dB, dL/dgamma)), gL being a
         one-element float64 device tensor (the incoming gradient); an output
         not wanted is None."""
-        torch = _torch()
         n, m = self.n, self.m
         if not (want_z or want_y or want_coef):
             raise ValueError("lagrangian_backward: no output is wanted")
-        zp = self._dev(z, self.sizes["nvar"], torch.float64, "z")
-        yp = self._dev(y, self.sizes["ncon"], torch.float64, "y")
-        gp = self._dev(gL, 1, torch.float64, "gL")
+        zp = self._dev(z, self.sizes["nvar"], _float64, "z")
+        yp = self._dev(y, self.sizes["ncon"], _float64, "y")
+        gp = self._dev(gL, 1, _float64, "gL")
         gz = gy = coef = None
         zo = yo = ap = bp = cp = None
         if want_z:
@@ -599,10 +599,10 @@ class Problem:
         if want_y:
             gy, yo = self._out(None, self.sizes["ncon"], "gy")
         if want_coef:
-            f64 = dict(dtype=torch.float64, device=self.device)
-            coef = (torch.empty(n, n, **f64), torch.empty(n, m, **f64), torch.empty(n, **f64))
-            ap, cp = ctypes.c_void_p(coef[0].data_ptr()), ctypes.c_void_p(coef[2].data_ptr())
-            bp = ctypes.c_void_p(coef[1].data_ptr()) if m else None
+            f64 = dict(dtype=_float64, device=self.device)
+            coef = (_torch_mod.empty(n, n, **f64), _torch_mod.empty(n, m, **f64), _torch_mod.empty(n, **f64))
+            ap, cp = coef[0].data_ptr(), coef[2].data_ptr()
+            bp = coef[1].data_ptr() if m else None
         _check(lib().ocp_eval_lagrangian_backward(self._h, zp, yp, float(sigma), gp, zo, yo, ap, bp, cp,
                                                   self._stream()), "ocp_eval_lagrangian_backward")
         return gz, gy, coef
@@ -613,15 +613,14 @@ class Problem:
         tA . dL/dA + tB . dL/dB + tgamma . dL/dgamma in z (nvar doubles) and
         in y (ncon doubles), as (gz, gy); an output not wanted is None.  The
         handle's coefficients are neither read nor changed."""
-        torch = _torch()
         n, m = self.n, self.m
         if not (want_z or want_y):
             raise ValueError("coef_adjoint: neither output is wanted")
-        zp = self._dev(z, self.sizes["nvar"], torch.float64, "z")
-        yp = self._dev(y, self.sizes["ncon"], torch.float64, "y")
-        ap = self._dev(tA, n * n, torch.float64, "tA")
-        bp = self._dev(tB, n * m, torch.float64, "tB") if m else None
-        gp = self._dev(tgamma, n, torch.float64, "tgamma")
+        zp = self._dev(z, self.sizes["nvar"], _float64, "z")
+        yp = self._dev(y, self.sizes["ncon"], _float64, "y")
+        ap = self._dev(tA, n * n, _float64, "tA")
+        bp = self._dev(tB, n * m, _float64, "tB") if m else None
+        gp = self._dev(tgamma, n, _float64, "tgamma")
         gz = gy = None
         zo = yo = None
         if want_z:
@@ -645,6 +644,7 @@ class QuadrotorProblem(Problem):
         self.boundary = int(boundary)
         self.device = torch.device("cuda", torch.cuda.current_device() if device is None
                                    else torch.device(device).index or 0)
+        self._index = self.device.index
         h = ctypes.c_void_p()
         with torch.cuda.device(self.device):
             _check(lib().ocp_quad_create(self.N, self.boundary, float(g), float(r), ctypes.byref(h)),
@@ -716,6 +716,7 @@ class Batch:
         self.Ns = Ns
         self.device = torch.device("cuda", torch.cuda.current_device() if device is None
                                    else torch.device(device).index or 0)
+        self._index = self.device.index
         c = self.count
         f64 = lambda a, shape: np.ascontiguousarray(np.asarray(a, np.float64).reshape(shape))
         A = f64(A, (c, n, n))
@@ -732,6 +733,7 @@ class Batch:
         _check(lib().ocp_batch_offsets(self._h, *(_hp(o) for o in offs[:4])), "ocp_batch_offsets")
         _check(lib().ocp_batch_offsets_ex(self._h, _hp(offs[4]), _hp(offs[5])), "ocp_batch_offsets_ex")
         self.offsets = dict(zip(("z", "c", "jac", "hess", "kkt", "dim"), offs))
+        self._totals = {k: int(v[-1]) for k, v in self.offsets.items()}
         self.tuning = None  # the autotuner's table of (shape, ms), once tuned
 
     @classmethod
@@ -766,16 +768,16 @@ class Batch:
 
     def _args(self, z, y, jac, hess, what):
         torch = _torch()
-        tot = {k: int(v[-1]) for k, v in self.offsets.items()}
+        tot = self._totals
         chk = self._dev  # the same tensor checks as a single problem
-        zp = chk(z, tot["z"], torch.float64, "z")
-        yp = chk(y, tot["c"], torch.float64, "y") if (what & EVAL_HESS) else None
+        zp = chk(z, tot["z"], _float64, "z")
+        yp = chk(y, tot["c"], _float64, "y") if (what & EVAL_HESS) else None
         if (what & EVAL_JAC) and jac is None:
             jac = torch.empty(tot["jac"], dtype=torch.float64, device=self.device)
         if (what & EVAL_HESS) and hess is None:
             hess = torch.empty(tot["hess"], dtype=torch.float64, device=self.device)
-        jp = chk(jac, tot["jac"], torch.float64, "jac") if (what & EVAL_JAC) else None
-        hp = chk(hess, tot["hess"], torch.float64, "hess") if (what & EVAL_HESS) else None
+        jp = chk(jac, tot["jac"], _float64, "jac") if (what & EVAL_JAC) else None
+        hp = chk(hess, tot["hess"], _float64, "hess") if (what & EVAL_HESS) else None
         return zp, yp, jp, hp, jac, hess
 
     _dev = Problem._dev
@@ -808,14 +810,14 @@ class Batch:
         """The BatchIO of one step and the output tensors (allocated where
         `out` lacks them; None for parts not requested)."""
         torch = _torch()
-        tot = {k: int(v[-1]) for k, v in self.offsets.items()}
+        tot = self._totals
         chk = self._dev
         io = BatchIO()
-        io.z = chk(z, tot["z"], torch.float64, "z")
+        io.z = chk(z, tot["z"], _float64, "z")
         if what & (EVAL_HESS | EVAL_KKT) or y is not None:
-            io.y = chk(y, tot["c"], torch.float64, "y") if y is not None else None
+            io.y = chk(y, tot["c"], _float64, "y") if y is not None else None
         if reg is not None:
-            io.reg = chk(reg, tot["dim"], torch.float64, "reg")
+            io.reg = chk(reg, tot["dim"], _float64, "reg")
         io.sigma = float(sigma)
         out = dict(out or {})
         res = {}
@@ -827,7 +829,7 @@ class Batch:
             t = out.get(name)
             if t is None:
                 t = torch.empty(size, dtype=torch.float64, device=self.device)
-            setattr(io, name, chk(t, size, torch.float64, name))
+            setattr(io, name, chk(t, size, _float64, name))
             res[name] = t
         return io, res
 

@@ -44,7 +44,7 @@ def _coefficients(prob, A, B, gamma, key=None):
     current = getattr(prob, "_coef_key", None)
     if getattr(prob, "_coef_uploaded", False) or (key is not None and current is key):
         return current
-    prob.set_coefficients(A.detach(), B.detach(), gamma.detach())
+    prob.set_coefficients(A, B, gamma)
     prob._coef_key = key = object()
     return key
 
@@ -140,7 +140,8 @@ class _Lagrangian(torch.autograd.Function):
         ctx.coef_key = _coefficients(prob, A, B, gamma)
         ctx.save_for_backward(z, y, A, B, gamma)
         ctx.sigma, ctx.prob = sigma, prob
-        return prob.lagrangian(z.detach().contiguous(), y.detach().contiguous(), sigma)[0]
+        # a Function's forward runs without grad mode: nothing to detach
+        return prob.lagrangian(z.contiguous(), y.contiguous(), sigma, out=z.new_empty(()))
 
     @staticmethod
     def backward(ctx, gL):
@@ -158,8 +159,8 @@ class _Lagrangian(torch.autograd.Function):
             want_coef = any(ctx.needs_input_grad[2:5])
             if not (want_z or want_y or want_coef):
                 return gz, gy, gA, gB, gg, None, None
-            gz, gy, coef = prob.lagrangian_backward(z.detach().contiguous(), y.detach().contiguous(), sigma,
-                                                    gL.detach().contiguous(), want_z, want_y, want_coef)
+            gz, gy, coef = prob.lagrangian_backward(z.contiguous(), y.contiguous(), sigma, gL.contiguous(), want_z,
+                                                    want_y, want_coef)
             if coef is not None:
                 gA, gB, gg = coef
             return gz, gy, gA, gB, gg, None, None
