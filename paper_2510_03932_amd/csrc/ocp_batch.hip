@@ -9,10 +9,10 @@
 // w, w + G, w + 2G, ... (G = grid size), so every wave reaches the end of the
 // list and exits, and the assignment is fixed (no queue).  A tile is
 // (instance, first interval or node, kind): a Jacobian column over `block`
-// intervals (or 2 `block` - 16 stored in whole lines), a Hessian, gradient or variable-row KKT run of
-// `block` nodes, a defect run of 63 intervals per wavefront, an objective
-// group of 256 nodes, a defect-row KKT run of 16-64 intervals, or an instance's
-// boundary rows.  One list per evaluation mask, instance-major (an instance's
+// intervals (or 2 `block` - 16 stored in whole lines), a Hessian or
+// variable-row KKT run of `block` nodes, a defect run of 63 intervals per
+// wavefront, the objective and gradient of 256 nodes, a defect-row KKT run of
+// 16-64 intervals, or an instance's boundary rows.  One list per evaluation mask, instance-major (an instance's
 // tiles together, so the workgroups in flight share the state rows they read).
 // The per-lane arithmetic is the single-instance path's (ocp_device.h,
 // ocp_step_device.h): the values are bitwise those of per-instance
@@ -63,7 +63,7 @@ struct InstDesc {
     double h, hh;
 };
 
-enum TileKind : int16_t { kJac = 0, kHess, kCons, kGrad, kObj, kKktDef, kKktVar, kBnd };
+enum TileKind : int16_t { kJac = 0, kHess, kCons, kObjGrad, kKktDef, kKktVar, kBnd };
 
 // One unit of work of the persistent kernel.
 struct TileDesc {
@@ -184,27 +184,20 @@ __global__ __launch_bounds__(BS, KINDS == kListKktDef ? 7 : KINDS == OCP_EVAL_JA
             }
             break;
         }
-        case kGrad: {
-            if (!(KINDS & OCP_EVAL_GRAD)) break;
-            const int64_t k = td.k0 + (int64_t)tid;
-            if (k <= P.N) {
-                double *gb = grad_ + id.z_off;
-                for (int c = 0; c < P.n + P.m; c++)
-                    if (c < P.n || k < P.NU) grad_entry(P, zb, gb, c, k);
-            }
-            break;
-        }
-        case kObj: {
-            if (!(KINDS & OCP_EVAL_OBJ)) break;
+        case kObjGrad: {
+            if (!(KINDS & (OCP_EVAL_OBJ | OCP_EVAL_GRAD))) break;
+            double *gb = what & OCP_EVAL_GRAD ? grad_ + id.z_off : nullptr;
             double v[256 / BS];
 #pragma unroll
             for (int r = 0; r < 256 / BS; r++) {
                 const int64_t k = td.k0 + tid + r * BS;
-                v[r] = k < P.N1 ? obj_node<NB>(P, zb, k) : 0.0;
+                v[r] = k < P.N1 ? obj_grad_node<NB>(P, zb, gb, k) : 0.0;
             }
-            const double s = sum256<BS>(v, ws);
-            if (tid == 0) parts_[id.part0 + td.k0 / kObjTile] = s;
-            __syncthreads();  // ws is reused by the next tile
+            if (what & OCP_EVAL_OBJ) {
+                const double s = sum256<BS>(v, ws);
+                if (tid == 0) parts_[id.part0 + td.k0 / kObjTile] = s;
+                __syncthreads();  // ws is reused by the next tile
+            }
             break;
         }
         case kKktDef:
@@ -321,10 +314,8 @@ static std::vector<TileDesc> build_tiles(const ocp_batch &b, const ocp_batch_con
             const int64_t span = euler ? c.block : 63 * (c.block / 64);  // 63 intervals per wavefront
             for (int64_t k0 = 0; k0 < N; k0 += span) put(k0, kCons, 1, 0);
         }
-        if (what & OCP_EVAL_GRAD)
-            for (int64_t k0 = 0; k0 <= N; k0 += c.block) put(k0, kGrad, 1, 0);
-        if (what & OCP_EVAL_OBJ)
-            for (int64_t k0 = 0; k0 <= N; k0 += kObjTile) put(k0, kObj, 1, 0);
+        if (what & (OCP_EVAL_OBJ | OCP_EVAL_GRAD))
+            for (int64_t k0 = 0; k0 <= N; k0 += kObjTile) put(k0, kObjGrad, 1, 0);
         if (what & (OCP_EVAL_KKT | kListKktDef))
             for (int64_t k0 = 0; k0 < N; k0 += (int64_t)1 << b.bp.defect_lg) put(k0, kKktDef, 1, 0);
         if (what & (OCP_EVAL_KKT | kListKktVar))

@@ -240,3 +240,35 @@ def test_scaled_backward_bits(ocp, quad, bnd):
     if not quad:
         assert all(same(a, b * g) for a, b in zip(coef, prob.coef_grad(z, y)))
     prob.close()
+
+
+# the gradient's workgroups take 256 nodes of whole lines of a row; batched
+# tiles take the objective's 256 nodes and the gradient from one load, more
+# controls than the state bound in groups
+@pytest.mark.parametrize("N,n,m,scheme,offset", [(255, 3, 1, 0, 1), (256, 4, 2, 1, 0), (241, 2, 7, 0, 15),
+                                                 (240, 4, 9, 1, 8), (511, 8, 4, 0, 3), (497, 5, 0, 0, 7),
+                                                 (1, 1, 1, 1, 2), (14, 1, 0, 0, 9)])
+def test_gradient_lines(ocp, N, n, m, scheme, offset):
+    print(f"[lines] gradient N={N} n={n} m={m} scheme={scheme} offset={offset}", flush=True)
+    insts = synth.make_batch(3, n, m, seed=76, Ns=[N, N + 1, max(1, N - 1)], scheme=scheme)
+    want, mu = oracle.grad_ex(insts[0], scheme, 0)
+    prob = ocp.Problem.from_instance(insts[0], torch.device("cuda", 0))
+    out = Guarded(prob.sizes["nvar"], offset)
+    prob.grad(_t(insts[0].z), out=out.out)
+    check_close(out.values(), want, mu, what="grad")
+    prob.close()
+    batch = ocp.Batch.from_instances(insts, scheme=scheme)
+    z = _t(synth.pack(insts)[0])
+    both = ocp.EVAL_OBJ | ocp.EVAL_GRAD
+    ref = batch.step(z, what=both, mode="per_instance")
+    for block in (128, 256):
+        for wgs in (0, 1):
+            batch.config = {"block": block, "pair": 1, "wgs_per_cu": wgs, "order": 1}
+            for what in (both, ocp.EVAL_OBJ, ocp.EVAL_GRAD):
+                g = Guarded(int(batch.offsets["z"][-1]), offset)
+                got = batch.step(z, what=what, out={"grad": g.out})
+                if what & ocp.EVAL_OBJ:
+                    assert torch.equal(got["obj"].view(torch.int64), ref["obj"].view(torch.int64))
+                if what & ocp.EVAL_GRAD:
+                    assert np.array_equal(g.values().view(np.uint64), ref["grad"].cpu().numpy().view(np.uint64))
+    batch.close()
