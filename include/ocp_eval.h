@@ -522,7 +522,8 @@ typedef struct ocp_batch_config {
     int32_t pair;         /* 1: Jacobian lanes take two intervals, stored in whole 128-byte
                              lines, for instances whose slot rows do not all begin on one; 0: one */
     int32_t wgs_per_cu;   /* persistent workgroups per compute unit, 1..32; 0: one
-                             workgroup per tile (the loop over tiles runs once) */
+                             workgroup per tile (the loop over tiles runs once; the
+                             defect tiles loop, 16 workgroups per unit) */
     int32_t order;        /* tile order within an instance: 0 node range major (all columns
                              of a node range together), 1 column major (a column's node
                              ranges together) */

@@ -48,6 +48,7 @@ using namespace ocp::dev;
 
 namespace {
 
+constexpr int kConsWgsPerCu = 16;  // looping workgroups per CU of the defect tiles under the default grid
 constexpr int kObjTile = 256;  // nodes per objective tile (the single-instance workgroup)
 constexpr int kMasks = 256;    // tile-list keys: evaluation masks 1 .. OCP_EVAL_ALL and the two KKT keys below
 // Tile-list keys of the two KKT groups (outside the OCP_EVAL_* bits): the
@@ -144,9 +145,10 @@ __global__ __launch_bounds__(BS, KINDS == kListKktDef ? 7 : KINDS == OCP_EVAL_JA
     __shared__ double ws[4];          // objective sums
     const int tid = threadIdx.x;
     for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        // the KKT tiles of an instance share lines with their neighbours, so
-        // each XCD takes a contiguous run of them (see xcd_order)
-        const TileDesc td = tiles[KINDS & (kListKktDef | kListKktVar) ? xcd_order(t, ntiles) : t];
+        // the KKT and defect tiles of an instance share lines with their
+        // neighbours, so each XCD takes a contiguous run of them (see xcd_order)
+        constexpr bool kRuns = (KINDS & (kListKktDef | kListKktVar | OCP_EVAL_CONS)) != 0;
+        const TileDesc td = tiles[kRuns ? xcd_order(t, ntiles) : t];
         const InstDesc id = inst[td.b];
         const KP P = make_kp<SCHEME>(bp, id, td.b);
         const double *zb = z_ + id.z_off;
@@ -419,7 +421,13 @@ template <int BS, int KINDS, int SCHEME>
 static void launch_batch_scheme(const ocp_batch *b, const TileDesc *tiles, int ntiles, int what, const BIO &io,
                                 hipStream_t s)
 {
-    const int cap = b->cfg.wgs_per_cu > 0 ? b->cus * b->cfg.wgs_per_cu : ntiles;
+    // One workgroup per tile by default, except for the defects: their tiles
+    // are short (252 intervals) and wait on their descriptors, so 16 looping
+    // workgroups per CU take 174 us where one per tile takes 190 (198 without
+    // the XCD runs; 512 instances, n = 6, m = 3).  The other kinds measured
+    // slower looping (defect-row KKT 1.16-1.21 against 1.10 ms).
+    const int cap = b->cfg.wgs_per_cu > 0 ? b->cus * b->cfg.wgs_per_cu
+                    : KINDS == OCP_EVAL_CONS ? b->cus * kConsWgsPerCu : ntiles;
     const unsigned grid = (unsigned)std::max(1, std::min(ntiles, cap));
     const size_t lds = ((KINDS & kListKktDef) && (what & OCP_EVAL_KKT))
                            ? kkt_defect_lds(b->n, b->m, b->shape.T, 1 << b->bp.defect_lg) * sizeof(double)
