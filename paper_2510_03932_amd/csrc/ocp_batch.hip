@@ -18,9 +18,8 @@
 // ocp_step_device.h): the values are bitwise those of per-instance
 // evaluation, for any tile shape.
 //
-// The evaluations fall into three groups, each with a kernel instantiation of
-// its own register footprint: Jacobian and Hessian values; objective,
-// gradient and defects; the fused KKT values.  A mask that spans several
+// The evaluations fall into six groups (see kGroupKinds), each with a kernel
+// instantiation of its own register footprint.  A mask that spans several
 // groups is one persistent launch per group, back to back on the stream.
 //
 // The objective of instance b is a fixed-order sum: each objective tile sums

@@ -383,13 +383,14 @@ __device__ __forceinline__ void hess_node(const KP &P, const double *__restrict_
 // Dynamics at node k <= N: the node's states x[i] = X_ik and F_i(k) for every
 // i < n (NB >= n, entries beyond n are zero).  F_i sums j ascending, then l
 // ascending, then the bilinear term.  dyn_load loads the states of node k and
-// the first MB controls of node ku, before any arithmetic; dyn_eval computes F
+// the first MB controls of node ku, before any arithmetic, and clears F;
+// dyn_eval adds the dynamics into F
 // (further controls, when m > MB, loaded there); a caller that knows
 // m <= MB < NB saves the registers of NB - MB controls.
 // ---------------------------------------------------------------------------
 template <int NB, int MB>
 __device__ __forceinline__ void dyn_load(const KP &P, const double *__restrict__ z, int64_t k, int64_t ku,
-                                         double (&x)[NB], double (&u)[MB])
+                                         double (&x)[NB], double (&u)[MB], double (&F)[NB])
 {
     static_assert(MB <= NB, "the control bound is at most the state bound");
     const double *U = z + (int64_t)P.n * P.N1;
@@ -397,6 +398,7 @@ __device__ __forceinline__ void dyn_load(const KP &P, const double *__restrict__
     for (int i = 0; i < NB; i++) {
         x[i] = (i < P.n) ? z[i * (int64_t)P.N1 + k] : 0.0;
         if (i < MB) u[i] = (i < P.m) ? U[(int64_t)i * P.NU + ku] : 0.0;
+        F[i] = 0.0;
     }
 }
 
@@ -406,8 +408,6 @@ __device__ __forceinline__ void dyn_eval(const KP &P, const double *__restrict__
 {
     const int n = P.n, m = P.m;
     const double *U = z + (int64_t)n * P.N1;
-#pragma unroll
-    for (int i = 0; i < NB; i++) F[i] = 0.0;
 #pragma unroll
     for (int j = 0; j < NB; j++) {
         if (j < n) {
@@ -445,7 +445,7 @@ __device__ __forceinline__ void dyn_node(const KP &P, const double *__restrict__
                                          double (&x)[NB], double (&F)[NB])
 {
     double u[MB];
-    dyn_load<NB, MB>(P, z, k, k, x, u);
+    dyn_load<NB, MB>(P, z, k, k, x, u, F);
     dyn_eval<NB, MB>(P, z, k, x, u, F);
 }
 

@@ -88,7 +88,7 @@ __device__ __forceinline__ void lag_chunk(const KP &P, const double *__restrict_
     const int64_t ky = min(k, N - 1), ku = min(k, NU - 1);
 #pragma unroll
     for (int i = 0; i < NB; i++) yv[i] = y[(int64_t)(i < n ? i : 0) * N + ky];
-    dyn_load<NB, MB>(P, z, min(k, N), ku, x, u);
+    dyn_load<NB, MB>(P, z, min(k, N), ku, x, u, F);
     dyn_eval<NB, MB>(P, z, ku, x, u, F);
 #pragma unroll
     for (int i = 0; i < NB; i++) {

@@ -262,13 +262,18 @@ inline size_t kkt_defect_lds(int n, int m, int T, int KT)
 // and 0.43 at N = 2e6), n = 12, m = 5 (0.232 against 0.237 and 0.237 at
 // N = 333,333) and n = 16, m = 8 (1.09 against 1.10 and 1.10 at N = 1e6): its
 // row blocks are long, so few of their lines are stored in part.  Short
-// problems take smaller tiles to reach every CU.
+// problems take smaller tiles to reach every CU.  Forward Euler (T < 2(n+m):
+// one entry per column) stores half as much per cosine and per barrier and
+// needs more workgroups per CU to hide them, so its tile gets half the LDS:
+// at N = 1e6 and n = 16, m = 8, 32 intervals (22 KB) 0.719 ms, 64 (41 KB)
+// 0.885 and 16 0.861; at n = 12, m = 6, 64 (31 KB) 0.460, 32 0.492; at
+// n = 10, m = 4, 64 (25 KB) 0.376, 32 0.399, 16 0.466.
 constexpr int64_t kDefectTiles = 1024;  // 4 workgroups for each of the 256 CUs
 inline int kkt_defect_kt(int n, int m, int T, int64_t intervals)
 {
+    const size_t lds = T < 2 * (n + m) ? kDefectLdsMax / 2 : kDefectLdsMax;
     int KT = kDefectKTMax;
-    while (KT > 16 && (intervals < kDefectTiles * KT || kkt_defect_lds(n, m, T, KT) * sizeof(double) > kDefectLdsMax))
-        KT /= 2;
+    while (KT > 16 && (intervals < kDefectTiles * KT || kkt_defect_lds(n, m, T, KT) * sizeof(double) > lds)) KT /= 2;
     return KT;
 }
 
