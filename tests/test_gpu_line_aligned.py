@@ -49,9 +49,11 @@ class Guarded:
 
 
 # the fused KKT call's defect rows take tiles of 64 intervals from N = 65,536
-# (n = 20, m = 10: 32, the LDS bound), 32 from 32,768, else 16
+# (n = 20, m = 10: 32, the LDS bound; forward Euler n = 13 is the last of its
+# half bound at m = 3, n = 14 takes 32), 32 from 32,768, else 16
 @pytest.mark.parametrize("N,n,m,scheme,bnd,offset", [
     (65536, 3, 1, 0, 0, 1), (65573, 2, 1, 0, 2, 15), (65599, 3, 2, 1, 1, 8), (65541, 20, 10, 0, 0, 3),
+    (65541, 13, 3, 1, 0, 1), (65541, 14, 3, 1, 2, 6),
     (32768, 4, 0, 0, 1, 9), (32799, 3, 1, 1, 2, 0), (32767, 5, 2, 0, 0, 7), (17, 3, 1, 0, 0, 5), (1, 1, 1, 1, 2, 2)])
 def test_fused_kkt_tiles(ocp, N, n, m, scheme, bnd, offset):
     print(f"[lines] fused N={N} n={n} m={m} scheme={scheme} bnd={bnd} offset={offset}", flush=True)
