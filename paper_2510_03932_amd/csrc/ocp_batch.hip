@@ -160,7 +160,7 @@ __global__ __launch_bounds__(BS, KINDS == kListKktDef ? 7 : KINDS == OCP_EVAL_JA
                 __syncthreads();  // vbuf is reused by the next tile
             } else {
                 const int64_t k = td.k0 + (int64_t)tid;
-                if (k < P.N) jac_column(P, zb, jb, k, td.col);
+                if (k < P.N) jac_column<1, SCHEME != 0>(P, zb, jb, k, td.col);
             }
             break;
         }

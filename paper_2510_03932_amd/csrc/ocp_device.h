@@ -195,53 +195,68 @@ __device__ __forceinline__ double jac_entry(bool own, bool prev, double a, doubl
 #pragma clang fp contract(off)
     double v = a * c;
     if (own) v = __builtin_fma(a, c, __builtin_fma(gj, xn, id));
-    if (prev) v = __builtin_fma(gp, xp, v);
+    const double lo = gp * xp;
+    if (prev) v = lo + v;
     return v;
 }
 
-// One column at interval k < N, stored directly: the path of arrays whose slot
-// rows all begin on a 128-byte line, and of small problems (see launch_jac).
+// One column at NPT intervals k .. k + NPT - 1 < N, stored directly.  NPT = 2
+// stores a 16-byte pair per lane, so a wavefront's store is one contiguous KiB
+// of a slot row: it needs an even N and 16-byte aligned rows (see jac_path for
+// the choice).  The scheme is a template argument: with it read from P, the
+// smallest calls took up to 15 % longer (N = 17, n = 32).
+template <int NPT, bool EULER>
 __device__ __forceinline__ void jac_column(const KP &P, const double *__restrict__ z, double *__restrict__ jac,
                                            int64_t k, int col)
 {
+    constexpr int kNodes = EULER ? NPT : NPT + 1;
     const int n = P.n, m = P.m, T = P.T;
     const int64_t N = P.N, N1 = P.N1;
-    const bool euler = P.scheme != 0;
-    const double w = euler ? P.h : P.hh;
+    const double w = EULER ? P.h : P.hh;
+    auto put = [](double *o, const double (&v)[NPT]) {
+        if constexpr (NPT == 2) st_nt2(o, dbl2{v[0], v[1]});
+        else st_nt(o, v[0]);
+    };
+    double v[NPT];
     if (col < n) {
         const int j = col;
         const int jn = (j + 1 == n) ? 0 : j + 1;
         const int jp = (j == 0) ? n - 1 : j - 1;
         const double gj = -w * P.gam[j], gp = -w * P.gam[jp];
         const double *xj = z + j * N1 + k, *xn = z + jn * N1 + k, *xp = z + jp * N1 + k;
-        double cs[2], vn[2], vp[2];
+        double cs[kNodes], vn[kNodes], vp[kNodes];
 #pragma unroll
-        for (int u = 0; u < 2; u++) {
-            if (u == 0 || !euler) {
-                cs[u] = cos(xj[u]);
-                vn[u] = xn[u];
-                vp[u] = xp[u];
-            }
+        for (int u = 0; u < kNodes; u++) {
+            cs[u] = cos(xj[u]);
+            vn[u] = xn[u];
+            vp[u] = xp[u];
         }
         for (int i = 0; i < n; i++) {
             const double a = -w * P.A[i * n + j];
-            const double v0 = jac_entry(i == j, i == jp, a, cs[0], -1.0, gj, gp, vn[0], vp[0]);
-            if (euler) {
-                st_nt(jac + ((int64_t)i * T + (j <= i ? j : j + 1)) * N + k, v0);
-            } else {
-                double *o = jac + ((int64_t)i * T + 2 * j) * N + k;
-                st_nt(o, v0);
-                st_nt(o + N, jac_entry(i == j, i == jp, a, cs[1], 1.0, gj, gp, vn[1], vp[1]));
+            const bool own = i == j, prev = i == jp;
+            double v1[NPT];
+#pragma unroll
+            for (int u = 0; u < NPT; u++) {
+                v[u] = jac_entry(own, prev, a, cs[u], -1.0, gj, gp, vn[u], vp[u]);
+                if constexpr (!EULER) v1[u] = jac_entry(own, prev, a, cs[u + 1], 1.0, gj, gp, vn[u + 1], vp[u + 1]);
             }
+            double *o = jac + ((int64_t)i * T + (!EULER ? 2 * j : j <= i ? j : j + 1)) * N + k;
+            put(o, v);
+            if constexpr (!EULER) put(o + N, v1);
         }
-        if (euler) st_nt(jac + ((int64_t)j * T + j + 1) * N + k, 1.0);
+        if constexpr (EULER) {
+#pragma unroll
+            for (int u = 0; u < NPT; u++) v[u] = 1.0;
+            put(jac + ((int64_t)j * T + j + 1) * N + k, v);
+        }
     } else {
         const int l = col - n;
         for (int i = 0; i < n; i++) {
-            const double v = -w * P.B[i * m + l];
-            double *o = jac + ((int64_t)i * T + (euler ? n + 1 + l : 2 * (n + l))) * N + k;
-            st_nt(o, v);
-            if (!euler) st_nt(o + N, v);
+#pragma unroll
+            for (int u = 0; u < NPT; u++) v[u] = -w * P.B[i * m + l];
+            double *o = jac + ((int64_t)i * T + (EULER ? n + 1 + l : 2 * (n + l))) * N + k;
+            put(o, v);
+            if constexpr (!EULER) put(o + N, v);
         }
     }
 }
@@ -514,14 +529,9 @@ __device__ __forceinline__ void hess_node_euler(const KP &P, const double *__res
 }
 
 // Host-side launchers of the single-instance kernels (ocp_eval.hip,
-// ocp_fused.hip); the batched path uses them for its per-instance mode.
-// launch_obj's `partials` holds min(4096, ceil((N+1) / 256)) doubles.  Each covers the
-// problem's boundary rows too.
-// Jacobian outputs up to this many bytes (the 8 L2s of 4 MiB) are stored
-// directly: the caches merge the partial lines (see launch_jac).
-constexpr int64_t kJacSmall = 32 << 20;
-// The Jacobian's slot rows all begin on a 128-byte line.
-inline bool jac_rows_on_lines(int64_t N, const void *jac) { return N % kLine == 0 && (uintptr_t)jac % 128 == 0; }
+// ocp_fused.hip); the batched path uses them for its per-instance mode.  Each
+// covers the problem's boundary rows too.  launch_obj's `partials` holds
+// min(4096, ceil((N+1) / 256)) doubles.
 hipError_t launch_jac(const KP &P, const double *z, double *jac, hipStream_t stream);
 hipError_t launch_hess(const KP &P, const double *z, const double *y, double sigma, double *hv,
                        hipStream_t stream);

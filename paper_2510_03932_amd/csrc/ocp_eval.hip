@@ -14,6 +14,7 @@
 #include "ocp_device.h"
 #include "ocp_internal.h"
 #include "ocp_problem.h"
+#include "ocp_rules.h"
 #include "ocp_quad.h"
 #include "ocp_step_device.h"
 
@@ -24,10 +25,10 @@ namespace {
 
 // ---------------------------------------------------------------------------
 // Jacobian values.  2-D grid: blockIdx.y is the column (state j < n, control
-// n + l), blockIdx.x the tile: kBlock intervals, one per lane, stored directly
-// (jac_kernel), or lines_span(kBlock) intervals stored in whole lines
-// (jac_lines_kernel).  Many short workgroups keep the write stream at the
-// device's rate for slot rows, 5.5-5.8 TB/s; see launch_jac for the choice.
+// n + l), blockIdx.x the tile: kBlock lanes of one or two intervals each,
+// stored directly (jac_kernel), or lines_span(kBlock) intervals stored in whole
+// lines (jac_lines_kernel).  Many short workgroups keep the write stream at the
+// device's rate for slot rows, 5.5-5.8 TB/s.
 // ---------------------------------------------------------------------------
 // Boundary row b's single Jacobian entry (1.0), after the defect entries.  The
 // boundary rows (at most 2 OCP_MAX_DIM = 64) ride in the first workgroup of
@@ -40,11 +41,12 @@ __device__ __forceinline__ void bnd_jac(const KP &P, double *__restrict__ jac, i
     if (b < P.nb) jac[(int64_t)P.n * P.N * P.T + b] = 1.0;
 }
 
+template <int NPT, bool EULER>
 __global__ __launch_bounds__(kBlock) void jac_kernel(KP P, const double *__restrict__ z, double *__restrict__ jac)
 {
-    const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (k < P.N) jac_column(P, z, jac, k, blockIdx.y);
-    bnd_jac(P, jac, blockIdx.y == 0 ? k : P.nb);
+    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (t * NPT < P.N) jac_column<NPT, EULER>(P, z, jac, t * NPT, blockIdx.y);
+    bnd_jac(P, jac, blockIdx.y == 0 ? t : P.nb);
 }
 
 __global__ __launch_bounds__(kBlock) void jac_lines_kernel(KP P, const double *__restrict__ z,
@@ -341,23 +343,26 @@ __global__ __launch_bounds__(kBlock) void assemble_kernel(
 namespace ocp {
 namespace dev {
 
-// Slot rows that begin on lines are stored directly, one interval per lane
-// (N = 1e6, n = 16, m = 8: 1.09 ms against 1.11 from LDS, and against 1.11 for
-// two intervals and a 16-byte store per lane); all others in whole lines from
-// LDS (N = 200,001, n = 16, m = 8, Euler: 203 -> 117 us; N = 333,333, n = 12,
-// m = 5: 370 -> 203 us), except outputs up to kJacSmall, the size of the L2s,
-// which merge the partial lines: there LDS and its barrier cost more (n = 8,
-// m = 4, directly against in lines: 31 MB 8.7 and 9.8 us, 61 MB 19.0 and 12.6;
-// N = 1000, n = 4, m = 2: 3.5 and 4.9).
+// The three ways to store the slot rows; rules::jac_path says which and why.
+static_assert(rules::kLineDoubles == kLine && rules::kJacLinesSpan == lines_span(kBlock), "jac_path's tiles");
 hipError_t launch_jac(const KP &P, const double *z, double *jac, hipStream_t stream)
 {
     const unsigned cols = (unsigned)(P.n + P.m);
-    const int64_t bytes = (int64_t)P.n * P.N * P.T * (int64_t)sizeof(double);
-    if (jac_rows_on_lines(P.N, jac) || bytes <= kJacSmall)
-        hipLaunchKernelGGL(jac_kernel, dim3(blocks_for(P.N, kBlock), cols), dim3(kBlock), 0, stream, P, z, jac);
-    else
+    const bool euler = P.scheme != 0;
+    const dim3 g1(blocks_for(P.N, kBlock), cols), g2(blocks_for(P.N / 2, kBlock), cols);
+    switch (rules::jac_path(P.N, P.n, P.m, P.T, euler, (uintptr_t)jac)) {
+    case rules::kJacLines:
         hipLaunchKernelGGL(jac_lines_kernel, dim3(blocks_for((int64_t)P.N + kHalo, lines_span(kBlock)), cols),
                            dim3(kBlock), 0, stream, P, z, jac);
+        break;
+    case rules::kJacPair:
+        if (euler) hipLaunchKernelGGL((jac_kernel<2, true>), g2, dim3(kBlock), 0, stream, P, z, jac);
+        else hipLaunchKernelGGL((jac_kernel<2, false>), g2, dim3(kBlock), 0, stream, P, z, jac);
+        break;
+    default:
+        if (euler) hipLaunchKernelGGL((jac_kernel<1, true>), g1, dim3(kBlock), 0, stream, P, z, jac);
+        else hipLaunchKernelGGL((jac_kernel<1, false>), g1, dim3(kBlock), 0, stream, P, z, jac);
+    }
     return hipGetLastError();
 }
 

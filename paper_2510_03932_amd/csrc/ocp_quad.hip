@@ -16,6 +16,7 @@
 #include "ocp_problem.h"
 #include "ocp_quad.h"
 #include "ocp_quad_device.h"
+#include "ocp_rules.h"
 
 using namespace ocp;
 using namespace ocp::dev;
@@ -46,8 +47,8 @@ __device__ __forceinline__ void load_att(const QP &P, const double *__restrict__
 // Jacobian values.  2-D grid: blockIdx.y is the defect row i, blockIdx.x the
 // tile.  Row i's 2 kSupLen[i] slots are unit-stride runs across lanes.  Rows 1,
 // 3, 5, 6, 7, 8 need the attitude trigonometry of a node; rows 0, 2, 4 are
-// constants.  quad_jac_kernel stores one interval per lane directly (two
-// nodes' trigonometry each): the path of outputs that fit the L2s.
+// constants.  quad_jac_kernel stores one or two intervals per lane directly (NPT
+// + 1 nodes' trigonometry each): the path of short grids (rules::quad_jac_path).
 // quad_jac_lines_kernel takes tiles of lines_span(kBlock) intervals, evaluates
 // each node's partials once into LDS and stores every slot row in whole lines
 // (see store_row_lines): 32 -> 20 us at N = 200,001 (5.9 TB/s written), 23 ->
@@ -63,15 +64,15 @@ __device__ __forceinline__ double jac_id(int i, int p, int s)
     return pair_is_own_state(i, p) ? (s ? 1.0 : -1.0) : 0.0;
 }
 
-template <int I>
+template <int I, int NPT>
 __device__ __forceinline__ void jac_row(const QP &P, const double *__restrict__ z, double *__restrict__ jac,
                                         int64_t k)
 {
-    Trig t[2] = {};
-    double u[2][4] = {};
+    Trig t[NPT + 1] = {};
+    double u[NPT + 1][4] = {};
     if constexpr (kRowHasTrig<I>) {
 #pragma unroll
-        for (int j = 0; j < 2; j++) {
+        for (int j = 0; j <= NPT; j++) {
             double a[3];
             load_att(P, z, k + j, a, u[j]);
             t[j] = node_trig(a[0], a[1], a[2]);
@@ -80,9 +81,15 @@ __device__ __forceinline__ void jac_row(const QP &P, const double *__restrict__ 
 #pragma unroll
     for (int p = 0; p < kSupLen[I]; p++)
 #pragma unroll
-        for (int s = 0; s < 2; s++)
-            st_nt(jac + (int64_t)(kRowSlot[I] + 2 * p + s) * P.N + k,
-                  __builtin_fma(-P.hh, partial(pair_index(I, p), t[s], u[s]), jac_id(I, p, s)));
+        for (int s = 0; s < 2; s++) {
+            double v[NPT];
+#pragma unroll
+            for (int j = 0; j < NPT; j++)
+                v[j] = __builtin_fma(-P.hh, partial(pair_index(I, p), t[j + s], u[j + s]), jac_id(I, p, s));
+            double *o = jac + (int64_t)(kRowSlot[I] + 2 * p + s) * P.N + k;
+            if constexpr (NPT == 2) st_nt2(o, dbl2{v[0], v[1]});
+            else st_nt(o, v[0]);
+        }
 }
 
 template <int I>
@@ -134,22 +141,23 @@ __device__ __forceinline__ double bnd_state(const QP &P, const double *__restric
     return z[(int64_t)(b % kStates) * P.N1 + (b < kStates ? 0 : P.N)];
 }
 
+template <int NPT>
 __global__ __launch_bounds__(kBlock) void quad_jac_kernel(QP P, const double *__restrict__ z,
                                                           double *__restrict__ jac)
 {
-    const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x, k = t * NPT;
     if (k < P.N) switch (blockIdx.y) {
-    case 0: jac_row<0>(P, z, jac, k); break;
-    case 1: jac_row<1>(P, z, jac, k); break;
-    case 2: jac_row<2>(P, z, jac, k); break;
-    case 3: jac_row<3>(P, z, jac, k); break;
-    case 4: jac_row<4>(P, z, jac, k); break;
-    case 5: jac_row<5>(P, z, jac, k); break;
-    case 6: jac_row<6>(P, z, jac, k); break;
-    case 7: jac_row<7>(P, z, jac, k); break;
-    default: jac_row<8>(P, z, jac, k); break;
+    case 0: jac_row<0, NPT>(P, z, jac, k); break;
+    case 1: jac_row<1, NPT>(P, z, jac, k); break;
+    case 2: jac_row<2, NPT>(P, z, jac, k); break;
+    case 3: jac_row<3, NPT>(P, z, jac, k); break;
+    case 4: jac_row<4, NPT>(P, z, jac, k); break;
+    case 5: jac_row<5, NPT>(P, z, jac, k); break;
+    case 6: jac_row<6, NPT>(P, z, jac, k); break;
+    case 7: jac_row<7, NPT>(P, z, jac, k); break;
+    default: jac_row<8, NPT>(P, z, jac, k); break;
     }
-    bnd_jac(P, jac, blockIdx.y == 0 ? k : P.nb);
+    bnd_jac(P, jac, blockIdx.y == 0 ? t : P.nb);
 }
 
 __global__ __launch_bounds__(kBlock) void quad_jac_lines_kernel(QP P, const double *__restrict__ z,
@@ -883,12 +891,19 @@ int eval_cons(const ocp_problem *p, const double *z, double *c, const double *sc
 int eval_jac(const ocp_problem *p, const double *z, double *jvals, hipStream_t stream)
 {
     const QP P = make_qp(p);
-    if ((int64_t)kSlots * P.N * (int64_t)sizeof(double) <= kJacSmall)
-        hipLaunchKernelGGL(quad_jac_kernel, dim3(blocks_for(P.N, kBlock), kStates), dim3(kBlock), 0, stream, P, z,
-                           jvals);
-    else
+    switch (rules::quad_jac_path(P.N, (uintptr_t)jvals)) {
+    case rules::kJacLines:
         hipLaunchKernelGGL(quad_jac_lines_kernel, dim3(blocks_for((int64_t)P.N + kHalo, lines_span(kBlock)), kStates),
                            dim3(kBlock), 0, stream, P, z, jvals);
+        break;
+    case rules::kJacPair:
+        hipLaunchKernelGGL(quad_jac_kernel<2>, dim3(blocks_for(P.N / 2, kBlock), kStates), dim3(kBlock), 0, stream, P,
+                           z, jvals);
+        break;
+    default:
+        hipLaunchKernelGGL(quad_jac_kernel<1>, dim3(blocks_for(P.N, kBlock), kStates), dim3(kBlock), 0, stream, P, z,
+                           jvals);
+    }
     return check_launch("ocp_eval_jac");
 }
 

@@ -1,0 +1,16 @@
+// The dispatch rules of the library (csrc/ocp_rules.h) behind C symbols, for
+// tests/test_dispatch_rules.py.
+#include "ocp_rules.h"
+
+using namespace ocp::rules;
+
+extern "C" {
+
+int jac_path_of(int64_t N, int n, int m, int slots, int euler, uint64_t addr)
+{
+    return jac_path(N, n, m, slots, euler != 0, addr);
+}
+
+int quad_jac_path_of(int64_t N, uint64_t addr) { return quad_jac_path(N, addr); }
+
+}  // extern "C"

@@ -1,0 +1,54 @@
+"""The rules that choose a kernel variant or a tile shape, on the CPU: each
+test holds sizes on both sides of a line at which the variants were timed."""
+from __future__ import annotations
+
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+
+SINGLE, PAIR, LINES = 0, 1, 2  # rules::JacPath
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("rules") / "rules.so")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC",
+                           "-I" + os.path.join(ROOT, "paper_2510_03932_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "dispatch_rules.cpp"), "-o", so])
+    lib = ctypes.CDLL(so)
+    i64, i32 = ctypes.c_int64, ctypes.c_int32
+    lib.jac_path_of.argtypes = [i64, i32, i32, i32, i32, ctypes.c_uint64]
+    lib.quad_jac_path_of.argtypes = [i64, ctypes.c_uint64]
+    return lib
+
+
+@pytest.mark.parametrize("N,n,m,euler,offset,want", [
+    # rows that take no pairs: whole lines once enough workgroups carry them
+    (13009, 8, 4, 0, 0, SINGLE), (52081, 4, 2, 0, 0, LINES), (5457, 32, 16, 0, 0, LINES),
+    (2049, 32, 16, 0, 0, SINGLE), (53569, 4, 2, 1, 0, SINGLE), (124993, 4, 2, 1, 0, LINES),
+    (20000, 8, 4, 0, 1, SINGLE), (1, 1, 0, 0, 0, SINGLE),
+    # an even grid: pairs past the smallest outputs, whole lines past the L2s
+    (734000, 1, 1, 0, 0, PAIR), (978656, 1, 1, 1, 0, PAIR), (32768, 8, 4, 0, 0, PAIR),
+    (2050, 32, 16, 0, 0, PAIR), (8194, 16, 8, 0, 0, PAIR), (58594, 8, 4, 0, 0, LINES),
+    (13008, 8, 4, 0, 0, SINGLE), (4544, 16, 8, 0, 0, SINGLE), (9952, 16, 8, 1, 0, PAIR),
+    (2500002, 1, 1, 1, 0, PAIR),
+    # rows on lines or half lines: never whole lines
+    (58600, 8, 4, 0, 0, PAIR), (65104, 16, 8, 0, 8, PAIR), (65104, 16, 8, 0, 4, LINES),
+    (100000, 8, 4, 0, 0, PAIR), (1000000, 16, 8, 0, 0, PAIR)])
+def test_jacobian_path(rules, N, n, m, euler, offset, want):
+    slots = n + 1 + m if euler else 2 * (n + m)
+    assert rules.jac_path_of(N, n, m, slots, euler, 1 << 20 | 8 * offset) == want
+
+
+@pytest.mark.parametrize("N,offset,want", [
+    (10000, 0, SINGLE), (20000, 0, SINGLE), (26000, 0, PAIR), (26001, 0, SINGLE), (26000, 1, SINGLE),
+    (30001, 0, LINES), (30000, 0, PAIR), (30000, 4, LINES), (50000, 0, PAIR), (60000, 0, LINES), (1, 0, SINGLE)])
+def test_quadrotor_jacobian_path(rules, N, offset, want):
+    assert rules.quad_jac_path_of(N, 1 << 20 | 8 * offset) == want

@@ -1,0 +1,50 @@
+"""Calls whose kernel variant or tile shape is chosen by their sizes, at sizes
+on each side of the lines.  Values against the oracle (within 1e-12 * mu) or
+bit for bit against another route; the elements around an output stay
+untouched."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from tests.helpers import check_close
+from tests.test_gpu_line_aligned import Guarded, _t, ocp  # noqa: F401 (the fixture)
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+# one interval per lane, two, and whole lines (the last of each group of three
+# differs from the first in the grid or the address only); remainders of the
+# 512 intervals of a workgroup of pairs; boundary rows beside each
+@pytest.mark.parametrize("N,n,m,scheme,bnd,offset", [
+    (374992, 1, 1, 0, 2, 0), (374992, 1, 1, 0, 1, 1), (374991, 1, 1, 0, 0, 2),
+    (500002, 1, 1, 1, 2, 2), (500002, 1, 0, 1, 1, 0), (500001, 1, 1, 1, 0, 0),
+    (9952, 16, 8, 1, 1, 0), (9954, 16, 8, 1, 2, 14), (9952, 16, 8, 1, 0, 3),
+    (8194, 16, 8, 0, 2, 0), (2050, 32, 16, 0, 0, 2), (2048, 32, 16, 0, 1, 8),
+    (512, 2, 1, 0, 2, 0), (514, 2, 1, 1, 2, 0), (2, 3, 1, 0, 1, 4), (30001, 2, 2, 0, 0, 0)])
+def test_jacobian_paths(ocp, N, n, m, scheme, bnd, offset):
+    print(f"[routes] jacobian N={N} n={n} m={m} scheme={scheme} bnd={bnd} offset={offset}", flush=True)
+    inst = synth.make_instance(N, n, m, seed=81, bnd=bnd, scheme=scheme)
+    prob = ocp.Problem.from_instance(inst, torch.device("cuda", 0))
+    out = Guarded(prob.sizes["nnzj"], offset)
+    prob.jac(_t(inst.z), out=out.out)
+    want, mu = oracle.jac_ex(inst, scheme, bnd)
+    check_close(out.values(), want, mu, what="jac")
+    prob.close()
+
+
+@pytest.mark.parametrize("N,bnd,offset", [(27265, 1, 0), (27266, 2, 1), (27267, 0, 9), (30000, 1, 15),
+                                          (30000, 2, 0), (25608, 1, 8), (512, 0, 1)])
+def test_quadrotor_jacobian_paths(ocp, N, bnd, offset):
+    print(f"[routes] quadrotor jacobian N={N} bnd={bnd} offset={offset}", flush=True)
+    q = synth.make_quadrotor(N, seed=82, bnd=bnd)
+    prob = ocp.QuadrotorProblem.from_instance(q, torch.device("cuda", 0))
+    out = Guarded(prob.sizes["nnzj"], offset)
+    prob.jac(_t(q.z), out=out.out)
+    want, mu = oracle.quad_jac(q)
+    check_close(out.values(), want, mu, what="jac")
+    prob.close()
