@@ -85,7 +85,7 @@ __device__ __forceinline__ void jac_row(const QP &P, const double *__restrict__ 
             double v[NPT];
 #pragma unroll
             for (int j = 0; j < NPT; j++)
-                v[j] = __builtin_fma(-P.hh, partial(pair_index(I, p), t[j + s], u[j + s]), jac_id(I, p, s));
+                v[j] = __builtin_fma(-P.hh, jac_partial(pair_index(I, p), t[j + s], u[j + s]), jac_id(I, p, s));
             double *o = jac + (int64_t)(kRowSlot[I] + 2 * p + s) * P.N + k;
             if constexpr (NPT == 2) st_nt2(o, dbl2{v[0], v[1]});
             else st_nt(o, v[0]);
@@ -107,7 +107,7 @@ __device__ __forceinline__ void jac_row_lines(const QP &P, const double *__restr
             load_att(P, z, k, a, u);
             const Trig t = node_trig(a[0], a[1], a[2]);
 #pragma unroll
-            for (int p = 0; p < L; p++) lds[p * W + x] = partial(pair_index(I, p), t, u);
+            for (int p = 0; p < L; p++) lds[p * W + x] = jac_partial(pair_index(I, p), t, u);
         }
         __syncthreads();
     }
@@ -773,7 +773,7 @@ __global__ __launch_bounds__(kBlock) void quad_kkt_defect_kernel(QP P, QLayout L
         double *row = buf + tid * len;
 #pragma unroll
         for (int p = 0; p < L; p++) {
-            const double v = partial(pair_index(i, p), tr, u);
+            const double v = jac_partial(pair_index(i, p), tr, u);
             row[2 * p] = __builtin_fma(-P.hh, v, jac_id(i, p, 0));
             if (tid > 0) row[2 * p + 1 - len] = __builtin_fma(-P.hh, v, jac_id(i, p, 1));
         }

@@ -98,6 +98,31 @@ __device__ __forceinline__ double partial(int q, const Trig &t, const double *u)
     }
 }
 
+// The same for the Jacobian's values, with the fused multiply-adds of the sums
+// written out: left to the compiler, which of two products it rounds depends on
+// the kernel around it, and the Jacobian's and the fused KKT's values then
+// differ where the two nearly cancel.
+__device__ __forceinline__ double jac_partial(int q, const Trig &t, const double *u)
+{
+#pragma clang fp contract(off)
+    const double p = __builtin_fma(u[1], t.c7, u[2] * t.s7);
+    const double w = __builtin_fma(-u[1], t.s7, u[2] * t.c7);
+    switch (q) {
+    case 3: return u[0] * __builtin_fma(t.c7, t.s9, -(t.s7 * t.s8 * t.c9));
+    case 5: return u[0] * __builtin_fma(t.s7, t.c9, -(t.c7 * t.s8 * t.s9));
+    case 6: return __builtin_fma(t.c7 * t.s8, t.c9, t.s7 * t.s9);
+    case 10: return -u[0] * __builtin_fma(t.s7 * t.s8, t.s9, t.c7 * t.c9);
+    case 12: return u[0] * __builtin_fma(t.c7 * t.s8, t.c9, t.s7 * t.s9);
+    case 13: return __builtin_fma(t.c7 * t.s8, t.s9, -(t.s7 * t.c9));
+    case 20: return w * t.sec;
+    case 21: return p * t.s8 * t.sec2;
+    case 24: return -p;
+    case 28: return __builtin_fma(u[2], t.c7, -(u[1] * t.s7)) * t.t8;  // w with its other product rounded
+    case 29: return p * t.sec2;
+    default: return partial(q, t, u);  // products and constants
+    }
+}
+
 // Hessian entries of one node: H[s] = sw C_s - hh S_s, where sw = sigma w_k,
 // C_s the cost's constant second derivative (1 on x1, x3, x5, x7, x8, x9; r on
 // the controls) and S_s = sum_i Y_i d2F_i / (dv_a dv_b) with Y the node

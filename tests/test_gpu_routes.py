@@ -48,3 +48,20 @@ def test_quadrotor_jacobian_paths(ocp, N, bnd, offset):
     want, mu = oracle.quad_jac(q)
     check_close(out.values(), want, mu, what="jac")
     prob.close()
+
+
+@pytest.mark.parametrize("N,bnd", [(1000, 1), (4097, 0), (30001, 2), (40000, 1)])
+def test_quadrotor_fused_kkt_has_the_separate_calls_bits(ocp, N, bnd):
+    """eval_kkt evaluates the expressions of jac and hess: without
+    regularization its entries are theirs bit for bit, also where the two
+    products of a partial derivative nearly cancel (one in 250 entries of such
+    slots), on every path of the Jacobian."""
+    print(f"[routes] quadrotor fused bits N={N} bnd={bnd}", flush=True)
+    q = synth.make_quadrotor(N, seed=83, bnd=bnd)
+    prob = ocp.QuadrotorProblem.from_instance(q, torch.device("cuda", 0))
+    z, y = _t(q.z), _t(q.y)
+    _, _, pj, ph = prob.kkt_pattern()
+    kkt = prob.eval_kkt(z, y, 0.7).view(torch.int64)
+    assert torch.equal(kkt[_t(pj).long()], prob.jac(z).view(torch.int64))
+    assert torch.equal(kkt[_t(ph).long()], prob.hess(z, y, 0.7).view(torch.int64))
+    prob.close()
