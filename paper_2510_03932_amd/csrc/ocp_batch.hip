@@ -131,7 +131,7 @@ __device__ __forceinline__ KP make_kp(const BP &bp, const InstDesc &id, int b)
 // registers spill).  The Jacobian tiles are held to 6 (80 VGPRs against 98).
 template <int NB, int BS, int KINDS, int SCHEME>
 __global__ __launch_bounds__(BS, KINDS == kListKktDef ? 7 : KINDS == OCP_EVAL_JAC ? 6 : 1) void batch_kernel(BP bp, KKTLayout Lo, const InstDesc *__restrict__ inst,
-                                                   const TileDesc *__restrict__ tiles, int ntiles, int what,
+                                                   const TileDesc *__restrict__ tiles, int ntiles, int what, int al,
                                                    const double *__restrict__ z_,
                                                    const double *__restrict__ y_, const double *__restrict__ reg_,
                                                    double sigma, double *__restrict__ grad_,
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(BS, KINDS == kListKktDef ? 7 : KINDS == OCP_EVAL_JA
             if (!(KINDS & OCP_EVAL_JAC)) break;
             double *jb = jac_ + id.jac_off;
             if (td.npt == 2) {
-                jac_column_lines<BS>(P, zb, jb, td.k0, td.col, vbuf);
+                jac_column_lines<BS>(P, zb, jb, line_pos_at(al, id.jac_off), td.k0, td.col, vbuf);
                 __syncthreads();  // vbuf is reused by the next tile
             } else {
                 const int64_t k = td.k0 + (int64_t)tid;
@@ -203,13 +203,13 @@ __global__ __launch_bounds__(BS, KINDS == kListKktDef ? 7 : KINDS == OCP_EVAL_JA
         }
         case kKktDef:
             if (!(KINDS & (OCP_EVAL_KKT | kListKktDef))) break;
-            kkt_defect_tile<BS>(P, Lo, zb, reg_ ? reg_ + id.dim_off : nullptr, kkt_ + id.kkt_off, td.k0,
-                                bp.defect_lg, lds);
+            kkt_defect_tile<BS>(P, Lo, zb, reg_ ? reg_ + id.dim_off : nullptr, kkt_ + id.kkt_off,
+                                line_pos_at(al, id.kkt_off), td.k0, bp.defect_lg, lds);
             break;
         case kKktVar:
             if (!(KINDS & (OCP_EVAL_KKT | kListKktVar))) break;
             kkt_var_tile<NB, BS>(P, Lo, zb, y_ + id.c_off, sigma, reg_ ? reg_ + id.dim_off : nullptr,
-                                 kkt_ + id.kkt_off, td.k0, vbuf);
+                                 kkt_ + id.kkt_off, line_pos_at(al, id.kkt_off), td.k0, vbuf);
             break;
         case kBnd: {
             const int b = tid;
@@ -431,15 +431,16 @@ static void launch_batch_scheme(const ocp_batch *b, const TileDesc *tiles, int n
     const size_t lds = ((KINDS & kListKktDef) && (what & OCP_EVAL_KKT))
                            ? kkt_defect_lds(b->n, b->m, b->shape.T, 1 << b->bp.defect_lg) * sizeof(double)
                            : 0;
+    const int al = line_pos(KINDS & OCP_EVAL_JAC ? io.jac : io.kkt);  // of the array stored in whole lines
     const int n = b->n;
     if (n <= 4)
-        hipLaunchKernelGGL((batch_kernel<4, BS, KINDS, SCHEME>), dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, io.z, io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
+        hipLaunchKernelGGL((batch_kernel<4, BS, KINDS, SCHEME>), dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, al, io.z, io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
     else if (n <= 8)
-        hipLaunchKernelGGL((batch_kernel<8, BS, KINDS, SCHEME>), dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, io.z, io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
+        hipLaunchKernelGGL((batch_kernel<8, BS, KINDS, SCHEME>), dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, al, io.z, io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
     else if (n <= 16)
-        hipLaunchKernelGGL((batch_kernel<16, BS, KINDS, SCHEME>), dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, io.z, io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
+        hipLaunchKernelGGL((batch_kernel<16, BS, KINDS, SCHEME>), dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, al, io.z, io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
     else
-        hipLaunchKernelGGL((batch_kernel<32, BS, KINDS, SCHEME>), dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, io.z, io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
+        hipLaunchKernelGGL((batch_kernel<32, BS, KINDS, SCHEME>), dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, al, io.z, io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
 }
 
 template <int BS, int KINDS>

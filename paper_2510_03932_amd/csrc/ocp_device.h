@@ -107,22 +107,30 @@ __device__ __forceinline__ uint32_t xcd_order(uint32_t b, uint32_t nb)
 }
 
 // ---------------------------------------------------------------------------
-// A workgroup of BS lanes copies cnt doubles from LDS to out (any 8-byte
-// aligned address), placed so that every wavefront's store begins on a
+// A workgroup of BS lanes copies cnt doubles from LDS to out (position sh in
+// its line), placed so that every wavefront's store begins on a
 // 128-byte line of HBM: pure 3 GiB write streams reach 5.7-6.2 TB/s that way
 // and 3.4-4.5 TB/s from anywhere else (8-byte lanes, 784-double runs), since
 // each wavefront then completes its lines instead of leaving two of them to be
 // merged with a neighbour's.  Non-temporal 8-byte stores: 16-byte ones measured
 // the same or slower here, ordinary ones 10-30 % slower.
+//
+// Where an output begins within its line (0 .. 15 doubles) is a kernel
+// argument, `al`, computed on the host by line_pos: a kernel that looks at an
+// output's address itself loses the proof that its stores leave the
+// coefficients alone, and loads those lane by lane instead of through the
+// scalar cache.
 // ---------------------------------------------------------------------------
 constexpr int kLine = 16;  // doubles per 128-byte line
+inline int line_pos(const double *p) { return (int)(((uintptr_t)p / sizeof(double)) % kLine); }
+// The position of element i of an output that begins at position al.
+__device__ __forceinline__ int line_pos_at(int al, int64_t i) { return (int)((al + i) & (kLine - 1)); }
 // Intervals per workgroup of the kernels whose lanes exchange values with the
 // next node's (kBlock nodes close kBlock - 1): a multiple of a line.
 constexpr int kSpan = kBlock - kLine;
 template <int BS>
-__device__ __forceinline__ void copy_lines(double *__restrict__ out, const double *src, int cnt)
+__device__ __forceinline__ void copy_lines(double *__restrict__ out, int sh, const double *src, int cnt)
 {
-    const int sh = (int)(((uintptr_t)out / sizeof(double)) % kLine);
     int x = (int)threadIdx.x - sh;
     if (x >= 0 && x < cnt) st_nt(out + x, src[x]);
     for (x += BS; x < cnt; x += BS) st_nt(out + x, src[x]);
@@ -263,17 +271,18 @@ __device__ __forceinline__ void jac_column(const KP &P, const double *__restrict
 
 // Slot rows stored in whole lines.  A workgroup of BS lanes takes a tile of
 // lines_span(BS) = 2 BS - 16 intervals from k0 (a multiple of the span) of a
-// slot row of N values and stores the row's intervals [k0 - sh, k0 - sh +
-// span), sh = row_shift: the 128-byte lines that begin there, so every
-// wavefront's 16-byte stores fill whole lines whatever the row's address.
+// slot row of N values, which begins at position al in its line, and stores the
+// row's intervals [k0 - sh, k0 - sh + span), sh the position of interval k0: the
+// 128-byte lines that begin there, so every wavefront's 16-byte stores fill
+// whole lines whatever the row's address.
 // val(x) is the value of interval k0 - 15 + x, 0 <= x < 2 BS - 1.  The tiles
 // of a row are ceil((N + 15) / span).
 constexpr int kHalo = kLine - 1;
 constexpr int lines_span(int bs) { return 2 * bs - kLine; }
 template <int BS, class F>
-__device__ __forceinline__ void store_row_lines(double *__restrict__ row, int64_t N, int64_t k0, F val)
+__device__ __forceinline__ void store_row_lines(double *__restrict__ row, int al, int64_t N, int64_t k0, F val)
 {
-    const int sh = (int)(((uintptr_t)(row + k0) / sizeof(double)) % kLine);
+    const int sh = line_pos_at(al, k0);
     const int x = 2 * (int)threadIdx.x;
     if (x >= lines_span(BS)) return;
     const int64_t k = k0 - sh + x;
@@ -291,12 +300,13 @@ __device__ __forceinline__ void store_row_lines(double *__restrict__ row, int64_
 // the tile's 2 BS nodes; each node is evaluated once).
 template <int BS>
 __device__ __forceinline__ void jac_column_lines(const KP &P, const double *__restrict__ z, double *__restrict__ jac,
-                                                 int64_t k0, int col, double *lds)
+                                                 int al, int64_t k0, int col, double *lds)
 {
     const int n = P.n, m = P.m, T = P.T;
     const int64_t N = P.N, N1 = P.N1;
     const bool euler = P.scheme != 0;
     const double w = euler ? P.h : P.hh;
+    auto put = [&](int64_t r, auto val) { store_row_lines<BS>(jac + r, line_pos_at(al, r), N, k0, val); };
     if (col < n) {
         const int j = col;
         const int jn = (j + 1 == n) ? 0 : j + 1;
@@ -317,18 +327,18 @@ __device__ __forceinline__ void jac_column_lines(const KP &P, const double *__re
             auto at = [&](int x, double id) {
                 return jac_entry(i == j, i == jp, a, cs[x], id, gj, gp, i == j ? xn[x] : 0.0, i == jp ? xp[x] : 0.0);
             };
-            double *row = jac + ((int64_t)i * T + (!euler ? 2 * j : j <= i ? j : j + 1)) * N;
-            store_row_lines<BS>(row, N, k0, [&](int x) { return at(x, -1.0); });
-            if (!euler) store_row_lines<BS>(row + N, N, k0, [&](int x) { return at(x + 1, 1.0); });
+            const int64_t r = ((int64_t)i * T + (!euler ? 2 * j : j <= i ? j : j + 1)) * N;
+            put(r, [&](int x) { return at(x, -1.0); });
+            if (!euler) put(r + N, [&](int x) { return at(x + 1, 1.0); });
         }
-        if (euler) store_row_lines<BS>(jac + ((int64_t)j * T + j + 1) * N, N, k0, [](int) { return 1.0; });
+        if (euler) put(((int64_t)j * T + j + 1) * N, [](int) { return 1.0; });
     } else {
         const int l = col - n;
         for (int i = 0; i < n; i++) {
             const double v = -w * P.B[i * m + l];
-            double *row = jac + ((int64_t)i * T + (euler ? n + 1 + l : 2 * (n + l))) * N;
-            store_row_lines<BS>(row, N, k0, [&](int) { return v; });
-            if (!euler) store_row_lines<BS>(row + N, N, k0, [&](int) { return v; });
+            const int64_t r = ((int64_t)i * T + (euler ? n + 1 + l : 2 * (n + l))) * N;
+            put(r, [&](int) { return v; });
+            if (!euler) put(r + N, [&](int) { return v; });
         }
     }
 }

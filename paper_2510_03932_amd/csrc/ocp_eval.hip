@@ -49,11 +49,11 @@ __global__ __launch_bounds__(kBlock) void jac_kernel(KP P, const double *__restr
     bnd_jac(P, jac, blockIdx.y == 0 ? t : P.nb);
 }
 
-__global__ __launch_bounds__(kBlock) void jac_lines_kernel(KP P, const double *__restrict__ z,
+__global__ __launch_bounds__(kBlock) void jac_lines_kernel(KP P, int al, const double *__restrict__ z,
                                                            double *__restrict__ jac)
 {
     __shared__ double lds[6 * kBlock];
-    jac_column_lines<kBlock>(P, z, jac, (int64_t)blockIdx.x * lines_span(kBlock), blockIdx.y, lds);
+    jac_column_lines<kBlock>(P, z, jac, al, (int64_t)blockIdx.x * lines_span(kBlock), blockIdx.y, lds);
     bnd_jac(P, jac, blockIdx.x == 0 && blockIdx.y == 0 ? threadIdx.x : P.nb);
 }
 
@@ -142,10 +142,10 @@ __global__ __launch_bounds__(kBlock) void hess_euler_kernel(KP P, const double *
 // takes the nodes of whole lines of its row: 70 -> 64 us at N = 1e6, n = 16,
 // m = 8 (6.0 TB/s), 18.0 -> 16.2 us at N = 333,333, n = 12, m = 5.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void grad_kernel(KP P, const double *__restrict__ z,
+__global__ __launch_bounds__(kBlock) void grad_kernel(KP P, int al, const double *__restrict__ z,
                                                       double *__restrict__ g)
 {
-    grad_row(P, z, g, blockIdx.y, (int64_t)blockIdx.x * kBlock);
+    grad_row(P, z, g, al, blockIdx.y, (int64_t)blockIdx.x * kBlock);
 }
 
 // ---------------------------------------------------------------------------
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(kBlock) void obj_final_kernel(const double *__restr
 constexpr int kHessBatch = 8;  // slots in flight per lane (Hessian part)
 
 __global__ __launch_bounds__(kBlock) void assemble_kernel(
-    KP P, int gj, int gh, int LG, const int32_t *__restrict__ perm_j, const int32_t *__restrict__ perm_h,
+    KP P, int gj, int gh, int LG, int al, const int32_t *__restrict__ perm_j, const int32_t *__restrict__ perm_h,
     const int32_t *__restrict__ rowptr, const double *__restrict__ jv,
     const double *__restrict__ hv, const double *__restrict__ reg, double *__restrict__ kkt)
 {
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(kBlock) void assemble_kernel(
         __syncthreads();
         if (!staged) return;
         if (filled == ext) {
-            copy_lines<kBlock>(kkt + base, tile, ext);
+            copy_lines<kBlock>(kkt + base, line_pos_at(al, base), tile, ext);
         } else {
             // not an exact cover: store this tile's values directly
             visit([&](int32_t q, double v) {
@@ -353,7 +353,7 @@ hipError_t launch_jac(const KP &P, const double *z, double *jac, hipStream_t str
     switch (rules::jac_path(P.N, P.n, P.m, P.T, euler, (uintptr_t)jac)) {
     case rules::kJacLines:
         hipLaunchKernelGGL(jac_lines_kernel, dim3(blocks_for((int64_t)P.N + kHalo, lines_span(kBlock)), cols),
-                           dim3(kBlock), 0, stream, P, z, jac);
+                           dim3(kBlock), 0, stream, P, line_pos(jac), z, jac);
         break;
     case rules::kJacPair:
         if (euler) hipLaunchKernelGGL((jac_kernel<2, true>), g2, dim3(kBlock), 0, stream, P, z, jac);
@@ -401,7 +401,7 @@ hipError_t launch_obj(const KP &P, const double *z, double *partials, double *ob
 hipError_t launch_grad(const KP &P, const double *z, double *g, hipStream_t stream)
 {
     dim3 grid(blocks_for((int64_t)P.N1 + kHalo, kBlock), P.n + P.m);
-    hipLaunchKernelGGL(grad_kernel, grid, dim3(kBlock), 0, stream, P, z, g);
+    hipLaunchKernelGGL(grad_kernel, grid, dim3(kBlock), 0, stream, P, line_pos(g), z, g);
     return hipGetLastError();
 }
 
@@ -625,7 +625,7 @@ int ocp_assemble_kkt(const ocp_problem *p, const int32_t *perm_j, const int32_t 
     const unsigned gb = blocks_for(p->d.nb, kBlock);
     const size_t lds = ((size_t)(p->d.T + 1) << LG) * sizeof(double);
     hipLaunchKernelGGL(assemble_kernel, dim3(gj + gh + gb), dim3(kBlock), lds, stream, p->kp, (int)gj,
-                       (int)gh, LG, perm_j, perm_h, rowptr, jvals, hvals, reg, kkt);
+                       (int)gh, LG, line_pos(kkt), perm_j, perm_h, rowptr, jvals, hvals, reg, kkt);
     return check_launch("ocp_assemble_kkt");
 }
 

@@ -38,24 +38,34 @@ using namespace ocp::dev;
 
 namespace {
 
-__global__ __launch_bounds__(kBlock) void kkt_defect_kernel(KP P, KKTLayout Lo, int LG, const double *__restrict__ z,
+__global__ __launch_bounds__(kBlock) void kkt_defect_kernel(KP P, KKTLayout Lo, int LG, int al,
+                                                            const double *__restrict__ z,
                                                             const double *__restrict__ reg,
                                                             double *__restrict__ kkt)
 {
     extern __shared__ double lds[];
-    kkt_defect_tile<kBlock>(P, Lo, z, reg, kkt, (int64_t)xcd_order(blockIdx.x, gridDim.x) << LG, LG, lds);
+    kkt_defect_tile<kBlock>(P, Lo, z, reg, kkt, al, (int64_t)xcd_order(blockIdx.x, gridDim.x) << LG, LG, lds);
 }
 
 template <int NB>
-__global__ __launch_bounds__(kBlock) void kkt_var_kernel(KP P, KKTLayout Lo, const double *__restrict__ z,
+__global__ __launch_bounds__(kBlock) void kkt_var_kernel(KP P, KKTLayout Lo, int al, const double *__restrict__ z,
                                                          const double *__restrict__ y, double sigma,
                                                          const double *__restrict__ reg,
                                                          double *__restrict__ kkt)
 {
     __shared__ double buf[3 * kBlock];  // one state block's rows of this workgroup (<= 3 entries each)
-    kkt_var_tile<NB, kBlock>(P, Lo, z, y, sigma, reg, kkt, (int64_t)xcd_order(blockIdx.x, gridDim.x) * kBlock, buf);
+    kkt_var_tile<NB, kBlock>(P, Lo, z, y, sigma, reg, kkt, al, (int64_t)xcd_order(blockIdx.x, gridDim.x) * kBlock,
+                             buf);
     // the boundary rows ride in the first workgroup, after its own
     if (blockIdx.x == 0 && (int)threadIdx.x < P.nb) kkt_bnd_row(P, Lo, reg, kkt, threadIdx.x);
+}
+
+template <int NB>
+void launch_kkt_var(const KP &P, const KKTLayout &Lo, int al, const double *z, const double *y, double sigma,
+                    const double *reg, double *kkt, hipStream_t stream)
+{
+    hipLaunchKernelGGL(kkt_var_kernel<NB>, dim3(blocks_for(P.N1, kBlock)), dim3(kBlock), 0, stream, P, Lo, al, z, y,
+                       sigma, reg, kkt);
 }
 
 }  // namespace
@@ -71,17 +81,16 @@ hipError_t launch_eval_kkt(const KP &P, const double *z, const double *y, double
     // their cosines, the rows' regularization, the scaled coefficients and the
     // output row block
     const int KT = kkt_defect_kt(P.n, P.m, P.T, P.N);
-    const int LG = __builtin_ctz((unsigned)KT);
+    const int LG = __builtin_ctz((unsigned)KT), al = line_pos(kkt);
     const size_t lds = kkt_defect_lds(P.n, P.m, P.T, KT) * sizeof(double);
-    hipLaunchKernelGGL(kkt_defect_kernel, dim3(blocks_for(P.N, KT)), dim3(kBlock), lds, stream, P, Lo, LG, z, reg,
-                       kkt);
+    hipLaunchKernelGGL(kkt_defect_kernel, dim3(blocks_for(P.N, KT)), dim3(kBlock), lds, stream, P, Lo, LG, al, z,
+                       reg, kkt);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const dim3 g(blocks_for(P.N1, kBlock));
-    if (P.n <= 4) hipLaunchKernelGGL(kkt_var_kernel<4>, g, dim3(kBlock), 0, stream, P, Lo, z, y, sigma, reg, kkt);
-    else if (P.n <= 8) hipLaunchKernelGGL(kkt_var_kernel<8>, g, dim3(kBlock), 0, stream, P, Lo, z, y, sigma, reg, kkt);
-    else if (P.n <= 16) hipLaunchKernelGGL(kkt_var_kernel<16>, g, dim3(kBlock), 0, stream, P, Lo, z, y, sigma, reg, kkt);
-    else hipLaunchKernelGGL(kkt_var_kernel<32>, g, dim3(kBlock), 0, stream, P, Lo, z, y, sigma, reg, kkt);
+    if (P.n <= 4) launch_kkt_var<4>(P, Lo, al, z, y, sigma, reg, kkt, stream);
+    else if (P.n <= 8) launch_kkt_var<8>(P, Lo, al, z, y, sigma, reg, kkt, stream);
+    else if (P.n <= 16) launch_kkt_var<16>(P, Lo, al, z, y, sigma, reg, kkt, stream);
+    else launch_kkt_var<32>(P, Lo, al, z, y, sigma, reg, kkt, stream);
     return hipGetLastError();
 }
 

@@ -219,9 +219,9 @@ __global__ __launch_bounds__(kBlock) void mapped_plan_kernel(MP P, const int32_t
 }
 
 __global__ __launch_bounds__(kBlock) void mapped_assemble_kernel(
-    MP P, const int32_t *__restrict__ plan, const int32_t *__restrict__ perm_j, const int32_t *__restrict__ perm_h,
-    const int32_t *__restrict__ diag, const double *__restrict__ jv, const double *__restrict__ hv,
-    const double *__restrict__ reg, double *__restrict__ kkt)
+    MP P, int al, const int32_t *__restrict__ plan, const int32_t *__restrict__ perm_j,
+    const int32_t *__restrict__ perm_h, const int32_t *__restrict__ diag, const double *__restrict__ jv,
+    const double *__restrict__ hv, const double *__restrict__ reg, double *__restrict__ kkt)
 {
     extern __shared__ double tile[];  // the tile's entries (host-sized, <= kMapCap)
     __shared__ int filled;            // tile slots written by this tile's entries
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(kBlock) void mapped_assemble_kernel(
         if (filled == count) {
             // the tile's slots (distinct, the maps being injective) cover the
             // range exactly: write it in whole lines
-            copy_lines<kBlock>(kkt + base, tile, count);
+            copy_lines<kBlock>(kkt + base, line_pos_at(al, base), tile, count);
             return;
         }
         // else a plan made from other slot maps: the staged values go to
@@ -376,7 +376,8 @@ int ocp_assemble_kkt_mapped(const ocp_problem *p, const int32_t *perm_j, const i
         if (e != hipSuccess) return hip_fail("ocp_assemble_kkt_mapped: LDS size", e);
     }
     hipLaunchKernelGGL(mapped_assemble_kernel, dim3(blocks_for(p->d.N1, P.KT)), dim3(kBlock),
-                       (size_t)P.cap * sizeof(double), stream, P, plan, perm_j, perm_h, diag, jvals, hvals, reg, kkt);
+                       (size_t)P.cap * sizeof(double), stream, P, line_pos(kkt), plan, perm_j, perm_h, diag, jvals, hvals,
+                       reg, kkt);
     return check_launch("ocp_assemble_kkt_mapped");
 }
 

@@ -94,7 +94,7 @@ __device__ __forceinline__ void jac_row(const QP &P, const double *__restrict__ 
 
 template <int I>
 __device__ __forceinline__ void jac_row_lines(const QP &P, const double *__restrict__ z, double *__restrict__ jac,
-                                              int64_t k0, double *lds)
+                                              int al, int64_t k0, double *lds)
 {
     constexpr int L = kSupLen[I], W = 2 * kBlock;
     const int64_t N = P.N;
@@ -115,14 +115,14 @@ __device__ __forceinline__ void jac_row_lines(const QP &P, const double *__restr
     for (int p = 0; p < L; p++)
 #pragma unroll
         for (int s = 0; s < 2; s++) {
-            double *row = jac + (int64_t)(kRowSlot[I] + 2 * p + s) * N;
+            const int64_t r = (int64_t)(kRowSlot[I] + 2 * p + s) * N;
             const double id = jac_id(I, p, s);
             if constexpr (kRowHasTrig<I>) {
-                store_row_lines<kBlock>(row, N, k0,
+                store_row_lines<kBlock>(jac + r, line_pos_at(al, r), N, k0,
                                         [&](int x) { return __builtin_fma(-P.hh, lds[p * W + x + s], id); });
             } else {
                 const double v = __builtin_fma(-P.hh, partial(pair_index(I, p), Trig{}, nullptr), id);
-                store_row_lines<kBlock>(row, N, k0, [&](int) { return v; });
+                store_row_lines<kBlock>(jac + r, line_pos_at(al, r), N, k0, [&](int) { return v; });
             }
         }
 }
@@ -160,21 +160,21 @@ __global__ __launch_bounds__(kBlock) void quad_jac_kernel(QP P, const double *__
     bnd_jac(P, jac, blockIdx.y == 0 ? t : P.nb);
 }
 
-__global__ __launch_bounds__(kBlock) void quad_jac_lines_kernel(QP P, const double *__restrict__ z,
+__global__ __launch_bounds__(kBlock) void quad_jac_lines_kernel(QP P, int al, const double *__restrict__ z,
                                                                 double *__restrict__ jac)
 {
     __shared__ double lds[6 * 2 * kBlock];
     const int64_t k0 = (int64_t)blockIdx.x * lines_span(kBlock);
     switch (blockIdx.y) {
-    case 0: jac_row_lines<0>(P, z, jac, k0, lds); break;
-    case 1: jac_row_lines<1>(P, z, jac, k0, lds); break;
-    case 2: jac_row_lines<2>(P, z, jac, k0, lds); break;
-    case 3: jac_row_lines<3>(P, z, jac, k0, lds); break;
-    case 4: jac_row_lines<4>(P, z, jac, k0, lds); break;
-    case 5: jac_row_lines<5>(P, z, jac, k0, lds); break;
-    case 6: jac_row_lines<6>(P, z, jac, k0, lds); break;
-    case 7: jac_row_lines<7>(P, z, jac, k0, lds); break;
-    default: jac_row_lines<8>(P, z, jac, k0, lds); break;
+    case 0: jac_row_lines<0>(P, z, jac, al, k0, lds); break;
+    case 1: jac_row_lines<1>(P, z, jac, al, k0, lds); break;
+    case 2: jac_row_lines<2>(P, z, jac, al, k0, lds); break;
+    case 3: jac_row_lines<3>(P, z, jac, al, k0, lds); break;
+    case 4: jac_row_lines<4>(P, z, jac, al, k0, lds); break;
+    case 5: jac_row_lines<5>(P, z, jac, al, k0, lds); break;
+    case 6: jac_row_lines<6>(P, z, jac, al, k0, lds); break;
+    case 7: jac_row_lines<7>(P, z, jac, al, k0, lds); break;
+    default: jac_row_lines<8>(P, z, jac, al, k0, lds); break;
     }
     bnd_jac(P, jac, blockIdx.x == 0 && blockIdx.y == 0 ? threadIdx.x : P.nb);
 }
@@ -347,7 +347,7 @@ struct AsmGroups {
 };
 
 __global__ __launch_bounds__(kBlock) void quad_assemble_kernel(
-    QP P, AsmGroups G, int nnzk, const int32_t *__restrict__ perm_j,
+    QP P, AsmGroups G, int nnzk, int al, const int32_t *__restrict__ perm_j,
     const int32_t *__restrict__ perm_h, const int32_t *__restrict__ rowptr, const double *__restrict__ jv,
     const double *__restrict__ hv, const double *__restrict__ reg, double *__restrict__ kkt)
 {
@@ -448,7 +448,7 @@ __global__ __launch_bounds__(kBlock) void quad_assemble_kernel(
     __syncthreads();
     if (!staged) return;
     if (filled == ext) {
-        copy_lines<kBlock>(kkt + base, tile, ext);
+        copy_lines<kBlock>(kkt + base, line_pos_at(al, base), tile, ext);
     } else {
         visit([&](int32_t q, double v) {
             if ((uint32_t)q < (uint32_t)nnzk) kkt[q] = v;
@@ -681,7 +681,7 @@ struct QLayout {
 // N = 2e5, 77 us at N = 1e6 as before (5.2 TB/s read and written).
 template <int V0, int V1>
 __device__ __forceinline__ void quad_store_var_rows(const QLayout &Lo, const double (&H)[kHessNode], int64_t k0,
-                                                    int kn, double *__restrict__ kkt, double *buf)
+                                                    int kn, double *__restrict__ kkt, int al, double *buf)
 {
     constexpr int f0 = kHessFirst[V0];
 #pragma unroll
@@ -694,11 +694,12 @@ __device__ __forceinline__ void quad_store_var_rows(const QLayout &Lo, const dou
 #pragma unroll
     for (int v = V0; v < V1; v++) {
         const int f = kHessFirst[v], len = kHessFirst[v + 1] - f;
-        copy_lines<kBlock>(kkt + Lo.var_start[v] + k0 * len, buf + (f - f0) * kBlock, kn * len);
+        const int64_t e = Lo.var_start[v] + k0 * len;
+        copy_lines<kBlock>(kkt + e, line_pos_at(al, e), buf + (f - f0) * kBlock, kn * len);
     }
 }
 
-__global__ __launch_bounds__(kBlock) void quad_kkt_var_kernel(QP P, QLayout Lo, const double *__restrict__ z,
+__global__ __launch_bounds__(kBlock) void quad_kkt_var_kernel(QP P, QLayout Lo, int al, const double *__restrict__ z,
                                                               const double *__restrict__ y, double sigma,
                                                               const double *__restrict__ reg,
                                                               double *__restrict__ kkt)
@@ -733,9 +734,9 @@ __global__ __launch_bounds__(kBlock) void quad_kkt_var_kernel(QP P, QLayout Lo, 
         }
     }
     static_assert(kHessFirst[9] == 12 && kHessNode - kHessFirst[9] <= 12, "two halves of the LDS buffer");
-    quad_store_var_rows<0, 9>(Lo, H, k0, kn, kkt, buf);
+    quad_store_var_rows<0, 9>(Lo, H, k0, kn, kkt, al, buf);
     __syncthreads();
-    quad_store_var_rows<9, kVars>(Lo, H, k0, kn, kkt, buf);
+    quad_store_var_rows<9, kVars>(Lo, H, k0, kn, kkt, al, buf);
     if (blockIdx.x == 0 && (int)threadIdx.x < P.nb) {  // a boundary row: its state entry (1) and its diagonal
         const int b = threadIdx.x;
         kkt[Lo.bnd_start + 2 * b] = 1.0;
@@ -752,7 +753,7 @@ __global__ __launch_bounds__(kBlock) void quad_kkt_var_kernel(QP P, QLayout Lo, 
 // it: 157 -> 142 us at N = 1e6, 34 -> 29.5 us at N = 2e5, 5.1 TB/s read and
 // written.  Two or three row blocks per barrier measured the same at N = 2e5
 // and slower at N = 1e6 (145-148 us, with 64, 128 or 256 lanes).
-__global__ __launch_bounds__(kBlock) void quad_kkt_defect_kernel(QP P, QLayout Lo, const double *__restrict__ z,
+__global__ __launch_bounds__(kBlock) void quad_kkt_defect_kernel(QP P, QLayout Lo, int al, const double *__restrict__ z,
                                                                  const double *__restrict__ reg,
                                                                  double *__restrict__ kkt)
 {
@@ -779,7 +780,8 @@ __global__ __launch_bounds__(kBlock) void quad_kkt_defect_kernel(QP P, QLayout L
         }
         row[len - 1] = rg[i];
         __syncthreads();
-        copy_lines<kBlock>(kkt + Lo.def_start[i] + k0 * len, buf, kn * len);
+        const int64_t e = Lo.def_start[i] + k0 * len;
+        copy_lines<kBlock>(kkt + e, line_pos_at(al, e), buf, kn * len);
         __syncthreads();
     }
 }
@@ -828,10 +830,11 @@ int eval_kkt(const ocp_problem *p, const double *z, const double *y, double sigm
         o += (int64_t)(kRowSlot[i + 1] - kRowSlot[i] + 1) * N;
     }
     Lo.bnd_start = o;
-    hipLaunchKernelGGL(quad_kkt_defect_kernel, dim3(blocks_for(N, kBlock - 1)), dim3(kBlock), 0, stream, P, Lo, z,
+    const int al = line_pos(kkt);
+    hipLaunchKernelGGL(quad_kkt_defect_kernel, dim3(blocks_for(N, kBlock - 1)), dim3(kBlock), 0, stream, P, Lo, al, z,
                        reg, kkt);
     if (int rc = check_launch("ocp_eval_kkt")) return rc;
-    hipLaunchKernelGGL(quad_kkt_var_kernel, dim3(blocks_for(N1, kBlock)), dim3(kBlock), 0, stream, P, Lo, z, y,
+    hipLaunchKernelGGL(quad_kkt_var_kernel, dim3(blocks_for(N1, kBlock)), dim3(kBlock), 0, stream, P, Lo, al, z, y,
                        sigma, reg, kkt);
     return check_launch("ocp_eval_kkt");
 }
@@ -894,7 +897,7 @@ int eval_jac(const ocp_problem *p, const double *z, double *jvals, hipStream_t s
     switch (rules::quad_jac_path(P.N, (uintptr_t)jvals)) {
     case rules::kJacLines:
         hipLaunchKernelGGL(quad_jac_lines_kernel, dim3(blocks_for((int64_t)P.N + kHalo, lines_span(kBlock)), kStates),
-                           dim3(kBlock), 0, stream, P, z, jvals);
+                           dim3(kBlock), 0, stream, P, line_pos(jvals), z, jvals);
         break;
     case rules::kJacPair:
         hipLaunchKernelGGL(quad_jac_kernel<2>, dim3(blocks_for(P.N / 2, kBlock), kStates), dim3(kBlock), 0, stream, P,
@@ -934,7 +937,7 @@ int assemble_kkt(const ocp_problem *p, const int32_t *perm_j, const int32_t *per
     G.tile0[kGroups] = (int)blocks;
     blocks += blocks_for(P.nb, kBlock);
     hipLaunchKernelGGL(quad_assemble_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, stream, P, G,
-                       (int)p->d.nnzk, perm_j, perm_h, rowptr, jvals, hvals, reg, kkt);
+                       (int)p->d.nnzk, line_pos(kkt), perm_j, perm_h, rowptr, jvals, hvals, reg, kkt);
     return check_launch("ocp_assemble_kkt");
 }
 

@@ -90,15 +90,14 @@ __device__ __forceinline__ double bnd_value(const KP &P, const double *__restric
 // g that begin at or before k0: whole lines whatever the row's address (a
 // value needs its own node only, so a lane simply takes another node).  The
 // tiles of a row are ceil((N + 1 + 15) / kBlock).
-__device__ __forceinline__ void grad_row(const KP &P, const double *__restrict__ z, double *__restrict__ g, int comp,
-                                         int64_t k0)
+__device__ __forceinline__ void grad_row(const KP &P, const double *__restrict__ z, double *__restrict__ g, int al,
+                                         int comp, int64_t k0)
 {
     const bool state = comp < P.n;
     const double coef = state ? P.q[comp] : P.r[comp - P.n];
     const int64_t len = state ? P.N1 : P.NU;
     const int64_t row = state ? (int64_t)comp * P.N1 : (int64_t)P.n * P.N1 + (int64_t)(comp - P.n) * P.NU;
-    const int sh = (int)(((uintptr_t)(g + row + k0) / sizeof(double)) % kLine);
-    const int64_t k = k0 - sh + (int)threadIdx.x;
+    const int64_t k = k0 - line_pos_at(al, row + k0) + (int)threadIdx.x;
     if (k >= 0 && k < len) st_nt(g + row + k, 2.0 * node_weight(P, (int)k) * coef * z[row + k]);
 }
 
@@ -351,7 +350,7 @@ __device__ __forceinline__ void defect_column(int i, int c, int kk, int n, int m
 // following tile may restage the LDS.
 template <int BS>
 __device__ __forceinline__ void kkt_defect_tile(const KP &P, const KKTLayout &Lo, const double *__restrict__ z,
-                                                const double *__restrict__ reg, double *__restrict__ kkt,
+                                                const double *__restrict__ reg, double *__restrict__ kkt, int al,
                                                 int64_t k0, int LG, double *lds)
 {
     // no implicit contraction: the single-instance and the batched kernels
@@ -395,8 +394,8 @@ __device__ __forceinline__ void kkt_defect_tile(const KP &P, const KKTLayout &Lo
             defect_column(i, c, kk, n, m, T, W, KT, euler, cf, gs, xs, cs, rg, tile + kk * T1);
         }
         __syncthreads();
-        double *out = kkt + cons_start + (i * N + k0) * T1;
-        copy_lines<BS>(out, tile, kn * T1);
+        const int64_t e = cons_start + (i * N + k0) * T1;
+        copy_lines<BS>(kkt + e, line_pos_at(al, e), tile, kn * T1);
         __syncthreads();
     }
 }
@@ -409,7 +408,7 @@ __device__ __forceinline__ void kkt_defect_tile(const KP &P, const KKTLayout &Lo
 template <int NB, int BS>
 __device__ __forceinline__ void kkt_var_tile(const KP &P, const KKTLayout &Lo, const double *__restrict__ z,
                                              const double *__restrict__ y, double sigma,
-                                             const double *__restrict__ reg, double *__restrict__ kkt,
+                                             const double *__restrict__ reg, double *__restrict__ kkt, int al,
                                              int64_t k0, double *buf)
 {
 #pragma clang fp contract(off)  // as in kkt_defect_tile
@@ -479,8 +478,8 @@ __device__ __forceinline__ void kkt_var_tile(const KP &P, const KKTLayout &Lo, c
                 if (n == 2 && a == 1) row[0] = pr[0];
             }
             __syncthreads();
-            double *out = kkt + (int64_t)Lo.pre[a] * N1 + k0 * len;
-            copy_lines<BS>(out, buf, kn * len);
+            const int64_t e = (int64_t)Lo.pre[a] * N1 + k0 * len;
+            copy_lines<BS>(kkt + e, line_pos_at(al, e), buf, kn * len);
             __syncthreads();
         }
     }
