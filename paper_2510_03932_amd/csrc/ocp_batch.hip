@@ -40,6 +40,7 @@
 
 #include "ocp_device.h"
 #include "ocp_internal.h"
+#include "ocp_rules.h"
 #include "ocp_step_device.h"
 
 using namespace ocp;
@@ -53,6 +54,9 @@ constexpr int kMasks = 256;    // tile-list keys: evaluation masks 1 .. OCP_EVAL
 // Tile-list keys of the two KKT groups (outside the OCP_EVAL_* bits): the
 // defect-row tiles (with the boundary rows), and the variable-row tiles.
 constexpr int kListKktDef = 64, kListKktVar = 128;
+// A kernel instantiation only (its lists have the key OCP_EVAL_JAC): Jacobian
+// tiles of one or two intervals per lane, at the registers the compiler takes.
+constexpr int kJacDirect = 256;
 
 // One instance's place in the packed arrays (device copy of the offset table).
 struct InstDesc {
@@ -70,7 +74,7 @@ struct TileDesc {
     int32_t b;     // instance
     int32_t k0;    // first interval or node
     int16_t kind;  // TileKind
-    int16_t npt;   // intervals per lane of a Jacobian tile: 1, or 2 in whole lines
+    int16_t npt;   // intervals per lane of a Jacobian tile stored directly: 1 or 2; 0: whole lines
     int32_t col;   // Jacobian column 0 .. n+m-1
 };
 
@@ -128,21 +132,28 @@ __device__ __forceinline__ KP make_kp(const BP &bp, const InstDesc &id, int b)
 // The defect-row KKT tiles wait on each tile's descriptors and loads, so more
 // of them in flight help: held to 7 wavefronts per SIMD (71 VGPRs against 73)
 // they take 1.10 ms against 1.17 for 512 instances, n = 6, m = 3 (at 8 the
-// registers spill).  The Jacobian tiles are held to 6 (80 VGPRs against 98).
+// registers spill).  The whole-line Jacobian tiles are held to 6 (80 VGPRs
+// against 98).
+constexpr int min_waves(int kinds) { return kinds == kListKktDef ? 7 : kinds == OCP_EVAL_JAC ? 6 : 1; }
+
 template <int NB, int BS, int KINDS, int SCHEME>
-__global__ __launch_bounds__(BS, KINDS == kListKktDef ? 7 : KINDS == OCP_EVAL_JAC ? 6 : 1) void batch_kernel(BP bp, KKTLayout Lo, const InstDesc *__restrict__ inst,
-                                                   const TileDesc *__restrict__ tiles, int ntiles, int what, int al,
-                                                   const double *__restrict__ z_,
-                                                   const double *__restrict__ y_, const double *__restrict__ reg_,
-                                                   double sigma, double *__restrict__ grad_,
-                                                   double *__restrict__ cons_, double *__restrict__ jac_,
-                                                   double *__restrict__ hess_, double *__restrict__ kkt_,
-                                                   double *__restrict__ parts_)
+__global__ __launch_bounds__(BS, min_waves(KINDS)) void batch_kernel(
+    BP bp, KKTLayout Lo, const InstDesc *__restrict__ inst, const TileDesc *__restrict__ tiles, int ntiles, int what,
+    int al, const double *__restrict__ z_, const double *__restrict__ y_, const double *__restrict__ reg_,
+    double sigma, double *__restrict__ grad_, double *__restrict__ cons_, double *__restrict__ jac_,
+    double *__restrict__ hess_, double *__restrict__ kkt_, double *__restrict__ parts_)
 {
     extern __shared__ double lds[];   // defect-row KKT tile (dynamic, only with OCP_EVAL_KKT)
-    __shared__ double vbuf[(KINDS & OCP_EVAL_JAC ? 6 : 3) * BS];  // Jacobian column or variable-row KKT tile
+    __shared__ double vbuf[(KINDS & OCP_EVAL_JAC ? 6 : 3) * BS];  // whole-line Jacobian or variable-row KKT tile
     __shared__ double ws[4];          // objective sums
-    const int tid = threadIdx.x;
+    int tid = threadIdx.x;
+    // Direct Jacobian tiles of the trapezoidal scheme: naming register 97 holds
+    // a SIMD to four wavefronts.  With the five that 81 registers allow, more
+    // slot rows are in flight than the L2s keep until a neighbour completes
+    // their lines: n = 6, N = 193 (346 MB) 92 against 75 us, n = 16, N in
+    // 50 .. 200 (0.8 GB) 218 against 205.  (Not volatile: a side effect here
+    // would send the coefficients' loads round the scalar cache.)
+    if constexpr (KINDS == kJacDirect && SCHEME == 0) asm("" : "+v"(tid) : : "v97");
     for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
         // the KKT and defect tiles of an instance share lines with their
         // neighbours, so each XCD takes a contiguous run of them (see xcd_order)
@@ -153,14 +164,27 @@ __global__ __launch_bounds__(BS, KINDS == kListKktDef ? 7 : KINDS == OCP_EVAL_JA
         const double *zb = z_ + id.z_off;
         switch (td.kind) {
         case kJac: {
-            if (!(KINDS & OCP_EVAL_JAC)) break;
+            if (!(KINDS & (OCP_EVAL_JAC | kJacDirect))) break;
             double *jb = jac_ + id.jac_off;
-            if (td.npt == 2) {
+            constexpr bool kEuler = SCHEME != 0;
+            if ((KINDS & OCP_EVAL_JAC) && td.npt == 0) {
                 jac_column_lines<BS>(P, zb, jb, line_pos_at(al, id.jac_off), td.k0, td.col, vbuf);
                 __syncthreads();  // vbuf is reused by the next tile
+            } else if ((KINDS & kJacDirect) && td.npt == 2) {
+                // paired stores need a 16-byte aligned output, else the lane
+                // stores its two intervals one by one
+                const int64_t k = td.k0 + 2 * (int64_t)tid;
+                if (k < P.N) {
+                    if (al % 2 == 0) {
+                        jac_column<2, kEuler>(P, zb, jb, k, td.col);
+                    } else {
+                        jac_column<1, kEuler>(P, zb, jb, k, td.col);
+                        jac_column<1, kEuler>(P, zb, jb, k + 1, td.col);
+                    }
+                }
             } else {
                 const int64_t k = td.k0 + (int64_t)tid;
-                if (k < P.N) jac_column<1, SCHEME != 0>(P, zb, jb, k, td.col);
+                if (k < P.N) jac_column<1, kEuler>(P, zb, jb, k, td.col);
             }
             break;
         }
@@ -213,10 +237,11 @@ __global__ __launch_bounds__(BS, KINDS == kListKktDef ? 7 : KINDS == OCP_EVAL_JA
             break;
         case kBnd: {
             const int b = tid;
-            if ((KINDS & (OCP_EVAL_CONS | OCP_EVAL_JAC | OCP_EVAL_KKT | kListKktDef)) && b < P.nb) {
+            if ((KINDS & (OCP_EVAL_CONS | OCP_EVAL_JAC | kJacDirect | OCP_EVAL_KKT | kListKktDef)) && b < P.nb) {
                 if ((KINDS & OCP_EVAL_CONS) && (what & OCP_EVAL_CONS))
                     cons_[id.c_off + (int64_t)P.n * P.N + b] = bnd_value(P, zb, b);
-                if ((KINDS & OCP_EVAL_JAC) && (what & OCP_EVAL_JAC)) jac_[id.jac_off + (int64_t)P.n * P.N * P.T + b] = 1.0;
+                if ((KINDS & (OCP_EVAL_JAC | kJacDirect)) && (what & OCP_EVAL_JAC))
+                    jac_[id.jac_off + (int64_t)P.n * P.N * P.T + b] = 1.0;
                 if ((KINDS & (OCP_EVAL_KKT | kListKktDef)) && (what & OCP_EVAL_KKT))
                     kkt_bnd_row(P, Lo, reg_ ? reg_ + id.dim_off : nullptr, kkt_ + id.kkt_off, b);
             }
@@ -259,6 +284,7 @@ struct ocp_batch {
     double *parts = nullptr;       // device objective partials (part_off[count] doubles)
     mutable std::mutex mu;         // guards the tile-list cache
     mutable TileList lists[kMasks];  // per evaluation mask, for cfg
+    bool jac_direct = false;         // the Jacobian tiles of cfg are those of kJacDirect
     ocp_batch_config cfg{256, 1, 0, 1};
     BP bp{};
     KKTLayout Lo{};
@@ -281,26 +307,31 @@ static bool valid_config(const ocp_batch_config &c)
            c.wgs_per_cu >= 0 && c.wgs_per_cu <= 32 && (c.order == 0 || c.order == 1);
 }
 
-// Tile list of a config and evaluation mask, instance-major.  With `pair`,
-// Jacobian tiles take two intervals per lane, stored in whole lines, for the
-// instances whose slot rows do not all begin on a 128-byte line of an aligned
-// packed array (those are stored directly, as launch_jac does).  In lines
-// against directly, n = 6, m = 3: 98 against 139 us (482 MB), 27 against 35 us
-// (118 MB); n = 4, m = 2: 8.3 against 9.1 us (26 MB), the same at 6.5 MB.
+static rules::BatchJac jac_path_of(const ocp_batch &b, const ocp_batch_config &c)
+{
+    return rules::batch_jac(b.Ns, b.n, b.shape.T, b.scheme != OCP_SCHEME_TRAPEZOIDAL, c.pair != 0, c.block);
+}
+
+// Tile list of a config and evaluation mask, instance-major.  The Jacobian
+// tiles follow rules::batch_jac; among those in whole lines, an instance whose
+// slot rows all begin on a line of an aligned packed array is stored directly.
 static std::vector<TileDesc> build_tiles(const ocp_batch &b, const ocp_batch_config &c, int what)
 {
     std::vector<TileDesc> t;
     const int cols = b.n + b.m;
     const bool euler = b.scheme != OCP_SCHEME_TRAPEZOIDAL;
+    const rules::BatchJac path = jac_path_of(b, c);
     for (int32_t i = 0; i < b.count; i++) {
         const int64_t N = b.Ns[i];
         auto put = [&](int64_t k0, TileKind kind, int npt, int col) {
             t.push_back({i, (int32_t)k0, (int16_t)kind, (int16_t)npt, (int32_t)col});
         };
         if (what & OCP_EVAL_JAC) {
-            const int npt = (c.pair && !(N % kLine == 0 && b.jac_off[i] % kLine == 0)) ? 2 : 1;
-            const int64_t span = npt == 2 ? lines_span(c.block) : c.block;
-            const int64_t last = npt == 2 ? N + kHalo : N;  // lines begin up to 15 intervals before k0
+            int npt = 1;
+            if (path == rules::kBatchLines) npt = N % kLine == 0 && b.jac_off[i] % kLine == 0 ? 1 : 0;
+            if (path == rules::kBatchDirect) npt = c.pair && N % 2 == 0 && b.jac_off[i] % 2 == 0 ? 2 : 1;
+            const int64_t span = npt == 0 ? lines_span(c.block) : npt * c.block;
+            const int64_t last = npt == 0 ? N + kHalo : N;  // lines begin up to 15 intervals before k0
             if (c.order == 0) {
                 for (int64_t k0 = 0; k0 < last; k0 += span)
                     for (int col = 0; col < cols; col++) put(k0, kJac, npt, col);
@@ -372,6 +403,7 @@ static int set_cfg(ocp_batch *b, const ocp_batch_config &c)
         std::lock_guard<std::mutex> lock(b->mu);
         free_lists(b);
         b->cfg = c;
+        b->jac_direct = jac_path_of(*b, c) == rules::kBatchDirect;
     }
     TileList l;
     if (int rc = tile_list(b, OCP_EVAL_JAC, &l)) return rc;
@@ -431,7 +463,8 @@ static void launch_batch_scheme(const ocp_batch *b, const TileDesc *tiles, int n
     const size_t lds = ((KINDS & kListKktDef) && (what & OCP_EVAL_KKT))
                            ? kkt_defect_lds(b->n, b->m, b->shape.T, 1 << b->bp.defect_lg) * sizeof(double)
                            : 0;
-    const int al = line_pos(KINDS & OCP_EVAL_JAC ? io.jac : io.kkt);  // of the array stored in whole lines
+    // where the array of the Jacobian or KKT tiles begins in its line
+    const int al = line_pos(KINDS & (OCP_EVAL_JAC | kJacDirect) ? io.jac : io.kkt);
     const int n = b->n;
     if (n <= 4)
         hipLaunchKernelGGL((batch_kernel<4, BS, KINDS, SCHEME>), dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, al, io.z, io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
@@ -457,7 +490,10 @@ static void launch_batch_bs(const ocp_batch *b, int g, const TileDesc *tiles, in
                             const BIO &io, hipStream_t s)
 {
     switch (g) {
-    case 0: launch_batch_kinds<BS, kGroupKinds[0]>(b, tiles, ntiles, what, io, s); break;
+    case 0:
+        if (b->jac_direct) launch_batch_kinds<BS, kJacDirect>(b, tiles, ntiles, what, io, s);
+        else launch_batch_kinds<BS, kGroupKinds[0]>(b, tiles, ntiles, what, io, s);
+        break;
     case 1: launch_batch_kinds<BS, kGroupKinds[1]>(b, tiles, ntiles, what, io, s); break;
     case 2: launch_batch_kinds<BS, kGroupKinds[2]>(b, tiles, ntiles, what, io, s); break;
     case 3: launch_batch_kinds<BS, kGroupKinds[3]>(b, tiles, ntiles, what, io, s); break;
@@ -707,6 +743,7 @@ int ocp_batch_create_ex(int32_t count, const int64_t *Ns, int32_t n, int32_t m, 
     b->bp.AT = b->coef + nplain;
     b->bp.BT = b->bp.AT + nAT;
     b->Lo = kkt_layout(n);
+    b->jac_direct = jac_path_of(*b, b->cfg) == rules::kBatchDirect;
     TileList l;
     rc = tile_list(b, OCP_EVAL_JAC, &l);
     if (rc) {

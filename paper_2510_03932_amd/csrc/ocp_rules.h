@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <vector>
 
 namespace ocp {
 namespace rules {
@@ -59,6 +60,49 @@ inline JacPath quad_jac_path(int64_t N, uint64_t addr)
     const bool halves = N % 8 == 0 && addr % 64 == 0;
     if (fills && (!halves || bytes > 30 * kMiB)) return kJacLines;
     return halves && bytes > 12 * kMiB ? kJacPair : kJacSingle;
+}
+
+// Jacobian tiles of a batch, one column of a run of intervals per workgroup:
+//   kBatchDirect  one or two intervals per lane, stored directly
+//   kBatchShort   one interval per lane in the kernel of the whole-line tiles,
+//                 which more workgroups fit: an instance gives a tile one
+//                 wavefront's work or little more, and only workgroups in flight
+//                 hide its descriptors and loads
+//   kBatchLines   whole lines of 2 `block` - 16 intervals (instances whose rows
+//                 begin on lines stored directly among them)
+// A whole-line tile takes its full time however few intervals it stores, so
+// what counts is its wavefronts against those of the direct tiles (r): at
+// N = 17, n = 6 (346 MB) whole lines take 2.4 times as long, at r = 1.1 and
+// n = 6 1.2 times, n = 16 0.91 times, at r = 0.8 and 122 MB 1.15 times, at
+// r = 0.6 0.8 times (n = 4 .. 24, 0.7 to 0.9 GB); below the size of the L2s
+// direct stores merge there and win (n = 4, 26 MB: 8.4 against 9.0 us; n = 8,
+// 54 MB: 16.5 against 14.5).  Forward Euler stores half as much per node:
+// r = 0.75 and 96 MB still 1.12 times.  Rows that all begin on lines need none
+// of it: direct (N = 384, n = 6: 33 against 37 us).
+// kBatchShort against kBatchDirect: N in 10 .. 60, n = 6 57 against 64 us,
+// forward Euler (n = 8) 83 against 115, N in 50 .. 200 37 against 42, but
+// under the trapezoidal scheme N in 50 .. 200, n = 8, 56 against 50.
+enum BatchJac { kBatchDirect = 0, kBatchShort, kBatchLines };
+
+inline BatchJac batch_jac(const std::vector<int64_t> &Ns, int n, int slots, bool euler, bool pair, int block)
+{
+    const int64_t span = 2 * block - kLineDoubles, waves = block / 64, count = (int64_t)Ns.size();
+    int64_t intervals = 0, direct = 0, lines = 0;  // and wavefronts of each form, per column
+    bool on_lines = true;
+    for (int64_t N : Ns) {
+        intervals += N;
+        on_lines = on_lines && N % kLineDoubles == 0;
+        direct += (N + 63) / 64;
+        lines += (N + kLineDoubles - 1 + span - 1) / span * waves;
+    }
+    const int64_t bytes = (int64_t)n * slots * intervals * 8;
+    if (10 * direct <= 11 * count || (euler && intervals <= 128 * count)) return kBatchShort;
+    if (!pair || on_lines) return kBatchDirect;
+    // the largest r, in hundredths: higher for an output that no cache holds,
+    // and then with many rows per column
+    const bool large = bytes > 256 * kMiB;
+    const int64_t r = euler ? (large && n >= 12 ? 80 : 70) : !large ? 78 : n >= 8 ? 110 : 85;
+    return 100 * lines <= r * direct && bytes > (euler ? 48 : 40) * kMiB ? kBatchLines : kBatchDirect;
 }
 
 }  // namespace rules

@@ -2,6 +2,8 @@
 // tests/test_dispatch_rules.py.
 #include "ocp_rules.h"
 
+#include <vector>
+
 using namespace ocp::rules;
 
 extern "C" {
@@ -12,5 +14,10 @@ int jac_path_of(int64_t N, int n, int m, int slots, int euler, uint64_t addr)
 }
 
 int quad_jac_path_of(int64_t N, uint64_t addr) { return quad_jac_path(N, addr); }
+
+int batch_jac_of(int64_t count, const int64_t *Ns, int n, int slots, int euler, int pair, int block)
+{
+    return batch_jac(std::vector<int64_t>(Ns, Ns + count), n, slots, euler != 0, pair != 0, block);
+}
 
 }  // extern "C"

@@ -7,6 +7,7 @@ import os
 import shutil
 import subprocess
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -26,6 +27,7 @@ def rules(tmp_path_factory):
     i64, i32 = ctypes.c_int64, ctypes.c_int32
     lib.jac_path_of.argtypes = [i64, i32, i32, i32, i32, ctypes.c_uint64]
     lib.quad_jac_path_of.argtypes = [i64, ctypes.c_uint64]
+    lib.batch_jac_of.argtypes = [i64, ctypes.POINTER(i64), i32, i32, i32, i32, i32]
     return lib
 
 
@@ -52,3 +54,29 @@ def test_jacobian_path(rules, N, n, m, euler, offset, want):
     (30001, 0, LINES), (30000, 0, PAIR), (30000, 4, LINES), (50000, 0, PAIR), (60000, 0, LINES), (1, 0, SINGLE)])
 def test_quadrotor_jacobian_path(rules, N, offset, want):
     assert rules.quad_jac_path_of(N, 1 << 20 | 8 * offset) == want
+
+
+DIRECT, SHORT, BATCH_LINES = 0, 1, 2  # rules::BatchJac
+
+
+def _lengths(Ns):
+    Ns = np.ascontiguousarray(Ns, np.int64)
+    return len(Ns), Ns.ctypes.data_as(ctypes.POINTER(ctypes.c_int64)), Ns
+
+
+@pytest.mark.parametrize("count,lo,hi,n,m,euler,pair,want", [
+    # short horizons, as model-predictive control has them
+    (4096, 10, 60, 4, 2, 0, 1, SHORT), (4096, 10, 60, 16, 8, 0, 1, SHORT), (23529, 17, 17, 6, 3, 0, 1, SHORT),
+    (4096, 10, 60, 16, 8, 1, 1, SHORT), (1024, 50, 200, 8, 4, 1, 1, SHORT), (40, 20, 20, 4, 2, 0, 0, SHORT),
+    # a wavefront or two more: direct, until whole lines pay
+    (6153, 65, 65, 16, 8, 0, 1, DIRECT), (1024, 50, 200, 6, 3, 0, 1, DIRECT), (2072, 193, 193, 6, 3, 0, 1, DIRECT),
+    (1024, 100, 300, 4, 2, 0, 1, DIRECT), (256, 100, 300, 6, 3, 1, 1, DIRECT), (2072, 193, 193, 16, 8, 0, 1, BATCH_LINES),
+    (804, 497, 497, 4, 2, 0, 1, DIRECT), (1556, 257, 257, 6, 3, 0, 1, BATCH_LINES),
+    # long instances: whole lines past the L2s
+    (512, 200, 20000, 6, 3, 0, 1, BATCH_LINES), (512, 200, 20000, 6, 3, 0, 0, DIRECT),
+    (9, 2001, 2001, 6, 3, 0, 1, DIRECT), (512, 100, 2000, 16, 8, 1, 1, BATCH_LINES), (402, 497, 497, 6, 3, 1, 1, DIRECT),
+    (77, 257, 257, 16, 8, 0, 1, DIRECT), (520, 384, 384, 6, 3, 0, 1, DIRECT), (1, 1, 1, 1, 0, 0, 1, SHORT)])
+def test_batched_jacobian_path(rules, count, lo, hi, n, m, euler, pair, want):
+    slots = n + 1 + m if euler else 2 * (n + m)
+    k, ptr, _keep = _lengths(np.random.default_rng(0).integers(lo, hi + 1, count))
+    assert rules.batch_jac_of(k, ptr, n, slots, euler, pair, 256) == want

@@ -65,3 +65,26 @@ def test_quadrotor_fused_kkt_has_the_separate_calls_bits(ocp, N, bnd):
     assert torch.equal(kkt[_t(pj).long()], prob.jac(z).view(torch.int64))
     assert torch.equal(kkt[_t(ph).long()], prob.hess(z, y, 0.7).view(torch.int64))
     prob.close()
+
+
+# a batch's Jacobian tiles: one interval per lane (every instance within a
+# wavefront), one or two (even lengths, at any 8-byte offset), and whole lines
+# (from 40 MiB on)
+@pytest.mark.parametrize("Ns,n,m,scheme,bnd", [
+    ([1, 2, 16, 17, 63, 64, 33, 20], 5, 2, 0, 2), ([10, 60, 128, 1, 65], 5, 2, 1, 1),
+    ([255, 256, 257, 512, 514, 70, 1, 300], 5, 2, 0, 1), ([512, 511, 2, 130, 1026, 700], 3, 0, 1, 2),
+    ([2000, 2001, 2016, 1, 480, 497] * 20, 4, 2, 0, 1), ([2000, 2001, 2016, 1, 992, 4096] * 20, 6, 3, 1, 2)])
+def test_batched_jacobian_paths(ocp, Ns, n, m, scheme, bnd):
+    print(f"[routes] batched jacobian {Ns[:6]} x {len(Ns)} n={n} m={m} scheme={scheme} bnd={bnd}", flush=True)
+    insts = synth.make_batch(len(Ns), n, m, seed=6, Ns=Ns, scheme=scheme, bnd=bnd)
+    batch = ocp.Batch.from_instances(insts, scheme=scheme, boundary=bnd)
+    z, total = _t(synth.pack(insts)[0]), int(batch.offsets["jac"][-1])
+    want = batch.eval(z, what=ocp.EVAL_JAC, mode="per_instance")[0].view(torch.int64)
+    for block, pair, wgs in ((256, 1, 0), (128, 1, 1), (256, 0, 1)):
+        batch.config = {"block": block, "pair": pair, "wgs_per_cu": wgs, "order": 1}
+        for offset in (0, 1, 2):
+            out = Guarded(total, offset)
+            batch.eval(z, jac=out.out, what=ocp.EVAL_JAC)
+            out.values()
+            assert torch.equal(out.out.view(torch.int64), want)
+    batch.close()
