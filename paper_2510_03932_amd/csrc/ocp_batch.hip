@@ -229,6 +229,11 @@ __global__ __launch_bounds__(BS, min_waves(KINDS)) void batch_kernel(
             if (!(KINDS & (OCP_EVAL_KKT | kListKktDef))) break;
             kkt_defect_tile<BS>(P, Lo, zb, reg_ ? reg_ + id.dim_off : nullptr, kkt_ + id.kkt_off,
                                 line_pos_at(al, id.kkt_off), td.k0, bp.defect_lg, lds);
+            // the boundary rows ride in the instance's first tile: a tile of
+            // their own held its LDS for two stores (4096 instances of 20
+            // intervals, n = 16: 301 against 255 us)
+            if (td.k0 == 0 && tid < P.nb)
+                kkt_bnd_row(P, Lo, reg_ ? reg_ + id.dim_off : nullptr, kkt_ + id.kkt_off, tid);
             break;
         case kKktVar:
             if (!(KINDS & (OCP_EVAL_KKT | kListKktVar))) break;
@@ -237,13 +242,11 @@ __global__ __launch_bounds__(BS, min_waves(KINDS)) void batch_kernel(
             break;
         case kBnd: {
             const int b = tid;
-            if ((KINDS & (OCP_EVAL_CONS | OCP_EVAL_JAC | kJacDirect | OCP_EVAL_KKT | kListKktDef)) && b < P.nb) {
+            if ((KINDS & (OCP_EVAL_CONS | OCP_EVAL_JAC | kJacDirect)) && b < P.nb) {
                 if ((KINDS & OCP_EVAL_CONS) && (what & OCP_EVAL_CONS))
                     cons_[id.c_off + (int64_t)P.n * P.N + b] = bnd_value(P, zb, b);
                 if ((KINDS & (OCP_EVAL_JAC | kJacDirect)) && (what & OCP_EVAL_JAC))
                     jac_[id.jac_off + (int64_t)P.n * P.N * P.T + b] = 1.0;
-                if ((KINDS & (OCP_EVAL_KKT | kListKktDef)) && (what & OCP_EVAL_KKT))
-                    kkt_bnd_row(P, Lo, reg_ ? reg_ + id.dim_off : nullptr, kkt_ + id.kkt_off, b);
             }
             break;
         }
@@ -352,7 +355,7 @@ static std::vector<TileDesc> build_tiles(const ocp_batch &b, const ocp_batch_con
             for (int64_t k0 = 0; k0 < N; k0 += (int64_t)1 << b.bp.defect_lg) put(k0, kKktDef, 1, 0);
         if (what & (OCP_EVAL_KKT | kListKktVar))
             for (int64_t k0 = 0; k0 <= N; k0 += c.block) put(k0, kKktVar, 1, 0);
-        if (b.shape.nb > 0 && (what & (OCP_EVAL_CONS | OCP_EVAL_JAC | OCP_EVAL_KKT | kListKktDef)))
+        if (b.shape.nb > 0 && (what & (OCP_EVAL_CONS | OCP_EVAL_JAC)))
             put(0, kBnd, 1, 0);
     }
     return t;
@@ -461,7 +464,7 @@ static void launch_batch_scheme(const ocp_batch *b, const TileDesc *tiles, int n
                     : KINDS == OCP_EVAL_CONS ? b->cus * kConsWgsPerCu : ntiles;
     const unsigned grid = (unsigned)std::max(1, std::min(ntiles, cap));
     const size_t lds = ((KINDS & kListKktDef) && (what & OCP_EVAL_KKT))
-                           ? kkt_defect_lds(b->n, b->m, b->shape.T, 1 << b->bp.defect_lg) * sizeof(double)
+                           ? rules::kkt_defect_lds(b->n, b->m, b->shape.T, 1 << b->bp.defect_lg) * sizeof(double)
                            : 0;
     // where the array of the Jacobian or KKT tiles begins in its line
     const int al = line_pos(KINDS & (OCP_EVAL_JAC | kJacDirect) ? io.jac : io.kkt);
@@ -732,9 +735,8 @@ int ocp_batch_create_ex(int32_t count, const int64_t *Ns, int32_t n, int32_t m, 
     b->bp.S = shape.S;
     b->bp.scheme = scheme;
     b->bp.nb = (int)shape.nb;
-    int64_t intervals = 0;
-    for (int64_t N : b->Ns) intervals += N;
-    b->bp.defect_lg = __builtin_ctz((unsigned)kkt_defect_kt(n, m, shape.T, intervals));
+    b->bp.defect_lg = __builtin_ctz(
+        (unsigned)rules::kkt_defect_kt(n, m, shape.T, scheme != OCP_SCHEME_TRAPEZOIDAL, b->Ns.data(), count));
     b->bp.A = b->coef;
     b->bp.B = b->coef + nA;
     b->bp.gam = b->bp.B + nB;

@@ -31,6 +31,7 @@
 #include "ocp_device.h"
 #include "ocp_problem.h"
 #include "ocp_quad.h"
+#include "ocp_rules.h"
 #include "ocp_step_device.h"
 
 using namespace ocp;
@@ -80,9 +81,10 @@ hipError_t launch_eval_kkt(const KP &P, const double *z, const double *y, double
     // defect-row tiles of KT = 2^LG intervals; LDS holds the tile's states,
     // their cosines, the rows' regularization, the scaled coefficients and the
     // output row block
-    const int KT = kkt_defect_kt(P.n, P.m, P.T, P.N);
+    const int64_t N = P.N;
+    const int KT = rules::kkt_defect_kt(P.n, P.m, P.T, P.scheme != 0, &N, 1);
     const int LG = __builtin_ctz((unsigned)KT), al = line_pos(kkt);
-    const size_t lds = kkt_defect_lds(P.n, P.m, P.T, KT) * sizeof(double);
+    const size_t lds = rules::kkt_defect_lds(P.n, P.m, P.T, KT) * sizeof(double);
     hipLaunchKernelGGL(kkt_defect_kernel, dim3(blocks_for(P.N, KT)), dim3(kBlock), lds, stream, P, Lo, LG, al, z,
                        reg, kkt);
     const hipError_t e = hipGetLastError();

@@ -4,6 +4,7 @@
 #pragma once
 
 #include <algorithm>
+#include <cstddef>
 #include <cstdint>
 #include <vector>
 
@@ -60,6 +61,53 @@ inline JacPath quad_jac_path(int64_t N, uint64_t addr)
     const bool halves = N % 8 == 0 && addr % 64 == 0;
     if (fills && (!halves || bytes > 30 * kMiB)) return kJacLines;
     return halves && bytes > 12 * kMiB ? kJacPair : kJacSingle;
+}
+
+// LDS doubles of one defect-row tile of KT intervals of the fused KKT values (n
+// states, m controls, T Jacobian slots per row): states and cosines at KT+1
+// nodes, the rows' regularization, the scaled coefficients, the output row block.
+inline size_t kkt_defect_lds(int n, int m, int T, int KT)
+{
+    return 2 * (size_t)n * (KT + 1) + (size_t)n * KT + (size_t)n * (n + m) + (size_t)n + (size_t)KT * (T + 1);
+}
+
+// Intervals per defect-row tile: 16, 32 or 64, for the instances Ns evaluated
+// together (one, or a batch).  Row blocks of 64 (T + 1) entries store the
+// fewest lines in part (n = 16: 1.09 ms against 1.10 and 1.10 at N = 1e6,
+// n = 6: 0.359 against 0.383 and 0.43 at N = 2e6), but a short grid needs
+// smaller tiles to reach every CU, the sooner the more work a tile is: n = 3,
+// N = 20,000 10.0 us with 64 and 11.0 with 16; n = 4, N = 5000 11.4, with 32
+// 10.3; n = 8, N = 20,001 (forward Euler) 22.4, 19.8; n = 16, N = 20,000 55,
+// with 32 43.0, with 16 45; n = 16, N = 20,001 (forward Euler) 50, 40.8, 38.0.
+// Forward Euler stores half as much per cosine and per barrier and needs more
+// workgroups per CU to hide them: its tile gets half the LDS (n = 16, N = 1e6:
+// 0.719 ms with 32 intervals in 22 KB, 0.885 with 64 in 41 KB), and until 64 pay
+// the trapezoidal one three quarters (n = 32, N = 33,000: 245 us with 32
+// intervals in 62 KB, 225 with 16).  In a batch, a tile taller than its instance
+// computes rows that it does not store (4096 instances of 16 intervals, n = 16:
+// 327 us with 64, 229 with 16): the tile is halved while that saves a third of
+// the rows.
+constexpr size_t kDefectLdsMax = 64 * 1024;  // bytes of LDS a tile may take
+inline int kkt_defect_kt(int n, int m, int T, bool euler, const int64_t *Ns, int64_t count)
+{
+    int64_t total = 0;
+    for (int64_t i = 0; i < count; i++) total += Ns[i];
+    auto rows = [&](int KT) {
+        int64_t r = 0;
+        for (int64_t i = 0; i < count; i++) r += (Ns[i] + KT - 1) / KT * KT;
+        return r;
+    };
+    const int64_t k = total / 1024;
+    const int T1 = T + 1;
+    const int64_t from64 = T1 < 10 ? 16 : T1 < 17 ? 40 : 64, from32 = T1 < 10 ? 0 : T1 < 17 || !euler ? 16 : 32;
+    const size_t lds = euler ? kDefectLdsMax / 2 : k >= 64 ? kDefectLdsMax : kDefectLdsMax / 4 * 3;
+    auto fits = [&](int KT) { return kkt_defect_lds(n, m, T, KT) * sizeof(double) <= lds; };
+    int KT = k >= from64 ? 64 : k >= from32 ? 32 : 16;
+    while (KT > 16 && !fits(KT)) KT /= 2;
+    // instances of an even number of 16s: half the tiles for the same rows
+    if (count > 1 && KT == 16 && fits(32) && rows(32) == rows(16)) KT = 32;
+    while (KT > 16 && 2 * rows(KT) >= 3 * rows(KT / 2)) KT /= 2;
+    return KT;
 }
 
 // Jacobian tiles of a batch, one column of a run of intervals per workgroup:

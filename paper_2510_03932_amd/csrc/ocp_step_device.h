@@ -240,42 +240,6 @@ __device__ __forceinline__ int64_t kkt_bnd_start(const KP &P, const KKTLayout &L
     return kkt_cons_start(P, Lo) + (int64_t)P.n * P.N * (P.T + 1);
 }
 
-// Defect-row tiles: KT intervals per tile (a power of two, 16 to 64), chosen
-// per problem by kkt_defect_kt; each row block is computed column by column
-// into an LDS tile and copied out (see kkt_defect_tile).
-constexpr int kDefectKTMax = 64;
-constexpr size_t kDefectLdsMax = 64 * 1024;  // bytes of LDS a tile may take
-
-// LDS doubles of one defect-row tile of KT intervals (n states, m controls,
-// T Jacobian slots per row): states and cosines at KT+1 nodes, the rows'
-// diagonals, the scaled coefficients, and the output tile.
-inline size_t kkt_defect_lds(int n, int m, int T, int KT)
-{
-    return 2 * (size_t)n * (KT + 1) + (size_t)n * KT + (size_t)n * (n + m) + (size_t)n + (size_t)KT * (T + 1);
-}
-
-// Intervals per defect-row tile, for `intervals` of them in all (a batch's
-// instances together): 64 while that leaves at least kDefectTiles tiles and
-// the tile fits the LDS bound, else 32 or 16.  A tile of 64 is the best of
-// 16, 32 and 64 or within 1 % of it at n = 6, m = 3 (0.359 ms against 0.383
-// and 0.43 at N = 2e6), n = 12, m = 5 (0.232 against 0.237 and 0.237 at
-// N = 333,333) and n = 16, m = 8 (1.09 against 1.10 and 1.10 at N = 1e6): its
-// row blocks are long, so few of their lines are stored in part.  Short
-// problems take smaller tiles to reach every CU.  Forward Euler (T < 2(n+m):
-// one entry per column) stores half as much per cosine and per barrier and
-// needs more workgroups per CU to hide them, so its tile gets half the LDS:
-// at N = 1e6 and n = 16, m = 8, 32 intervals (22 KB) 0.719 ms, 64 (41 KB)
-// 0.885 and 16 0.861; at n = 12, m = 6, 64 (31 KB) 0.460, 32 0.492; at
-// n = 10, m = 4, 64 (25 KB) 0.376, 32 0.399, 16 0.466.
-constexpr int64_t kDefectTiles = 1024;  // 4 workgroups for each of the 256 CUs
-inline int kkt_defect_kt(int n, int m, int T, int64_t intervals)
-{
-    const size_t lds = T < 2 * (n + m) ? kDefectLdsMax / 2 : kDefectLdsMax;
-    int KT = kDefectKTMax;
-    while (KT > 16 && (intervals < kDefectTiles * KT || kkt_defect_lds(n, m, T, KT) * sizeof(double) > lds)) KT /= 2;
-    return KT;
-}
-
 // The entries of column c (state c < n, control c - n, or c = n + m: the
 // row's diagonal) in defect row (i, k0 + kk), into the tile row `o` (T + 1
 // entries), from the tile's LDS arrays: states xs and cosines cs at

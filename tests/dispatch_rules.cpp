@@ -20,4 +20,9 @@ int batch_jac_of(int64_t count, const int64_t *Ns, int n, int slots, int euler, 
     return batch_jac(std::vector<int64_t>(Ns, Ns + count), n, slots, euler != 0, pair != 0, block);
 }
 
+int kkt_defect_kt_of(int64_t count, const int64_t *Ns, int n, int m, int T, int euler)
+{
+    return kkt_defect_kt(n, m, T, euler != 0, Ns, count);
+}
+
 }  // extern "C"

@@ -27,6 +27,7 @@ def rules(tmp_path_factory):
     i64, i32 = ctypes.c_int64, ctypes.c_int32
     lib.jac_path_of.argtypes = [i64, i32, i32, i32, i32, ctypes.c_uint64]
     lib.quad_jac_path_of.argtypes = [i64, ctypes.c_uint64]
+    lib.kkt_defect_kt_of.argtypes = [i64, ctypes.POINTER(i64), i32, i32, i32, i32]
     lib.batch_jac_of.argtypes = [i64, ctypes.POINTER(i64), i32, i32, i32, i32, i32]
     return lib
 
@@ -80,3 +81,19 @@ def test_batched_jacobian_path(rules, count, lo, hi, n, m, euler, pair, want):
     slots = n + 1 + m if euler else 2 * (n + m)
     k, ptr, _keep = _lengths(np.random.default_rng(0).integers(lo, hi + 1, count))
     assert rules.batch_jac_of(k, ptr, n, slots, euler, pair, 256) == want
+
+
+@pytest.mark.parametrize("count,lo,hi,n,m,euler,want", [
+    # one instance: by its length and the work of a tile
+    (1, 20000, 20000, 3, 1, 0, 64), (1, 10000, 10000, 2, 1, 0, 32), (1, 5000, 5000, 4, 2, 0, 16),
+    (1, 20000, 20000, 4, 2, 0, 32), (1, 41000, 41000, 4, 2, 0, 64), (1, 20000, 20000, 16, 8, 0, 32),
+    (1, 20001, 20001, 16, 8, 1, 16), (1, 10000, 10000, 12, 5, 0, 16), (1, 333333, 333333, 12, 5, 0, 64),
+    (1, 1000000, 1000000, 16, 8, 0, 64), (1, 1000000, 1000000, 16, 8, 1, 32), (1, 33000, 33000, 32, 16, 0, 16),
+    # a batch: by the length of its instances too
+    (4096, 16, 16, 16, 8, 0, 16), (4096, 16, 16, 6, 3, 0, 16), (4096, 5, 5, 12, 5, 1, 16), (4096, 20, 20, 12, 5, 0, 32),
+    (4096, 33, 33, 6, 3, 0, 64), (4096, 10, 60, 6, 3, 0, 64), (1024, 20, 20, 16, 8, 0, 32), (300, 200, 200, 4, 2, 1, 64),
+    (300, 16, 16, 16, 8, 0, 16), (512, 200, 20000, 6, 3, 0, 64), (1, 1, 1, 1, 1, 1, 16)])
+def test_kkt_defect_tile(rules, count, lo, hi, n, m, euler, want):
+    T = n + 1 + m if euler else 2 * (n + m)
+    k, ptr, _keep = _lengths(np.random.default_rng(0).integers(lo, hi + 1, count))
+    assert rules.kkt_defect_kt_of(k, ptr, n, m, T, euler) == want

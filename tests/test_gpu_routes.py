@@ -88,3 +88,26 @@ def test_batched_jacobian_paths(ocp, Ns, n, m, scheme, bnd):
             out.values()
             assert torch.equal(out.out.view(torch.int64), want)
     batch.close()
+
+
+# a batch's defect-row tiles of 16, 32 and 64 intervals over instances shorter
+# and longer than a tile; the boundary rows ride in an instance's first tile
+@pytest.mark.parametrize("Ns,n,m,scheme,bnd", [
+    ([1, 15, 16, 17, 5], 6, 3, 0, 2), ([20] * 30 + [31, 32, 1], 6, 3, 1, 1), ([32, 64, 20, 30], 16, 8, 0, 2),
+    ([200, 1, 63, 64, 65, 7000, 9000], 3, 1, 0, 2), ([2049, 64, 127, 15000, 1], 4, 2, 1, 2),
+    ([40000, 25500, 65, 64, 1, 16], 12, 5, 0, 1), ([33000, 1, 32800, 5], 24, 10, 0, 2)])
+def test_batched_kkt_tiles(ocp, Ns, n, m, scheme, bnd):
+    print(f"[routes] batched kkt {Ns[:6]} x {len(Ns)} n={n} m={m} scheme={scheme} bnd={bnd}", flush=True)
+    insts = synth.make_batch(len(Ns), n, m, seed=7, Ns=Ns, scheme=scheme, bnd=bnd)
+    batch = ocp.Batch.from_instances(insts, scheme=scheme, boundary=bnd)
+    z, y = (_t(a) for a in synth.pack(insts))
+    reg = _t(np.random.default_rng(5).normal(size=int(batch.offsets["dim"][-1])))
+    for r in (None, reg):
+        want = batch.step(z, y, 0.7, r, what=ocp.EVAL_KKT, mode="per_instance")["kkt"].view(torch.int64)
+        for block in (128, 256):
+            batch.config = {"block": block, "pair": 1, "wgs_per_cu": 0, "order": 1}
+            out = Guarded(int(batch.offsets["kkt"][-1]), 3)
+            batch.step(z, y, 0.7, r, what=ocp.EVAL_KKT, out={"kkt": out.out})
+            out.values()
+            assert torch.equal(out.out.view(torch.int64), want)
+    batch.close()
