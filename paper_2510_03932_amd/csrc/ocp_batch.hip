@@ -54,9 +54,10 @@ constexpr int kMasks = 256;    // tile-list keys: evaluation masks 1 .. OCP_EVAL
 // Tile-list keys of the two KKT groups (outside the OCP_EVAL_* bits): the
 // defect-row tiles (with the boundary rows), and the variable-row tiles.
 constexpr int kListKktDef = 64, kListKktVar = 128;
-// A kernel instantiation only (its lists have the key OCP_EVAL_JAC): Jacobian
-// tiles of one or two intervals per lane, at the registers the compiler takes.
-constexpr int kJacDirect = 256;
+// Kernel instantiations only (their lists have the keys OCP_EVAL_JAC and
+// OCP_EVAL_OBJ | OCP_EVAL_GRAD): Jacobian tiles of one or two intervals per
+// lane; objective and gradient tiles that load each node once.
+constexpr int kJacDirect = 256, kObjGradOnce = 512;
 
 // One instance's place in the packed arrays (device copy of the offset table).
 struct InstDesc {
@@ -67,7 +68,7 @@ struct InstDesc {
     double h, hh;
 };
 
-enum TileKind : int16_t { kJac = 0, kHess, kCons, kObjGrad, kKktDef, kKktVar, kBnd };
+enum TileKind : int16_t { kJac = 0, kHess, kCons, kGrad, kObj, kObjGrad, kKktDef, kKktVar, kBnd };
 
 // One unit of work of the persistent kernel.
 struct TileDesc {
@@ -209,20 +210,32 @@ __global__ __launch_bounds__(BS, min_waves(KINDS)) void batch_kernel(
             }
             break;
         }
+        case kGrad: {
+            if (!(KINDS & OCP_EVAL_GRAD)) break;
+            const int64_t k = td.k0 + (int64_t)tid;
+            if (k <= P.N) {
+                double *gb = grad_ + id.z_off;
+                for (int c = 0; c < P.n + P.m; c++)
+                    if (c < P.n || k < P.NU) grad_entry(P, zb, gb, c, k);
+            }
+            break;
+        }
+        case kObj:
         case kObjGrad: {
-            if (!(KINDS & (OCP_EVAL_OBJ | OCP_EVAL_GRAD))) break;
-            double *gb = what & OCP_EVAL_GRAD ? grad_ + id.z_off : nullptr;
+            if (!(KINDS & (OCP_EVAL_OBJ | kObjGradOnce))) break;
             double v[256 / BS];
 #pragma unroll
             for (int r = 0; r < 256 / BS; r++) {
                 const int64_t k = td.k0 + tid + r * BS;
-                v[r] = k < P.N1 ? obj_grad_node<NB>(P, zb, gb, k) : 0.0;
+                v[r] = 0.0;
+                if (k < P.N1) {
+                    if constexpr (KINDS == kObjGradOnce) v[r] = obj_grad_node<NB>(P, zb, grad_ + id.z_off, k);
+                    else v[r] = obj_node<NB>(P, zb, k);
+                }
             }
-            if (what & OCP_EVAL_OBJ) {
-                const double s = sum256<BS>(v, ws);
-                if (tid == 0) parts_[id.part0 + td.k0 / kObjTile] = s;
-                __syncthreads();  // ws is reused by the next tile
-            }
+            const double s = sum256<BS>(v, ws);
+            if (tid == 0) parts_[id.part0 + td.k0 / kObjTile] = s;
+            __syncthreads();  // ws is reused by the next tile
             break;
         }
         case kKktDef:
@@ -288,6 +301,7 @@ struct ocp_batch {
     mutable std::mutex mu;         // guards the tile-list cache
     mutable TileList lists[kMasks];  // per evaluation mask, for cfg
     bool jac_direct = false;         // the Jacobian tiles of cfg are those of kJacDirect
+    bool obj_grad_once = false;      // objective and gradient together take the tiles of kObjGradOnce
     ocp_batch_config cfg{256, 1, 0, 1};
     BP bp{};
     KKTLayout Lo{};
@@ -349,8 +363,11 @@ static std::vector<TileDesc> build_tiles(const ocp_batch &b, const ocp_batch_con
             const int64_t span = euler ? c.block : 63 * (c.block / 64);  // 63 intervals per wavefront
             for (int64_t k0 = 0; k0 < N; k0 += span) put(k0, kCons, 1, 0);
         }
-        if (what & (OCP_EVAL_OBJ | OCP_EVAL_GRAD))
-            for (int64_t k0 = 0; k0 <= N; k0 += kObjTile) put(k0, kObjGrad, 1, 0);
+        const bool once = b.obj_grad_once && what == (OCP_EVAL_OBJ | OCP_EVAL_GRAD);
+        if ((what & OCP_EVAL_GRAD) && !once)
+            for (int64_t k0 = 0; k0 <= N; k0 += c.block) put(k0, kGrad, 1, 0);
+        if (what & OCP_EVAL_OBJ)
+            for (int64_t k0 = 0; k0 <= N; k0 += kObjTile) put(k0, once ? kObjGrad : kObj, 1, 0);
         if (what & (OCP_EVAL_KKT | kListKktDef))
             for (int64_t k0 = 0; k0 < N; k0 += (int64_t)1 << b.bp.defect_lg) put(k0, kKktDef, 1, 0);
         if (what & (OCP_EVAL_KKT | kListKktVar))
@@ -498,7 +515,11 @@ static void launch_batch_bs(const ocp_batch *b, int g, const TileDesc *tiles, in
         else launch_batch_kinds<BS, kGroupKinds[0]>(b, tiles, ntiles, what, io, s);
         break;
     case 1: launch_batch_kinds<BS, kGroupKinds[1]>(b, tiles, ntiles, what, io, s); break;
-    case 2: launch_batch_kinds<BS, kGroupKinds[2]>(b, tiles, ntiles, what, io, s); break;
+    case 2:
+        if (b->obj_grad_once && what == kGroupBits[2])
+            launch_batch_kinds<BS, kObjGradOnce>(b, tiles, ntiles, what, io, s);
+        else launch_batch_kinds<BS, kGroupKinds[2]>(b, tiles, ntiles, what, io, s);
+        break;
     case 3: launch_batch_kinds<BS, kGroupKinds[3]>(b, tiles, ntiles, what, io, s); break;
     case 4: launch_batch_kinds<BS, kGroupKinds[4]>(b, tiles, ntiles, what, io, s); break;
     default: launch_batch_kinds<BS, kGroupKinds[5]>(b, tiles, ntiles, what, io, s); break;
@@ -746,6 +767,7 @@ int ocp_batch_create_ex(int32_t count, const int64_t *Ns, int32_t n, int32_t m, 
     b->bp.BT = b->bp.AT + nAT;
     b->Lo = kkt_layout(n);
     b->jac_direct = jac_path_of(*b, b->cfg) == rules::kBatchDirect;
+    b->obj_grad_once = rules::batch_obj_grad_once(b->Ns);
     TileList l;
     rc = tile_list(b, OCP_EVAL_JAC, &l);
     if (rc) {

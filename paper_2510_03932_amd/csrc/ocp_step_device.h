@@ -101,6 +101,16 @@ __device__ __forceinline__ void grad_row(const KP &P, const double *__restrict__
     if (k >= 0 && k < len) st_nt(g + row + k, 2.0 * node_weight(P, (int)k) * coef * z[row + k]);
 }
 
+// One entry of it, at node k of component comp (a node the component has).
+__device__ __forceinline__ void grad_entry(const KP &P, const double *__restrict__ z, double *__restrict__ g,
+                                           int comp, int64_t k)
+{
+    const double coef = comp < P.n ? P.q[comp] : P.r[comp - P.n];
+    const int64_t e = comp < P.n ? (int64_t)comp * P.N1 + k
+                                 : (int64_t)P.n * P.N1 + (int64_t)(comp - P.n) * P.NU + k;
+    st_nt(g + e, 2.0 * node_weight(P, (int)k) * coef * z[e]);
+}
+
 // The objective's term of node k: w_k (sum_j q_j X_jk^2 + sum_l r_l U_lk^2),
 // states first (every load issued before the sum), then the controls in
 // groups of NB, each in component order.  (Loading the controls together
@@ -131,44 +141,48 @@ __device__ __forceinline__ double obj_node(const KP &P, const double *__restrict
 }
 
 // The objective's term of node k, as obj_node gives it, and the node's gradient
-// entries into g (skipped when null), as grad_row gives them, from one load of
-// the node's values.  Both are bound by memory: one kernel tile that loads each
-// node once takes 150 us for the objectives and gradients of 512 instances
-// (n = 6, m = 3, 5.2 TB/s), a tile of its own for each 211 us, and one tile with
-// two passes over its nodes, the second in whole lines, 202 us.
+// entries into g, as grad_row gives them, from one load of the node's values.
+// Both are bound by memory: one kernel tile that loads each node once takes
+// 150 us for the objectives and gradients of 512 instances (n = 6, m = 3,
+// 5.2 TB/s), a tile of its own for each 211 us, and one tile with two passes
+// over its nodes, the second in whole lines, 202 us.  (See rules::batch_obj_grad
+// for the batches that take it.)
 template <int NB>
 __device__ __forceinline__ double obj_grad_node(const KP &P, const double *__restrict__ z, double *__restrict__ g,
                                                 int64_t k)
 {
+    // up to 16 states the first controls are loaded with them; above, their
+    // registers cost more than the wait (2048 instances of 50 to 200: n = 12 18
+    // against 20 us, n = 24 48 against 42.5)
+    constexpr bool kEarly = NB <= 16;
     const int n = P.n, m = P.m;
     const int64_t N1 = P.N1, NU = P.NU, ub = (int64_t)n * N1 + k;
     const bool ctrl = k < NU;
     const double w = node_weight(P, (int)k);
-    double v[NB], u[NB];
+    double v[NB], u[kEarly ? NB : 1];
 #pragma unroll
     for (int c = 0; c < NB; c++) {
         v[c] = c < n ? z[c * N1 + k] : 0.0;
-        u[c] = c < m && ctrl ? z[ub + c * NU] : 0.0;
+        if (kEarly) u[kEarly ? c : 0] = c < m && ctrl ? z[ub + c * NU] : 0.0;
     }
     double s = 0.0;
 #pragma unroll
     for (int c = 0; c < NB; c++) {
         if (c < n) {
             s += P.q[c] * v[c] * v[c];
-            if (g) st_nt(g + c * N1 + k, 2.0 * w * P.q[c] * v[c]);
+            st_nt(g + c * N1 + k, 2.0 * w * P.q[c] * v[c]);
         }
     }
     if (ctrl) {
         for (int l0 = 0; l0 < m; l0 += NB) {
-            if (l0 > 0) {
 #pragma unroll
-                for (int c = 0; c < NB; c++) u[c] = l0 + c < m ? z[ub + (l0 + c) * NU] : 0.0;
-            }
+            for (int c = 0; c < NB; c++)
+                v[c] = kEarly && l0 == 0 ? u[kEarly ? c : 0] : l0 + c < m ? z[ub + (l0 + c) * NU] : 0.0;
 #pragma unroll
             for (int c = 0; c < NB; c++) {
                 if (l0 + c < m) {
-                    s += P.r[l0 + c] * u[c] * u[c];
-                    if (g) st_nt(g + ub + (l0 + c) * NU, 2.0 * w * P.r[l0 + c] * u[c]);
+                    s += P.r[l0 + c] * v[c] * v[c];
+                    st_nt(g + ub + (l0 + c) * NU, 2.0 * w * P.r[l0 + c] * v[c]);
                 }
             }
         }

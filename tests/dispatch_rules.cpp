@@ -25,4 +25,9 @@ int kkt_defect_kt_of(int64_t count, const int64_t *Ns, int n, int m, int T, int 
     return kkt_defect_kt(n, m, T, euler != 0, Ns, count);
 }
 
+int batch_obj_grad_once_of(int64_t count, const int64_t *Ns)
+{
+    return batch_obj_grad_once(std::vector<int64_t>(Ns, Ns + count));
+}
+
 }  // extern "C"

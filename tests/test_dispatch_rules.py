@@ -28,6 +28,7 @@ def rules(tmp_path_factory):
     lib.jac_path_of.argtypes = [i64, i32, i32, i32, i32, ctypes.c_uint64]
     lib.quad_jac_path_of.argtypes = [i64, ctypes.c_uint64]
     lib.kkt_defect_kt_of.argtypes = [i64, ctypes.POINTER(i64), i32, i32, i32, i32]
+    lib.batch_obj_grad_once_of.argtypes = [i64, ctypes.POINTER(i64)]
     lib.batch_jac_of.argtypes = [i64, ctypes.POINTER(i64), i32, i32, i32, i32, i32]
     return lib
 
@@ -97,3 +98,20 @@ def test_kkt_defect_tile(rules, count, lo, hi, n, m, euler, want):
     T = n + 1 + m if euler else 2 * (n + m)
     k, ptr, _keep = _lengths(np.random.default_rng(0).integers(lo, hi + 1, count))
     assert rules.kkt_defect_kt_of(k, ptr, n, m, T, euler) == want
+
+
+@pytest.mark.parametrize("count,N,once", [(1, 1, 0), (256, 255, 0), (256, 256, 1), (257, 1, 1), (1, 65535, 0),
+                                          (1, 65536, 1), (512, 10000, 1)])
+def test_batched_objective_and_gradient_tiles(rules, count, N, once):
+    k, ptr, _keep = _lengths(np.full(count, N))
+    assert rules.batch_obj_grad_once_of(k, ptr) == once
+
+
+def test_kernels_look_at_no_address():
+    """Addresses become integers on the host only (line_pos, the Jacobian's
+    path): in a kernel they cost the coefficients the scalar cache."""
+    csrc = os.path.join(ROOT, "paper_2510_03932_amd", "csrc")
+    hits = [line.strip() for name in sorted(os.listdir(csrc)) if name.endswith((".hip", ".h"))
+            for line in open(os.path.join(csrc, name)) if "uintptr_t" in line]
+    allowed = ("inline int line_pos(const double *p)", "switch (rules::jac_path(", "switch (rules::quad_jac_path(")
+    assert len(hits) == 3 and all(h.startswith(allowed) for h in hits), hits

@@ -111,3 +111,30 @@ def test_batched_kkt_tiles(ocp, Ns, n, m, scheme, bnd):
             out.values()
             assert torch.equal(out.out.view(torch.int64), want)
     batch.close()
+
+
+# objective and gradient: tiles of their own up to 256 tiles and for a mask of
+# one, tiles that load each node once above; controls in groups of the state
+# bound, with and after the states
+@pytest.mark.parametrize("Ns,n,m,scheme", [
+    ([255, 256, 1, 20] * 3, 3, 9, 0), ([255, 256, 1, 20] * 70, 3, 9, 0), ([511, 512, 7] * 60, 8, 4, 1),
+    ([70000], 12, 5, 0), ([40, 300] * 90, 16, 17, 1), ([40, 257] * 90, 24, 10, 0)])
+def test_batched_objective_and_gradient(ocp, Ns, n, m, scheme):
+    print(f"[routes] batched obj+grad {Ns[:4]} x {len(Ns)} n={n} m={m} scheme={scheme}", flush=True)
+    insts = synth.make_batch(len(Ns), n, m, seed=8, Ns=Ns, scheme=scheme)
+    batch = ocp.Batch.from_instances(insts, scheme=scheme)
+    z = _t(synth.pack(insts)[0])
+    both = ocp.EVAL_OBJ | ocp.EVAL_GRAD
+    ref = batch.step(z, what=both, mode="per_instance")
+    for block in (128, 256):
+        for wgs in (0, 1):
+            batch.config = {"block": block, "pair": 1, "wgs_per_cu": wgs, "order": 1}
+            for what in (both, ocp.EVAL_OBJ, ocp.EVAL_GRAD):
+                g = Guarded(int(batch.offsets["z"][-1]), 5)
+                got = batch.step(z, what=what, out={"grad": g.out})
+                if what & ocp.EVAL_OBJ:
+                    assert torch.equal(got["obj"].view(torch.int64), ref["obj"].view(torch.int64))
+                if what & ocp.EVAL_GRAD:
+                    g.values()
+                    assert torch.equal(g.out.view(torch.int64), ref["grad"].view(torch.int64))
+    batch.close()
