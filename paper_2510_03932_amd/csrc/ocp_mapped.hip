@@ -17,10 +17,10 @@
 // once and later assemblies skip the first pass.
 //
 // Reading bounds it: a tile takes KT consecutive values and slots of every
-// slot row, runs of 64 to 256 bytes that share their 128-byte lines with the
-// neighbouring tiles.  Each XCD therefore takes a contiguous run of the tiles,
-// so that a line fetched for one tile is found in the L2 by the next.  With
-// that, four entries in flight per lane and tiles of twice the height (runs of
+// slot row, runs that share their 128-byte lines with the neighbouring tiles
+// (64 bytes at 8 nodes, whole lines and more only from 16 nodes on).  Each XCD therefore takes a
+// contiguous run of the tiles, so that a line fetched for one tile is found in
+// the L2 by the next.  With that, four entries in flight per lane and tiles of twice the height (runs of
 // 128 bytes at n = 8, m = 4), against tiles dealt round-robin over the XCDs:
 // 159 -> 81 us at N = 1e5, n = 8, m = 4 (2.8 -> 5.6 TB/s), 94 -> 38 us at
 // N = 60,361, n = 10, m = 5 (Euler), 279 -> 115 us at N = 22,869, n = 18,
@@ -38,16 +38,14 @@
 #include "ocp_problem.h"
 #include "ocp_quad.h"
 #include "ocp_quad_model.h"
+#include "ocp_rules.h"
 
 using namespace ocp;
 using namespace ocp::dev;
 
 namespace {
 
-constexpr int kMapTarget = 4096;       // values staged per workgroup (32 KiB of LDS)
-constexpr int kMapTargetSmall = 2048;  // the same for grids too short to give every CU two such tiles
-constexpr int kMapCap = 9216;          // most values staged per workgroup (72 KiB, two workgroups per CU)
-constexpr int kMapBatch = 4;           // Jacobian entries in flight per lane
+constexpr int kMapBatch = 4;  // Jacobian entries in flight per lane
 
 struct MP {
     int N, N1, NU;
@@ -223,7 +221,7 @@ __global__ __launch_bounds__(kBlock) void mapped_assemble_kernel(
     const int32_t *__restrict__ perm_h, const int32_t *__restrict__ diag, const double *__restrict__ jv,
     const double *__restrict__ hv, const double *__restrict__ reg, double *__restrict__ kkt)
 {
-    extern __shared__ double tile[];  // the tile's entries (host-sized, <= kMapCap)
+    extern __shared__ double tile[];  // the tile's entries (host-sized, <= rules::kMapCap)
     __shared__ int filled;            // tile slots written by this tile's entries
     const uint32_t tb = xcd_order(blockIdx.x, gridDim.x);
     int base, count;
@@ -268,11 +266,6 @@ __global__ __launch_bounds__(kBlock) void mapped_assemble_kernel(
     });
 }
 
-// Tile shape for a handle: the largest power of two of nodes whose entries
-// fit a 32 KiB tile (five workgroups per CU), 16 KiB where that would leave
-// fewer than two tiles per CU, but at least 8 nodes (half a line of values)
-// while they fit the 72 KiB maximum: at n = 18, m = 10, 8 nodes in 69 KiB take
-// 115 us and 4 nodes 148 us (N = 22,869).
 MP make_mp(const ocp_problem *p)
 {
     const Dims &d = p->d;
@@ -295,15 +288,10 @@ MP make_mp(const ocp_problem *p)
     P.nnzj_def = d.nnzj_def;
     P.nnzk = (int)d.nnzk;
     const int64_t per_node = (int64_t)P.nJ + P.sA + P.sB + P.n;
-    auto need = [&](int lgk) { return ((int64_t)1 << lgk) * per_node + 2 * P.n; };
-    int lg = 0;
-    while (lg < 10 && need(lg + 1) <= kMapTargetSmall) lg++;
-    const bool many = (P.N1 >> (lg + 1)) >= 512;
-    while (many && lg < 10 && need(lg + 1) <= kMapTarget) lg++;
-    while (lg < 3 && need(lg + 1) <= kMapCap) lg++;
+    const int lg = rules::map_lg(P.N1, per_node, P.n);
     P.KT = 1 << lg;
     P.lgKT = lg;
-    P.cap = (int)need(lg);
+    P.cap = (int)(((int64_t)per_node << lg) + 2 * P.n);
     return P;
 }
 
@@ -372,7 +360,7 @@ int ocp_assemble_kkt_mapped(const ocp_problem *p, const int32_t *perm_j, const i
         // call, since the attribute belongs to the current device
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(mapped_assemble_kernel),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 kMapCap * (int)sizeof(double));
+                                                 rules::kMapCap * (int)sizeof(double));
         if (e != hipSuccess) return hip_fail("ocp_assemble_kkt_mapped: LDS size", e);
     }
     hipLaunchKernelGGL(mapped_assemble_kernel, dim3(blocks_for(p->d.N1, P.KT)), dim3(kBlock),

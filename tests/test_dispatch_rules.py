@@ -29,6 +29,7 @@ def rules(tmp_path_factory):
     lib.quad_jac_path_of.argtypes = [i64, ctypes.c_uint64]
     lib.kkt_defect_kt_of.argtypes = [i64, ctypes.POINTER(i64), i32, i32, i32, i32]
     lib.batch_obj_grad_once_of.argtypes = [i64, ctypes.POINTER(i64)]
+    lib.map_lg_of.argtypes = [i64, i64, i32]
     lib.batch_jac_of.argtypes = [i64, ctypes.POINTER(i64), i32, i32, i32, i32, i32]
     return lib
 
@@ -105,6 +106,22 @@ def test_kkt_defect_tile(rules, count, lo, hi, n, m, euler, want):
 def test_batched_objective_and_gradient_tiles(rules, count, N, once):
     k, ptr, _keep = _lengths(np.full(count, N))
     assert rules.batch_obj_grad_once_of(k, ptr) == once
+
+
+@pytest.mark.parametrize("N,n,m,euler,lg", [
+    # short grids: tiles small enough to reach every CU
+    (50, 18, 10, 0, 0), (100, 18, 10, 1, 1), (500, 18, 10, 0, 1), (1000, 18, 10, 0, 2), (2000, 18, 10, 0, 2),
+    (100, 12, 6, 0, 2), (2000, 12, 6, 0, 2), (100, 8, 4, 0, 3), (1, 1, 0, 0, 8), (100, 24, 12, 1, 1),
+    (50, 32, 32, 0, 0), (100, 32, 32, 1, 0),
+    # long ones: half a line of values per slot row, as far as 72 KiB go
+    (4000, 18, 10, 0, 3), (3500, 12, 6, 0, 3), (500, 32, 32, 0, 1), (100000, 8, 4, 0, 4), (100000, 32, 32, 0, 1),
+    (100000, 32, 32, 1, 2), (1000000, 2, 1, 0, 7), (100000, 1, 0, 1, 8)])
+def test_mapped_assembly_tile(rules, N, n, m, euler, lg):
+    slots = n + 1 + m if euler else 2 * (n + m)
+    pairs = 0 if n < 2 else (1 if n == 2 else n)
+    per_node = n * slots + n + pairs + m + n
+    assert rules.map_lg_of(N + 1, per_node, n) == lg
+    assert (per_node << lg) + 2 * n <= 9216
 
 
 def test_kernels_look_at_no_address():

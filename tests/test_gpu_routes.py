@@ -113,6 +113,29 @@ def test_batched_kkt_tiles(ocp, Ns, n, m, scheme, bnd):
     batch.close()
 
 
+# the mapped assembly's tiles of 1, 2, 4 and 8 nodes, shorter on a short grid
+@pytest.mark.parametrize("N,n,m,scheme,bnd", [
+    (499, 18, 10, 0, 1), (997, 18, 10, 0, 2), (1001, 18, 10, 0, 0), (3201, 18, 10, 0, 2), (101, 12, 6, 0, 2),
+    (1, 32, 32, 0, 2), (249, 32, 32, 0, 1), (503, 32, 32, 1, 0), (2, 24, 12, 1, 2)])
+def test_mapped_assembly_on_short_grids(ocp, N, n, m, scheme, bnd):
+    print(f"[routes] mapped N={N} n={n} m={m} scheme={scheme} bnd={bnd}", flush=True)
+    inst = synth.make_instance(N, n, m, seed=84, bnd=bnd, scheme=scheme)
+    prob = ocp.Problem.from_instance(inst, torch.device("cuda", 0))
+    s = prob.sizes
+    rng = np.random.default_rng(4)
+    jv, hv, reg = (rng.normal(size=s[k]) for k in ("nnzj", "nnzh", "dim"))
+    pj2, ph2, dg2 = ocp.kkt_permute(*prob.kkt_pattern(), ocp.stage_order(N, n, m, scheme, bnd))[2:]
+    shuffled = rng.permutation(s["nnzk"]).astype(np.int32)
+    for maps in ((pj2, ph2, dg2), tuple(shuffled[q] for q in (pj2, ph2, dg2))):
+        dmaps = [_t(q) for q in maps]
+        want = oracle.assemble_mapped(s["nnzk"], maps[2], maps[0], jv, maps[1], hv, reg)
+        for plan in (None, prob.mapped_plan(*dmaps)):
+            out = Guarded(s["nnzk"], 3)
+            prob.assemble_kkt_mapped(*dmaps, _t(jv), _t(hv), _t(reg), out=out.out, plan=plan)
+            assert np.array_equal(out.values().view(np.uint64), want.view(np.uint64))
+    prob.close()
+
+
 # objective and gradient: tiles of their own up to 256 tiles and for a mask of
 # one, tiles that load each node once above; controls in groups of the state
 # bound, with and after the states
