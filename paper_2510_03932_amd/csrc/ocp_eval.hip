@@ -614,13 +614,8 @@ int ocp_assemble_kkt(const ocp_problem *p, const int32_t *perm_j, const int32_t 
         return fail(OCP_ERR_ARG, "ocp_assemble_kkt: null array");
     if (p->model == quad::kModel)
         return quad::assemble_kkt(p, perm_j, perm_h, rowptr, jvals, hvals, reg, kkt, stream);
-    // Tile height: 128 constraint rows while the staged CSR range fits in
-    // 64 KiB of LDS, else 64 or 32; shorter while that leaves fewer than two
-    // tiles per CU (a small problem is bound by the latency of one tile).
-    int LG = 7;
-    auto tiles = [&] { return ((p->d.N + (1 << LG) - 1) >> LG) * p->d.n; };
-    while (LG > 5 && (((size_t)(p->d.T + 1) << LG) * sizeof(double) > 64 * 1024 || tiles() < 512)) LG--;
-    const unsigned gj = (unsigned)tiles();
+    const int LG = rules::assembly_lg(p->d.N, p->d.n, p->d.T);
+    const unsigned gj = (unsigned)(((p->d.N + (1 << LG) - 1) >> LG) * p->d.n);
     const unsigned gh = blocks_for(p->d.N1, kBlock);
     const unsigned gb = blocks_for(p->d.nb, kBlock);
     const size_t lds = ((size_t)(p->d.T + 1) << LG) * sizeof(double);

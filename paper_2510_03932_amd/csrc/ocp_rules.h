@@ -165,6 +165,21 @@ inline bool batch_obj_grad_once(const std::vector<int64_t> &Ns)
     return tiles > 256;
 }
 
+// log2 of the constraint rows per tile of the assembly: 128 rows while their
+// T + 1 entries each fit 64 KiB of LDS, else 64 or 32, and fewer where that
+// leaves most CUs without a tile.  From 128 tiles on the taller ones win (128
+// rows against 64 or 32: n = 4, N = 16,000 6.7 us and 7.5; n = 8, N = 4000 8.1
+// and 8.4; n = 16, N = 1000 11.2 and 12.2; n = 2, N = 16,000 5.5 and 5.9),
+// below that the shorter (n = 4, N = 1000: 5.4 and 5.1; n = 2, N = 4000: 5.3
+// and 5.0).
+inline int assembly_lg(int64_t N, int n, int T)
+{
+    int lg = 7;
+    auto tiles = [&] { return ((N + (1 << lg) - 1) >> lg) * n; };
+    while (lg > 5 && (((size_t)(T + 1) << lg) * sizeof(double) > 64 * 1024 || tiles() < 128)) lg--;
+    return lg;
+}
+
 // log2 of the nodes per tile of the mapped assembly, for N1 nodes of `per_node`
 // entries (and 2 n that overhang): as many as fit 16 KiB of values, 32 KiB
 // (five workgroups per CU) where that leaves two tiles per CU, and up to 8

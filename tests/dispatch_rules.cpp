@@ -30,6 +30,8 @@ int batch_obj_grad_once_of(int64_t count, const int64_t *Ns)
     return batch_obj_grad_once(std::vector<int64_t>(Ns, Ns + count));
 }
 
+int assembly_lg_of(int64_t N, int n, int T) { return assembly_lg(N, n, T); }
+
 int map_lg_of(int64_t N1, int64_t per_node, int n) { return map_lg(N1, per_node, n); }
 
 }  // extern "C"

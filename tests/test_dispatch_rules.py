@@ -29,6 +29,7 @@ def rules(tmp_path_factory):
     lib.quad_jac_path_of.argtypes = [i64, ctypes.c_uint64]
     lib.kkt_defect_kt_of.argtypes = [i64, ctypes.POINTER(i64), i32, i32, i32, i32]
     lib.batch_obj_grad_once_of.argtypes = [i64, ctypes.POINTER(i64)]
+    lib.assembly_lg_of.argtypes = [i64, i32, i32]
     lib.map_lg_of.argtypes = [i64, i64, i32]
     lib.batch_jac_of.argtypes = [i64, ctypes.POINTER(i64), i32, i32, i32, i32, i32]
     return lib
@@ -122,6 +123,18 @@ def test_mapped_assembly_tile(rules, N, n, m, euler, lg):
     per_node = n * slots + n + pairs + m + n
     assert rules.map_lg_of(N + 1, per_node, n) == lg
     assert (per_node << lg) + 2 * n <= 9216
+
+
+@pytest.mark.parametrize("N,n,m,euler,lg", [
+    # fewer than 128 tiles: shorter ones
+    (1000, 4, 2, 0, 5), (4000, 2, 1, 0, 5), (1000, 8, 4, 0, 6), (300, 8, 4, 0, 5), (1, 1, 0, 0, 5), (992, 8, 4, 1, 6),
+    # from there on as tall as 64 KiB allow
+    (2000, 8, 4, 0, 7), (16000, 4, 2, 0, 7), (16000, 2, 1, 0, 7), (16257, 1, 0, 0, 7), (16256, 1, 0, 0, 6),
+    (1000, 16, 8, 0, 7), (1000, 32, 16, 0, 6), (1000, 32, 32, 0, 5), (1000000, 24, 10, 0, 6)])
+def test_assembly_tile(rules, N, n, m, euler, lg):
+    T = n + 1 + m if euler else 2 * (n + m)
+    assert rules.assembly_lg_of(N, n, T) == lg
+    assert (T + 1) * 8 << lg <= 64 * 1024
 
 
 def test_kernels_look_at_no_address():

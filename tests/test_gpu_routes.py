@@ -113,6 +113,32 @@ def test_batched_kkt_tiles(ocp, Ns, n, m, scheme, bnd):
     batch.close()
 
 
+# the assembly's tiles of 32, 64 and 128 rows, and an injective map under which
+# no tile covers its range: a row's entry in each run of 32 rows goes to the next
+@pytest.mark.parametrize("N,n,m,scheme,bnd", [
+    (1000, 4, 2, 0, 0), (1001, 8, 4, 0, 1), (2065, 8, 4, 1, 2), (16257, 1, 0, 0, 1), (700, 32, 32, 0, 2), (33, 3, 1, 1, 0)])
+def test_assembly_without_a_covering_tile(ocp, N, n, m, scheme, bnd):
+    print(f"[routes] assembly N={N} n={n} m={m} scheme={scheme} bnd={bnd}", flush=True)
+    inst = synth.make_instance(N, n, m, seed=85, bnd=bnd, scheme=scheme)
+    prob = ocp.Problem.from_instance(inst, torch.device("cuda", 0))
+    s = prob.sizes
+    rng = np.random.default_rng(6)
+    jv, hv, reg = (rng.normal(size=s[k]) for k in ("nnzj", "nnzh", "dim"))
+    rp, _, pj, ph = prob.kkt_pattern()
+    T = (s["nnzj"] - bnd * n) // (n * N)
+    one = np.concatenate([i * T * N + np.arange(0, N, 32) for i in range(n)])  # slot row 0 of each component
+    rotated = pj.copy()
+    rotated[one] = np.roll(pj[one], 1)
+    assert len(np.unique(rotated)) == len(rotated)
+    for maps in (pj, rotated):
+        for r in (None, reg):
+            out = Guarded(s["nnzk"], 1)
+            prob.assemble_kkt(_t(maps), _t(ph), _t(rp), _t(jv), _t(hv), None if r is None else _t(r), out=out.out)
+            want = oracle.assemble(rp, maps, jv, ph, hv, r)
+            assert np.array_equal(out.values().view(np.uint64), want.view(np.uint64))
+    prob.close()
+
+
 # the mapped assembly's tiles of 1, 2, 4 and 8 nodes, shorter on a short grid
 @pytest.mark.parametrize("N,n,m,scheme,bnd", [
     (499, 18, 10, 0, 1), (997, 18, 10, 0, 2), (1001, 18, 10, 0, 0), (3201, 18, 10, 0, 2), (101, 12, 6, 0, 2),
