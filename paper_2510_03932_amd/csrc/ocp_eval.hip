@@ -80,6 +80,14 @@ __global__ __launch_bounds__(kBlock) void hess_kernel(KP P, const double *__rest
 // where N is one too every wavefront stores whole lines.  `scale`: null, or a
 // device double that multiplies every value (a backward pass).
 // ---------------------------------------------------------------------------
+// The boundary rows' values, by one workgroup.
+__device__ __forceinline__ void bnd_cons(const KP &P, const double *__restrict__ z, double *__restrict__ c,
+                                         const double *__restrict__ scale)
+{
+    const int b = threadIdx.x;
+    if (b < P.nb) c[(int64_t)P.n * P.N + b] = bnd_value(P, z, b) * (scale ? *scale : 1.0);
+}
+
 template <int NB, int MB>
 __global__ __launch_bounds__(kBlock) void cons_kernel(KP P, const double *__restrict__ z,
                                                       double *__restrict__ c, const double *__restrict__ scale)
@@ -89,7 +97,6 @@ __global__ __launch_bounds__(kBlock) void cons_kernel(KP P, const double *__rest
     const int64_t k = (int64_t)blockIdx.x * kSpan + tid;
     const int n = P.n;
     const int64_t N = P.N;
-    const double f = scale ? *scale : 1.0;
     double Pk[NB];
     if (k <= N) {
         double x[NB], F[NB];
@@ -104,16 +111,22 @@ __global__ __launch_bounds__(kBlock) void cons_kernel(KP P, const double *__rest
     }
     __syncthreads();
     if (tid < kSpan && k < N) {
+        const double f = scale ? *scale : 1.0;
 #pragma unroll
         for (int i = 0; i < NB; i++)
             if (i < n) st_nt(c + i * N + k, (Ms[i][tid + 1] - Pk[i]) * f);
     }
-    if (blockIdx.x == 0 && tid < P.nb) c[n * N + tid] = bnd_value(P, z, tid) * f;  // boundary rows
+    if (blockIdx.x == 0) bnd_cons(P, z, c, scale);
 }
 
 // ---------------------------------------------------------------------------
 // Forward-Euler defects: one lane per interval k < N,
 //   c_ik = (X_{i,k+1} - X_ik) - h F_i(k)  (paper Sec. 3).
+// The boundary rows have a workgroup of their own, the last: beside the defects
+// they and *scale, loaded ahead, cost the sums scalar registers (N = 4e5,
+// n = 32, m = 16 140 -> 135 us, n = 24, m = 10 103.8 -> 101.6; the trapezoidal
+// kernel shows no such loss, and at N = 1000, n = 24, m = 10 takes 22.6 us with
+// them beside the defects and 23.2 so).
 // ---------------------------------------------------------------------------
 template <int NB, int MB>
 __global__ __launch_bounds__(kBlock) void cons_euler_kernel(KP P, const double *__restrict__ z,
@@ -121,9 +134,11 @@ __global__ __launch_bounds__(kBlock) void cons_euler_kernel(KP P, const double *
                                                             const double *__restrict__ scale)
 {
     const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const double f = scale ? *scale : 1.0;
-    if (k < P.N) cons_euler_interval<NB, MB>(P, z, c, k, f);
-    if (k < P.nb) c[(int64_t)P.n * P.N + k] = bnd_value(P, z, (int)k) * f;  // boundary rows
+    if ((int64_t)blockIdx.x * kBlock >= P.N) {  // the workgroup of the boundary rows
+        bnd_cons(P, z, c, scale);
+        return;
+    }
+    if (k < P.N) cons_euler_interval<NB, MB>(P, z, c, k, scale);
 }
 
 template <int NB>
@@ -434,7 +449,7 @@ hipError_t launch_cons(const KP &P, const double *z, double *c, const double *sc
         else if (n <= 16) launch_cons_trap<16>(P, g, z, c, scale, stream);
         else launch_cons_trap<32>(P, g, z, c, scale, stream);
     } else {
-        const unsigned g = blocks_for(P.N, kBlock);
+        const unsigned g = blocks_for(P.N, kBlock) + (P.nb > 0);
         if (n <= 4) launch_cons_euler<4>(P, g, z, c, scale, stream);
         else if (n <= 8) launch_cons_euler<8>(P, g, z, c, scale, stream);
         else if (n <= 16) launch_cons_euler<16>(P, g, z, c, scale, stream);

@@ -55,7 +55,8 @@ __device__ __forceinline__ void cons_wave(const KP &P, const double *__restrict_
 // bound, as in dyn_node.)
 template <int NB, int MB = NB>
 __device__ __forceinline__ void cons_euler_interval(const KP &P, const double *__restrict__ z,
-                                                    double *__restrict__ c, int64_t k, double scale = 1.0)
+                                                    double *__restrict__ c, int64_t k,
+                                                    const double *__restrict__ scale = nullptr)
 {
     constexpr bool kEarly = NB <= 16;
     const int n = P.n;
@@ -66,11 +67,12 @@ __device__ __forceinline__ void cons_euler_interval(const KP &P, const double *_
         for (int i = 0; i < NB; i++) xn[i] = (i < n) ? z[i * N1 + k + 1] : 0.0;
     }
     dyn_node<NB, MB>(P, z, k, x, F);
+    const double f = scale ? *scale : 1.0;
 #pragma unroll
     for (int i = 0; i < NB; i++) {
         if (i < n) {
             const double next = kEarly ? xn[kEarly ? i : 0] : z[i * N1 + k + 1];
-            st_nt(c + i * N + k, __builtin_fma(-P.h, F[i], next - x[i]) * scale);
+            st_nt(c + i * N + k, __builtin_fma(-P.h, F[i], next - x[i]) * f);
         }
     }
 }

@@ -67,6 +67,24 @@ def test_quadrotor_fused_kkt_has_the_separate_calls_bits(ocp, N, bnd):
     prob.close()
 
 
+# the forward-Euler defects' boundary rows have a workgroup of their own, after
+# the 256 intervals of each of the others; also scaled, in a backward pass
+@pytest.mark.parametrize("N,n,m,bnd", [(1, 2, 1, 2), (255, 3, 1, 1), (256, 3, 1, 2), (257, 32, 4, 2), (512, 17, 9, 1),
+                                       (256, 5, 2, 0)])
+def test_euler_boundary_rows(ocp, N, n, m, bnd):
+    print(f"[routes] euler boundary N={N} n={n} m={m} bnd={bnd}", flush=True)
+    inst = synth.make_instance(N, n, m, seed=86, bnd=bnd, scheme=1)
+    prob = ocp.Problem.from_instance(inst, torch.device("cuda", 0))
+    z, y = _t(inst.z), _t(inst.y)
+    out = Guarded(prob.sizes["ncon"], 1)
+    prob.cons(z, out=out.out)
+    want, mu = oracle.cons_ex(inst, 1, bnd)
+    check_close(out.values(), want, mu, what="cons")
+    gy = prob.lagrangian_backward(z, y, 0.7, _t(np.array([-3.0])))[1].cpu().numpy()
+    assert np.array_equal(gy.view(np.uint64), (-3.0 * out.values()).view(np.uint64))
+    prob.close()
+
+
 # a batch's Jacobian tiles: one interval per lane (every instance within a
 # wavefront), one or two (even lengths, at any 8-byte offset), and whole lines
 # (from 40 MiB on)
