@@ -39,6 +39,7 @@
 #include "ocp_internal.h"
 #include "ocp_problem.h"
 #include "ocp_quad.h"
+#include "ocp_rules.h"
 #include "ocp_step_device.h"
 
 using namespace ocp;
@@ -609,8 +610,8 @@ __global__ __launch_bounds__(kBlock) void coef_final_kernel(KP P, const double *
 //   at U_lk  -wF (tB^T yt)_l,
 // q = (j-1) mod n being the row whose bilinear partner is j.  Workgroups
 // of kBlock nodes close kSpan intervals, as in the defect kernel: lane k publishes
-// Ft(k) in LDS for lane k-1, and node k's z-entries are written by the chunk
-// in which it is not the overlap node.  Every workgroup copies t from the
+// Ft(k) in LDS for lane k-1, and node k's z-entries are written by the one
+// workgroup that owns it (rules::owns_node).  Every workgroup copies t from the
 // caller's row-major arrays into zero-padded columns in LDS (the same region
 // later holds the exchange), so the call reads no coefficients of the handle.
 // ---------------------------------------------------------------------------
@@ -663,7 +664,7 @@ __global__ __launch_bounds__(kBlock) void coef_adjoint_kernel(KP P, const double
     if (gy && blockIdx.x == 0 && tid < P.nb) gy[(int64_t)n * N + tid] = 0.0;  // boundary rows
     __syncthreads();
     if (live) {
-        if (gz && (tid < kSpan || k == N)) {
+        if (gz && rules::owns_node(tid, k, N, kSpan)) {
             const double x_last = last_of<NB>(x, n), yt_last = last_of<NB>(yt, n);
 #pragma unroll
             for (int j = 0; j < NB; j++) {

@@ -63,6 +63,14 @@ inline JacPath quad_jac_path(int64_t N, uint64_t addr)
     return halves && bytes > 12 * kMiB ? kJacPair : kJacSingle;
 }
 
+// Whether lane `tid` of a workgroup that evaluates nodes k = b span + tid, of
+// which the next one's begin after `span`, stores node k: the last of N + 1
+// nodes is the overlap's first where the workgroups end with the intervals.
+constexpr bool owns_node(int tid, int64_t k, int64_t N, int span)
+{
+    return k <= N && (tid < span || (tid == span && k == N));
+}
+
 // LDS doubles of one defect-row tile of KT intervals of the fused KKT values (n
 // states, m controls, T Jacobian slots per row): states and cosines at KT+1
 // nodes, the rows' regularization, the scaled coefficients, the output row block.

@@ -25,6 +25,15 @@ int kkt_defect_kt_of(int64_t count, const int64_t *Ns, int n, int m, int T, int 
     return kkt_defect_kt(n, m, T, euler != 0, Ns, count);
 }
 
+// How often a grid of ceil(N / span) workgroups of `block` lanes stores each
+// of the N + 1 nodes.
+void node_owners(int64_t N, int block, int span, int *count)
+{
+    for (int64_t b = 0; b * span < N; b++)
+        for (int tid = 0; tid < block; tid++)
+            if (owns_node(tid, b * span + tid, N, span)) count[b * span + tid]++;
+}
+
 int batch_obj_grad_once_of(int64_t count, const int64_t *Ns)
 {
     return batch_obj_grad_once(std::vector<int64_t>(Ns, Ns + count));

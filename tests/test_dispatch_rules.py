@@ -137,6 +137,13 @@ def test_assembly_tile(rules, N, n, m, euler, lg):
     assert (T + 1) * 8 << lg <= 64 * 1024
 
 
+@pytest.mark.parametrize("N", [1, 15, 239, 240, 241, 254, 255, 256, 479, 480, 481, 495, 496, 1000])
+def test_one_workgroup_stores_a_node(rules, N):
+    count = np.zeros(N + 256, np.int32)
+    rules.node_owners(ctypes.c_int64(N), 256, 240, count.ctypes.data_as(ctypes.c_void_p))
+    assert np.array_equal(count[:N + 1], np.ones(N + 1)) and not count[N + 1:].any()
+
+
 def test_kernels_look_at_no_address():
     """Addresses become integers on the host only (line_pos, the Jacobian's
     path): in a kernel they cost the coefficients the scalar cache."""
