@@ -615,7 +615,14 @@ __global__ __launch_bounds__(kBlock) void coef_final_kernel(KP P, const double *
 // caller's row-major arrays into zero-padded columns in LDS (the same region
 // later holds the exchange), so the call reads no coefficients of the handle.
 // ---------------------------------------------------------------------------
-template <int NB>
+template <bool NT>
+__device__ __forceinline__ void st_adj(double *p, double v)
+{
+    if constexpr (NT) st_nt(p, v);
+    else *p = v;
+}
+
+template <int NB, bool NT>
 __global__ __launch_bounds__(kBlock) void coef_adjoint_kernel(KP P, const double *__restrict__ z,
                                                               const double *__restrict__ y,
                                                               const double *__restrict__ tA,
@@ -677,7 +684,7 @@ __global__ __launch_bounds__(kBlock) void coef_adjoint_kernel(KP P, const double
                     const double xm = (j == 0) ? x_last : x[(j + NB - 1) % NB];
                     const double ym = (j == 0) ? yt_last : yt[(j + NB - 1) % NB];
                     const double G = cos(x[j]) * s + yt[j] * cg[j] * xn + ym * cg[jm] * xm;
-                    st_nt(gz + j * N1 + k, -wF * G);
+                    st_adj<NT>(gz + j * N1 + k, -wF * G);
                 }
             }
             if (k < NU) {
@@ -685,7 +692,7 @@ __global__ __launch_bounds__(kBlock) void coef_adjoint_kernel(KP P, const double
                     double s = 0.0;
 #pragma unroll
                     for (int i = 0; i < NB; i++) s = __builtin_fma(yt[i], cB[l * NB + i], s);
-                    st_nt(gz + n * N1 + l * NU + k, -wF * s);
+                    st_adj<NT>(gz + n * N1 + l * NU + k, -wF * s);
                 }
             }
         }
@@ -728,7 +735,7 @@ __global__ __launch_bounds__(kBlock) void coef_adjoint_kernel(KP P, const double
         for (int i = 0; i < NB; i++) {
             if (i < n) {
                 const double v = euler ? -P.h * Ft[i] : -P.hh * (Ft[i] + lds[i * kBlock + tid + 1]);
-                st_nt(gy + i * N + k, v);
+                st_adj<NT>(gy + i * N + k, v);
             }
         }
     }
@@ -808,6 +815,22 @@ static int launch_lag_grad(const ocp_problem *p, const double *z, const double *
         default: hipLaunchKernelGGL(KERNEL<32>, grid, dim3(kBlock), 0, __VA_ARGS__); break;    \
         }                                                                                       \
     } while (0)
+
+template <bool NT>
+static void launch_coef_adjoint(const ocp_problem *p, const double *z, const double *y, const double *tA,
+                                const double *tB, const double *tg, double *gz, double *gy, hipStream_t stream)
+{
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(blocks_for(p->d.N, kSpan)), dim3(kBlock), 0, stream, p->kp, z, y, tA, tB, tg,
+                           gz, gy);
+    };
+    switch (nb_of(p->d.n)) {
+    case 4: launch(coef_adjoint_kernel<4, NT>); break;
+    case 8: launch(coef_adjoint_kernel<8, NT>); break;
+    case 16: launch(coef_adjoint_kernel<16, NT>); break;
+    default: launch(coef_adjoint_kernel<32, NT>); break;
+    }
+}
 
 // The first pass of the Lagrangian's value for the state bound NB: the
 // controls' register bound is halved when m <= NB / 2, as for the defects, and
@@ -972,8 +995,10 @@ int ocp_eval_coef_adjoint(const ocp_problem *p, const double *z, const double *y
     if (int rc = check_coefficients(p, fn)) return rc;
     if (!z || !y || !tA || !tgamma || (p->d.m > 0 && !tB)) return fail(OCP_ERR_ARG, std::string(fn) + ": null array");
     if (!gz && !gy) return fail(OCP_ERR_ARG, std::string(fn) + ": no output (gz and gy are both NULL)");
-    OCP_DISPATCH_NB(p->d.n, coef_adjoint_kernel, dim3(blocks_for(p->d.N, kSpan)), stream, p->kp, z, y, tA, tB,
-                    tgamma, gz, gy);
+    if (rules::adjoint_nt((gz ? p->d.nvar : 0) + (gy ? p->d.ncon : 0)))
+        launch_coef_adjoint<true>(p, z, y, tA, tB, tgamma, gz, gy, stream);
+    else
+        launch_coef_adjoint<false>(p, z, y, tA, tB, tgamma, gz, gy, stream);
     return check_launch(fn);
 }
 

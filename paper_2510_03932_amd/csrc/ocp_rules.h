@@ -71,6 +71,13 @@ constexpr bool owns_node(int tid, int64_t k, int64_t N, int span)
     return k <= N && (tid < span || (tid == span && k == N));
 }
 
+// Whether the adjoint of the coefficient gradient stores its `values` doubles
+// past the caches: from 8 MiB on (n = 8, N = 100,000: 16.2 -> 13.5 us, n = 16,
+// N = 1e6 258 -> 236, n = 12, N = 333,333 52.2 -> 50.8); a short call waits
+// longer for such stores (n = 2, N = 1000 4.4 -> 4.6 us, n = 4, N = 50,001 6.7 ->
+// 7.0, n = 8, N = 20,000 11.1 -> 11.4).
+constexpr bool adjoint_nt(int64_t values) { return values * 8 > 8 * kMiB; }
+
 // LDS doubles of one defect-row tile of KT intervals of the fused KKT values (n
 // states, m controls, T Jacobian slots per row): states and cosines at KT+1
 // nodes, the rows' regularization, the scaled coefficients, the output row block.

@@ -25,6 +25,8 @@ int kkt_defect_kt_of(int64_t count, const int64_t *Ns, int n, int m, int T, int 
     return kkt_defect_kt(n, m, T, euler != 0, Ns, count);
 }
 
+int adjoint_nt_of(int64_t values) { return adjoint_nt(values); }
+
 // How often a grid of ceil(N / span) workgroups of `block` lanes stores each
 // of the N + 1 nodes.
 void node_owners(int64_t N, int block, int span, int *count)

@@ -144,6 +144,12 @@ def test_one_workgroup_stores_a_node(rules, N):
     assert np.array_equal(count[:N + 1], np.ones(N + 1)) and not count[N + 1:].any()
 
 
+@pytest.mark.parametrize("N,n,m,nt", [(1000, 2, 1, 0), (50001, 4, 2, 0), (20000, 8, 4, 0), (100000, 8, 4, 1),
+                                      (333333, 12, 5, 1), (1, 1, 0, 0)])
+def test_adjoint_stores(rules, N, n, m, nt):
+    assert rules.adjoint_nt_of(ctypes.c_int64(n * (N + 1) + m * (N + 1) + n * N)) == nt
+
+
 def test_kernels_look_at_no_address():
     """Addresses become integers on the host only (line_pos, the Jacobian's
     path): in a kernel they cost the coefficients the scalar cache."""

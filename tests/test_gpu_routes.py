@@ -85,6 +85,29 @@ def test_euler_boundary_rows(ocp, N, n, m, bnd):
     prob.close()
 
 
+# the adjoint of the coefficient gradient stores 8 MiB and less through the
+# caches; both outputs, and each alone, which may take the other kernel
+@pytest.mark.parametrize("N,n,m,scheme,bnd", [
+    (149000, 3, 1, 0, 1), (150241, 3, 1, 0, 2), (62005, 8, 1, 1, 1), (33360, 16, 0, 0, 0), (15615, 32, 4, 0, 2),
+    (239, 2, 2, 0, 2), (495, 20, 1, 0, 1)])
+def test_coefficient_adjoint_stores(ocp, N, n, m, scheme, bnd):
+    print(f"[routes] coefficient adjoint N={N} n={n} m={m} scheme={scheme} bnd={bnd}", flush=True)
+    inst = synth.make_instance(N, n, m, seed=87, bnd=bnd, scheme=scheme)
+    prob = ocp.Problem.from_instance(inst, torch.device("cuda", 0))
+    z, y = _t(inst.z), _t(inst.y)
+    rng = np.random.default_rng(8)
+    t = [rng.normal(size=shape) for shape in ((n, n), (n, m), (n,))]
+    outs = [Guarded(prob.sizes[k], 3) for k in ("nvar", "ncon")]
+    prob.coef_adjoint(z, y, *(_t(a) for a in t), out_z=outs[0].out, out_y=outs[1].out)
+    (oz, oy), (mz, my) = oracle.coef_adjoint_ex(inst, *t, scheme, bnd)
+    check_close(outs[0].values(), oz, mz, what="z")
+    check_close(outs[1].values(), oy, my, what="y")
+    for i in (0, 1):
+        alone = prob.coef_adjoint(z, y, *(_t(a) for a in t), want_z=i == 0, want_y=i == 1)[i]
+        assert torch.equal(alone.view(torch.int64), outs[i].out.view(torch.int64))
+    prob.close()
+
+
 # a batch's Jacobian tiles: one interval per lane (every instance within a
 # wavefront), one or two (even lengths, at any 8-byte offset), and whole lines
 # (from 40 MiB on)
