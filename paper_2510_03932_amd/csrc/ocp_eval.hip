@@ -227,7 +227,7 @@ __global__ __launch_bounds__(kBlock) void assemble_kernel(
     const int32_t *__restrict__ rowptr, const double *__restrict__ jv,
     const double *__restrict__ hv, const double *__restrict__ reg, double *__restrict__ kkt)
 {
-    extern __shared__ double tile[];
+    extern __shared__ __align__(16) double tile[];
     __shared__ int filled;
     const int64_t N = P.N, N1 = P.N1;
     const int64_t nvar = (int64_t)P.n * N1 + (int64_t)P.m * P.NU;
@@ -247,6 +247,12 @@ __global__ __launch_bounds__(kBlock) void assemble_kernel(
         // to bounds-checked direct stores)
         const bool staged = ext >= 0 && ext <= cap && base >= 0 && (int64_t)base + ext <= (int64_t)nnzk;
         if (threadIdx.x == 0) filled = 0;
+        // Zeros first (up to 2 % of the call): a map that names a slot twice
+        // and another of the range never has the right count all the same, and
+        // must not store what the LDS held.  An odd ext leaves room for its
+        // pair: cap is even.
+        if (staged)
+            for (int x = 2 * threadIdx.x; x < ext; x += 2 * kBlock) *reinterpret_cast<dbl2 *>(tile + x) = dbl2{0.0, 0.0};
         __syncthreads();
         const int64_t e0 = (int64_t)i * T * N + k0;
         // Visit every (slot, value) of the tile; `put` decides where it goes.

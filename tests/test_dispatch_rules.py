@@ -150,6 +150,16 @@ def test_adjoint_stores(rules, N, n, m, nt):
     assert rules.adjoint_nt_of(ctypes.c_int64(n * (N + 1) + m * (N + 1) + n * N)) == nt
 
 
+def test_assembly_clears_its_tile():
+    """A slot map that names a slot twice is outside the contract, so no test
+    runs one; the tile's places that it leaves empty have to be zeros all the
+    same, not what the LDS held."""
+    src = open(os.path.join(ROOT, "paper_2510_03932_amd", "csrc", "ocp_eval.hip")).read()
+    kernel = src[src.index("void assemble_kernel("):]
+    clear, barrier, put = (kernel.find(s) for s in ("(tile + x) = dbl2{0.0, 0.0}", "__syncthreads()", "tile[loc] = v"))
+    assert 0 < clear < barrier < put
+
+
 def test_kernels_look_at_no_address():
     """Addresses become integers on the host only (line_pos, the Jacobian's
     path): in a kernel they cost the coefficients the scalar cache."""
