@@ -225,9 +225,11 @@ int ocp_assemble_kkt(const ocp_problem *p, const int32_t *perm_j, const int32_t 
  * ocp_build_kkt and the same reg) would produce, written straight into kkt
  * (nnzk doubles, device, the layout of ocp_build_kkt), without the COO value
  * arrays.  This is what an interior-point iteration factorizes (Sec. 6); the
- * matrix is written once.  Same expressions as the separate calls.  Supports
- * the synthetic family under either scheme and any boundary option, and the
- * quadrotor model (the layout of ocp_quad_kkt). */
+ * matrix is written once.  The quadrotor's values are those of the separate
+ * calls bit for bit, the synthetic family's up to the last bit of a Jacobian
+ * entry that sums two products.  Supports the synthetic family under either
+ * scheme and any boundary option, and the quadrotor model (the layout of
+ * ocp_quad_kkt). */
 int ocp_eval_kkt(const ocp_problem *p, const double *z, const double *y, double sigma, const double *reg,
                  double *kkt, hipStream_t stream);
 
@@ -519,8 +521,8 @@ typedef struct ocp_graph ocp_graph;
 /* Tile shape of the persistent launch. */
 typedef struct ocp_batch_config {
     int32_t block;        /* threads per workgroup: 128 or 256 */
-    int32_t pair;         /* 1: Jacobian lanes take two intervals, stored in whole 128-byte
-                             lines, for instances whose slot rows do not all begin on one; 0: one */
+    int32_t pair;         /* 1: Jacobian lanes take two intervals where that pays (instances of
+                             even length, or slot rows stored in whole 128-byte lines); 0: one */
     int32_t wgs_per_cu;   /* persistent workgroups per compute unit, 1..32; 0: one
                              workgroup per tile (the loop over tiles runs once; the
                              defect tiles loop, 16 workgroups per unit) */
@@ -534,7 +536,7 @@ typedef struct ocp_batch_config {
  * gamma: count x n, q: count x n, r: count x m, all host, instance-major and
  * row-major within an instance (B and r may be NULL when m = 0).  Copies the
  * coefficients to the device, builds the offset table and the tile list of
- * the default configuration {256, 1, 8}.
+ * the default configuration {256, 1, 0, 1}.
  * Errors: OCP_ERR_ARG (count < 1, bad N_b, n, m or pointers), OCP_ERR_OVERFLOW
  * (an instance's sizes do not fit int32), OCP_ERR_ALLOC, OCP_ERR_HIP. */
 int ocp_batch_create(int32_t count, const int64_t *Ns, int32_t n, int32_t m, const double *A,

@@ -9,11 +9,13 @@
 // w, w + G, w + 2G, ... (G = grid size), so every wave reaches the end of the
 // list and exits, and the assignment is fixed (no queue).  A tile is
 // (instance, first interval or node, kind): a Jacobian column over `block`
-// intervals (or 2 `block` - 16 stored in whole lines), a Hessian or
-// variable-row KKT run of `block` nodes, a defect run of 63 intervals per
-// wavefront, the objective and gradient of 256 nodes, a defect-row KKT run of
-// 16-64 intervals, or an instance's boundary rows.  One list per evaluation mask, instance-major (an instance's
-// tiles together, so the workgroups in flight share the state rows they read).
+// intervals (2 `block` with two per lane, 2 `block` - 16 stored in whole lines;
+// rules::batch_jac), a Hessian or variable-row KKT run of `block` nodes, a
+// defect run of 63 intervals per wavefront, the objective, the gradient or both
+// of 256 nodes (rules::batch_obj_grad_once), a defect-row KKT run of 16 to 64
+// intervals (rules::kkt_defect_kt), or an instance's boundary rows.  One list
+// per evaluation mask, instance-major (an instance's tiles together, so the
+// workgroups in flight share the state rows they read).
 // The per-lane arithmetic is the single-instance path's (ocp_device.h,
 // ocp_step_device.h): the values are bitwise those of per-instance
 // evaluation, for any tile shape.
@@ -485,15 +487,15 @@ static void launch_batch_scheme(const ocp_batch *b, const TileDesc *tiles, int n
                            : 0;
     // where the array of the Jacobian or KKT tiles begins in its line
     const int al = line_pos(KINDS & (OCP_EVAL_JAC | kJacDirect) ? io.jac : io.kkt);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, al, io.z,
+                           io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
+    };
     const int n = b->n;
-    if (n <= 4)
-        hipLaunchKernelGGL((batch_kernel<4, BS, KINDS, SCHEME>), dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, al, io.z, io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
-    else if (n <= 8)
-        hipLaunchKernelGGL((batch_kernel<8, BS, KINDS, SCHEME>), dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, al, io.z, io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
-    else if (n <= 16)
-        hipLaunchKernelGGL((batch_kernel<16, BS, KINDS, SCHEME>), dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, al, io.z, io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
-    else
-        hipLaunchKernelGGL((batch_kernel<32, BS, KINDS, SCHEME>), dim3(grid), dim3(BS), lds, s, b->bp, b->Lo, b->inst, tiles, ntiles, what, al, io.z, io.y, io.reg, io.sigma, io.grad, io.cons, io.jac, io.hess, io.kkt, io.parts);
+    if (n <= 4) launch(batch_kernel<4, BS, KINDS, SCHEME>);
+    else if (n <= 8) launch(batch_kernel<8, BS, KINDS, SCHEME>);
+    else if (n <= 16) launch(batch_kernel<16, BS, KINDS, SCHEME>);
+    else launch(batch_kernel<32, BS, KINDS, SCHEME>);
 }
 
 template <int BS, int KINDS>

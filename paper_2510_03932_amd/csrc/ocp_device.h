@@ -25,7 +25,6 @@ namespace dev {
 
 typedef double dbl2 __attribute__((ext_vector_type(2)));
 typedef double d4 __attribute__((ext_vector_type(4)));  // FP64 MFMA 16x16 accumulator
-typedef int32_t int2v __attribute__((ext_vector_type(2)));
 
 // pairs loaded from any element of an array
 typedef double dbl2_any __attribute__((ext_vector_type(2), aligned(8)));

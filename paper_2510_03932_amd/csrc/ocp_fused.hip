@@ -6,12 +6,14 @@
 // the state rows, y and reg in, the KKT values out (about 7 GB at N = 1e6,
 // n = 16, m = 8, against 23 GB for eval_jac + eval_hess + assemble_kkt).
 //
-// The values are computed with the same expressions, in the same order, as
-// the COO kernels and the assembly.  The tile bodies (ocp_step_device.h) are
-// shared with the batched evaluation.
+// The values are the COO kernels' and the assembly's, except that the defect
+// rows round each product of a state's partial derivative before it is added
+// (defect_column), where the COO kernels fuse one into the sum: an entry at a
+// row's own state or its bilinear partner may differ in the last bit.  The tile
+// bodies (ocp_step_device.h) are shared with the batched evaluation.
 //
 // Defect rows: a workgroup owns KT = 16, 32 or 64 consecutive intervals
-// (kkt_defect_kt); each XCD takes a contiguous run of the tiles, so that the
+// (rules::kkt_defect_kt); each XCD takes a contiguous run of the tiles, so that the
 // lines neighbouring tiles share (states read, rows stored) meet in one L2.
 // It stages the states and their cosines at the KT+1 nodes, the rows'
 // regularization and the scaled coefficients -hh A, -hh B, -hh gamma in LDS
