@@ -106,7 +106,7 @@ __device__ __forceinline__ double jac_partial(int q, const Trig &t, const double
 {
 #pragma clang fp contract(off)
     const double p = __builtin_fma(u[1], t.c7, u[2] * t.s7);
-    const double w = __builtin_fma(-u[1], t.s7, u[2] * t.c7);
+    const double w = __builtin_fma(u[2], t.c7, -(u[1] * t.s7));
     switch (q) {
     case 3: return u[0] * __builtin_fma(t.c7, t.s9, -(t.s7 * t.s8 * t.c9));
     case 5: return u[0] * __builtin_fma(t.s7, t.c9, -(t.c7 * t.s8 * t.s9));
@@ -117,7 +117,7 @@ __device__ __forceinline__ double jac_partial(int q, const Trig &t, const double
     case 20: return w * t.sec;
     case 21: return p * t.s8 * t.sec2;
     case 24: return -p;
-    case 28: return __builtin_fma(u[2], t.c7, -(u[1] * t.s7)) * t.t8;  // w with its other product rounded
+    case 28: return w * t.t8;
     case 29: return p * t.sec2;
     default: return partial(q, t, u);  // products and constants
     }

@@ -4,6 +4,8 @@ bit for bit against another route; the elements around an output stay
 untouched."""
 from __future__ import annotations
 
+from fractions import Fraction
+
 import numpy as np
 import pytest
 
@@ -105,6 +107,37 @@ def test_coefficient_adjoint_stores(ocp, N, n, m, scheme, bnd):
     for i in (0, 1):
         alone = prob.coef_adjoint(z, y, *(_t(a) for a in t), want_z=i == 0, want_y=i == 1)[i]
         assert torch.equal(alone.view(torch.int64), outs[i].out.view(torch.int64))
+    prob.close()
+
+
+def _fma(a, b, c):
+    """a b + c of doubles, rounded once."""
+    return np.array([float(Fraction(x) * Fraction(y) + Fraction(w)) for x, y, w in zip(a, b, c)])
+
+
+@pytest.mark.parametrize("N", [1, 64, 4096])
+def test_quadrotor_roll_rate_rounding(ocp, N):
+    """d x7' / d x7 = (u3 cos x7 - u2 sin x7) sec x8: the second product is
+    rounded, the first fused into the difference.  At x8 = 0 (sec = 1) and a
+    step that is a power of two, the sine and cosine that the kernel used stand
+    in other entries, so the values follow bit for bit."""
+    print(f"[routes] quadrotor roll rate N={N}", flush=True)
+    q = synth.make_quadrotor(N, seed=88, bnd=0)
+    prob = ocp.QuadrotorProblem.from_instance(q, torch.device("cuda", 0))
+    rng = np.random.default_rng(9)
+    z = np.array(q.z)
+    z[:9 * (N + 1)].reshape(9, N + 1)[7] = 0.0
+    z[:9 * (N + 1)].reshape(9, N + 1)[6] = rng.uniform(-1.5, 1.5, N + 1)
+    u2, u3 = z[9 * (N + 1):].reshape(4, N + 1)[1:3]
+    u2[:], u3[:] = rng.uniform(-2, 2, (2, N + 1))
+    slot = prob.jac(_t(z)).cpu().numpy().reshape(68, N)
+    hh = -slot[66][0]  # d x9' / d u4 = 1
+    assert np.log2(hh) == np.round(np.log2(hh))
+    for side in (0, 1):  # node k, node k + 1 of the intervals
+        s7, c7 = slot[52 + side] / hh, -slot[54 + side] / hh
+        a, b = u2[side:N + side], u3[side:N + side]
+        want = _fma(np.full(N, -hh), _fma(b, c7, -(a * s7)), np.full(N, 2.0 * side - 1.0))
+        assert np.array_equal(slot[40 + side].view(np.uint64), want.view(np.uint64))
     prob.close()
 
 
