@@ -197,12 +197,13 @@ inline int assembly_lg(int64_t N, int n, int T)
 
 // log2 of the nodes per tile of the mapped assembly, for N1 nodes of `per_node`
 // entries (and 2 n that overhang): as many as fit 16 KiB of values, 32 KiB
-// (five workgroups per CU) where that leaves two tiles per CU, and up to 8
-// nodes (half a line of values) in 72 KiB while the tiles still reach every
-// CU.  n = 18, m = 10: 16.9 us with 8 nodes and 20.5 with 4 at N = 4000, 12.7
-// and 11.0 at N = 2000, 10.1 with 8, 6.4 with 4 and 4.4 with one at N = 100;
-// n = 32, m = 32: 17.2 with 2 nodes and 23.1 with one at N = 500, 10.5 and 8.1
-// at N = 50.
+// (five workgroups per CU) where that leaves two tiles per CU, 4 nodes while
+// those fit 62 KiB, and up to 8 (half a line of values) in 72 KiB while 250
+// tiles are left, 400 with 8 nodes, to reach every CU.  n = 18, m = 10: 16.9 us
+// with 8 nodes and 20.5 with 4 at N = 4000, 12.7 and 11.0 at N = 2000, 10.1 and
+// 6.4 at N = 100.  Fewer than 4 nodes would gain on the shortest grids (n = 18,
+// N = 100: one node 4.4 us), but a plan that a caller kept from a library with
+// tiles of 4 would be too short for them, and its length is not passed.
 constexpr int kMapCap = 9216;  // most values staged per workgroup (72 KiB, two workgroups per CU)
 inline int map_lg(int64_t N1, int64_t per_node, int n)
 {
@@ -211,6 +212,7 @@ inline int map_lg(int64_t N1, int64_t per_node, int n)
     while (lg < 10 && need(lg + 1) <= 2048) lg++;
     const bool many = (N1 >> (lg + 1)) >= 512;
     while (many && lg < 10 && need(lg + 1) <= 4096) lg++;
+    while (lg < 2 && need(lg + 1) <= 7936) lg++;
     while (lg < 3 && need(lg + 1) <= kMapCap && (N1 >> (lg + 1)) >= (lg < 2 ? 250 : 400)) lg++;
     return lg;
 }

@@ -110,10 +110,10 @@ def test_batched_objective_and_gradient_tiles(rules, count, N, once):
 
 
 @pytest.mark.parametrize("N,n,m,euler,lg", [
-    # short grids: tiles small enough to reach every CU
-    (50, 18, 10, 0, 0), (100, 18, 10, 1, 1), (500, 18, 10, 0, 1), (1000, 18, 10, 0, 2), (2000, 18, 10, 0, 2),
-    (100, 12, 6, 0, 2), (2000, 12, 6, 0, 2), (100, 8, 4, 0, 3), (1, 1, 0, 0, 8), (100, 24, 12, 1, 1),
-    (50, 32, 32, 0, 0), (100, 32, 32, 1, 0),
+    # short grids: tiles no taller than 4 nodes, and 16 KiB
+    (50, 18, 10, 0, 2), (100, 18, 10, 1, 2), (500, 18, 10, 0, 2), (1000, 18, 10, 0, 2), (2000, 18, 10, 0, 2),
+    (100, 12, 6, 0, 2), (2000, 12, 6, 0, 2), (100, 8, 4, 0, 3), (1, 1, 0, 0, 8), (100, 24, 12, 1, 2),
+    (50, 32, 32, 0, 0), (100, 32, 32, 1, 1), (499, 32, 20, 0, 1),
     # long ones: half a line of values per slot row, as far as 72 KiB go
     (4000, 18, 10, 0, 3), (3500, 12, 6, 0, 3), (500, 32, 32, 0, 1), (100000, 8, 4, 0, 4), (100000, 32, 32, 0, 1),
     (100000, 32, 32, 1, 2), (1000000, 2, 1, 0, 7), (100000, 1, 0, 1, 8)])
@@ -123,6 +123,21 @@ def test_mapped_assembly_tile(rules, N, n, m, euler, lg):
     per_node = n * slots + n + pairs + m + n
     assert rules.map_lg_of(N + 1, per_node, n) == lg
     assert (per_node << lg) + 2 * n <= 9216
+
+
+def test_mapped_assembly_tiles_never_shrink(rules):
+    """A caller may hold a plan made when the tiles were as many nodes as fit
+    2048 values, at least 4 while those fit 7936: it has an entry for every
+    tile as long as no tile is shorter than that."""
+    for N in (1, 50, 300, 999, 4000, 100000):
+        for per_node in list(range(4, 300, 7)) + list(range(300, 5000, 53)):
+            n = min(32, max(1, per_node // 30))
+            lg = 0
+            while lg < 10 and (per_node << (lg + 1)) + 2 * n <= 2048:
+                lg += 1
+            while lg < 2 and (per_node << (lg + 1)) + 2 * n <= 7936:
+                lg += 1
+            assert rules.map_lg_of(N + 1, per_node, n) >= lg
 
 
 @pytest.mark.parametrize("N,n,m,euler,lg", [
